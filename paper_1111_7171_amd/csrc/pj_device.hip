@@ -16,55 +16,6 @@
 
 namespace pj {
 
-// ------------------------------------------------------------------------------------------
-// Wave / block primitives (wave64, 256-thread blocks)
-// ------------------------------------------------------------------------------------------
-
-constexpr int kBlock = 256;
-constexpr int kWaves = kBlock / 64;
-
-template <typename T>
-__device__ inline T wave_incl_scan(T v)
-{
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        T t = __shfl_up(v, d, 64);
-        if (lane >= d) v += t;
-    }
-    return v;
-}
-
-template <typename T>
-__device__ inline T wave_sum(T v)
-{
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-    return v;
-}
-
-// Exclusive scan over the 256 threads of a block; *total receives the block sum.
-template <typename T>
-__device__ inline T block_excl_scan(T v, T* s_wave, T* total)
-{
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    T inc = wave_incl_scan(v);
-    if (lane == 63) s_wave[w] = inc;
-    __syncthreads();
-    T off = 0, tot = 0;
-#pragma unroll
-    for (int k = 0; k < kWaves; ++k) {
-        T s = s_wave[k];
-        if (k < w) off += s;
-        tot += s;
-    }
-    __syncthreads();
-    *total = tot;
-    return off + inc - v;
-}
-
-__device__ inline uint64_t lanemask_lt() { return (1ull << (threadIdx.x & 63)) - 1ull; }
-
 // Wave-private append buffer in LDS: lanes push items without touching global atomics; the
 // wave reserves space in the global output with one atomic per flush (a single-address device
 // atomic is serialised across all XCDs, so one per item would throttle the kernel).  `buf`
@@ -100,244 +51,6 @@ struct WaveAppender {
 };
 
 constexpr int kAppendCap = 256;
-
-// ------------------------------------------------------------------------------------------
-// Device-wide exclusive scan (reduce -> scan partials -> apply), 2048 elements per block
-// ------------------------------------------------------------------------------------------
-
-constexpr int kScanItems = 8;
-constexpr int kScanTile = kBlock * kScanItems;
-
-template <typename TI, typename TO>
-__global__ __launch_bounds__(kBlock) void k_scan_reduce(const TI* __restrict__ in, uint64_t n,
-                                                        TO* __restrict__ partial)
-{
-    __shared__ TO s_wave[kWaves];
-    const uint64_t base = (uint64_t)blockIdx.x * kScanTile + (uint64_t)threadIdx.x * kScanItems;
-    TO sum = 0;
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k)
-        if (base + k < n) sum += (TO)in[base + k];
-    TO tot;
-    block_excl_scan<TO>(sum, s_wave, &tot);
-    if (threadIdx.x == 0) partial[blockIdx.x] = tot;
-}
-
-template <typename TO>
-__global__ __launch_bounds__(kBlock) void k_scan_partials(TO* __restrict__ partial, uint64_t nb)
-{
-    __shared__ TO s_wave[kWaves];
-    __shared__ TO s_carry;
-    if (threadIdx.x == 0) s_carry = 0;
-    __syncthreads();
-    for (uint64_t c = 0; c < nb; c += kBlock) {
-        uint64_t k = c + threadIdx.x;
-        TO v = (k < nb) ? partial[k] : 0;
-        TO tot;
-        TO ex = block_excl_scan<TO>(v, s_wave, &tot);
-        TO carry = s_carry;
-        if (k < nb) partial[k] = carry + ex;
-        __syncthreads();
-        if (threadIdx.x == 0) s_carry = carry + tot;
-        __syncthreads();
-    }
-}
-
-template <typename TI, typename TO>
-__global__ __launch_bounds__(kBlock) void k_scan_apply(const TI* __restrict__ in, TO* __restrict__ out,
-                                                       uint64_t n, const TO* __restrict__ partial)
-{
-    __shared__ TO s_wave[kWaves];
-    const uint64_t base = (uint64_t)blockIdx.x * kScanTile + (uint64_t)threadIdx.x * kScanItems;
-    TO v[kScanItems];
-    TO sum = 0;
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        v[k] = (base + k < n) ? (TO)in[base + k] : 0;
-        sum += v[k];
-    }
-    TO tot;
-    TO run = block_excl_scan<TO>(sum, s_wave, &tot) + partial[blockIdx.x];
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        if (base + k < n) out[base + k] = run;
-        run += v[k];
-    }
-    // the thread holding the last element writes the total
-    if (n > 0 && base <= n - 1 && n - 1 < base + kScanItems) out[n] = run;
-}
-
-size_t scan_tmp_bytes(uint64_t n)
-{
-    uint64_t nb = (n + kScanTile - 1) / kScanTile;
-    return (size_t)(nb + 1) * sizeof(unsigned long long);
-}
-
-template <typename TO>
-__global__ void k_zero_one(TO* __restrict__ out)
-{
-    if (threadIdx.x == 0) *out = 0;
-}
-
-template <typename TI, typename TO>
-static hipError_t scan_impl(const TI* in, TO* out, uint64_t n, void* tmp, size_t tmp_bytes,
-                            hipStream_t s)
-{
-    if (n == 0) {
-        // a kernel, not a memset, so that the call can be captured in a graph
-        hipLaunchKernelGGL((k_zero_one<TO>), dim3(1), dim3(64), 0, s, out);
-        return hipGetLastError();
-    }
-    uint64_t nb = (n + kScanTile - 1) / kScanTile;
-    if (tmp_bytes < (nb + 1) * sizeof(TO)) return hipErrorInvalidValue;
-    TO* partial = (TO*)tmp;
-    hipLaunchKernelGGL((k_scan_reduce<TI, TO>), dim3((unsigned)nb), dim3(kBlock), 0, s, in, n, partial);
-    hipLaunchKernelGGL((k_scan_partials<TO>), dim3(1), dim3(kBlock), 0, s, partial, nb);
-    hipLaunchKernelGGL((k_scan_apply<TI, TO>), dim3((unsigned)nb), dim3(kBlock), 0, s, in, out, n,
-                       (const TO*)partial);
-    return hipGetLastError();
-}
-
-hipError_t scan_u32_to_u32(const uint32_t* in, uint32_t* out, uint64_t n, void* tmp,
-                           size_t tmp_bytes, hipStream_t s)
-{
-    return scan_impl<uint32_t, uint32_t>(in, out, n, tmp, tmp_bytes, s);
-}
-
-hipError_t scan_u32_to_u64(const uint32_t* in, unsigned long long* out, uint64_t n, void* tmp,
-                           size_t tmp_bytes, hipStream_t s)
-{
-    return scan_impl<uint32_t, unsigned long long>(in, out, n, tmp, tmp_bytes, s);
-}
-
-// ------------------------------------------------------------------------------------------
-// Stable LSD radix sort, 8-bit digits.  A block owns a tile of 16 rounds x 256 keys; within a
-// round, keys with equal digits are ranked by wave ballots (8 ballots per key find its peers)
-// and across waves/rounds by LDS counters, so every pass is stable.
-// ------------------------------------------------------------------------------------------
-
-constexpr int kRadixRounds = 16;
-constexpr int kRadixTile = kBlock * kRadixRounds;
-
-template <typename K>
-__global__ __launch_bounds__(kBlock) void k_radix_hist(const K* __restrict__ keys, uint64_t n,
-                                                       int shift, uint32_t* __restrict__ hist,
-                                                       uint32_t nblocks)
-{
-    __shared__ uint32_t cnt[256];
-    cnt[threadIdx.x] = 0;
-    __syncthreads();
-    const uint64_t base = (uint64_t)blockIdx.x * kRadixTile;
-#pragma unroll 4
-    for (int r = 0; r < kRadixRounds; ++r) {
-        uint64_t idx = base + (uint64_t)r * kBlock + threadIdx.x;
-        if (idx < n) atomicAdd(&cnt[(uint32_t)(keys[idx] >> shift) & 255u], 1u);
-    }
-    __syncthreads();
-    hist[(uint64_t)threadIdx.x * nblocks + blockIdx.x] = cnt[threadIdx.x];
-}
-
-template <typename K>
-__global__ __launch_bounds__(kBlock) void k_radix_scatter(const K* __restrict__ keys,
-                                                          const uint32_t* __restrict__ vals,
-                                                          uint64_t n, int shift,
-                                                          const uint32_t* __restrict__ offsets,
-                                                          uint32_t nblocks,
-                                                          K* __restrict__ keys_out,
-                                                          uint32_t* __restrict__ vals_out)
-{
-    __shared__ uint32_t cnt[256];
-    __shared__ uint32_t wcnt[kWaves][256];
-    const int w = threadIdx.x >> 6;
-    cnt[threadIdx.x] = offsets[(uint64_t)threadIdx.x * nblocks + blockIdx.x];
-#pragma unroll
-    for (int k = 0; k < kWaves; ++k) wcnt[k][threadIdx.x] = 0;
-    __syncthreads();
-    const uint64_t base = (uint64_t)blockIdx.x * kRadixTile;
-    for (int r = 0; r < kRadixRounds; ++r) {
-        uint64_t idx = base + (uint64_t)r * kBlock + threadIdx.x;
-        bool valid = idx < n;
-        K key = valid ? keys[idx] : (K)0;
-        uint32_t d = (uint32_t)(key >> shift) & 255u;
-        uint64_t peers = __ballot(valid);
-#pragma unroll
-        for (int bit = 0; bit < 8; ++bit) {
-            uint64_t bb = __ballot((d >> bit) & 1u);
-            peers &= ((d >> bit) & 1u) ? bb : ~bb;
-        }
-        uint32_t rank = (uint32_t)__popcll(peers & lanemask_lt());
-        bool leader = valid && ((peers & lanemask_lt()) == 0);
-        if (leader) wcnt[w][d] = (uint32_t)__popcll(peers);
-        __syncthreads();
-        if (valid) {
-            uint32_t pos = cnt[d] + rank;
-            for (int k = 0; k < w; ++k) pos += wcnt[k][d];
-            keys_out[pos] = key;
-            if (vals) vals_out[pos] = vals[idx];
-        }
-        __syncthreads();
-        uint32_t add = 0;
-#pragma unroll
-        for (int k = 0; k < kWaves; ++k) {
-            add += wcnt[k][threadIdx.x];
-            wcnt[k][threadIdx.x] = 0;
-        }
-        cnt[threadIdx.x] += add;
-        __syncthreads();
-    }
-}
-
-size_t radix_tmp_bytes(uint64_t n)
-{
-    uint64_t nb = (n + kRadixTile - 1) / kRadixTile;
-    uint64_t h = 256 * nb;
-    // histogram + its scan + scan partials
-    return (size_t)(2 * (h + 1)) * sizeof(uint32_t) + scan_tmp_bytes(h) + 256;
-}
-
-template <typename K>
-static hipError_t radix_impl(K* keys, uint32_t* vals, K* keys_alt, uint32_t* vals_alt,
-                             uint64_t n, int bits, void* tmp, size_t tmp_bytes, bool* in_alt,
-                             hipStream_t s)
-{
-    *in_alt = false;
-    if (n <= 1 || bits <= 0) return hipSuccess;
-    uint64_t nb = (n + kRadixTile - 1) / kRadixTile;
-    uint64_t h = 256 * nb;
-    if (tmp_bytes < radix_tmp_bytes(n)) return hipErrorInvalidValue;
-    uint32_t* hist = (uint32_t*)tmp;
-    uint32_t* offs = hist + (h + 1);
-    void* stmp = (void*)(offs + (h + 1));
-    size_t stmp_bytes = tmp_bytes - (size_t)(2 * (h + 1)) * sizeof(uint32_t);
-    K* kin = keys; uint32_t* vin = vals;
-    K* kout = keys_alt; uint32_t* vout = vals_alt;
-    for (int shift = 0; shift < bits; shift += 8) {
-        hipLaunchKernelGGL((k_radix_hist<K>), dim3((unsigned)nb), dim3(kBlock), 0, s, kin, n,
-                           shift, hist, (uint32_t)nb);
-        hipError_t e = scan_u32_to_u32(hist, offs, h, stmp, stmp_bytes, s);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_radix_scatter<K>), dim3((unsigned)nb), dim3(kBlock), 0, s, kin,
-                           vin, n, shift, offs, (uint32_t)nb, kout, vout);
-        K* tk = kin; kin = kout; kout = tk;
-        uint32_t* tv = vin; vin = vout; vout = tv;
-        *in_alt = !*in_alt;
-    }
-    return hipGetLastError();
-}
-
-hipError_t radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt,
-                          uint64_t n, int bits, void* tmp, size_t tmp_bytes, bool* in_alt,
-                          hipStream_t s)
-{
-    return radix_impl<uint64_t>(keys, vals, keys_alt, vals_alt, n, bits, tmp, tmp_bytes, in_alt, s);
-}
-
-hipError_t radix_sort_u32(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
-                          uint64_t n, int bits, void* tmp, size_t tmp_bytes, bool* in_alt,
-                          hipStream_t s)
-{
-    return radix_impl<uint32_t>(keys, vals, keys_alt, vals_alt, n, bits, tmp, tmp_bytes, in_alt, s);
-}
 
 // ------------------------------------------------------------------------------------------
 // String arena: length histogram + validation, (length, id) keys, packing
@@ -479,13 +192,6 @@ __global__ __launch_bounds__(kBlock) void k_emit_segments(const uint8_t* __restr
     vals[e] = (uint32_t)g;
 }
 
-__global__ __launch_bounds__(kBlock) void k_mark_heads(const uint64_t* __restrict__ keys, int64_t E,
-                                                       uint32_t* __restrict__ flags)
-{
-    int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (e < E) flags[e] = (e == 0 || keys[e] != keys[e - 1]) ? 1u : 0u;
-}
-
 // Inline copies of the list members' strings: entry j of the sorted index (length l, read from
 // its key's group) gets the bytes of string vals[j], in a slot of stride_of(l) bytes at
 // inl + inl_base[l] + j * stride_of(l).  Entries of one length are contiguous in the sorted
@@ -512,16 +218,6 @@ __global__ __launch_bounds__(kBlock) void k_clear_table(uint4* __restrict__ tabl
 {
     uint64_t k = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
     if (k < slots) table[k] = make_uint4(0xffffffffu, 0xffffffffu, 0u, 0u);
-}
-
-// runstart[r] = first entry of list r (runid[e] = number of list heads before e).
-__global__ __launch_bounds__(kBlock) void k_scatter_runstart(const uint32_t* __restrict__ flags,
-                                                             const uint32_t* __restrict__ runid,
-                                                             int64_t E,
-                                                             uint32_t* __restrict__ runstart)
-{
-    int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (e < E && flags[e]) runstart[runid[e]] = (uint32_t)e;
 }
 
 // One thread per list: inserts key -> (start, count) into the table by linear probing.
@@ -2343,28 +2039,6 @@ __global__ __launch_bounds__(kBlock) void k_pairs_to_keys(const uint64_t* __rest
     keys[k] = ((uint64_t)a << bbits) | b;
 }
 
-__global__ __launch_bounds__(kBlock) void k_unique_flags(const uint64_t* __restrict__ keys,
-                                                         uint64_t m, uint32_t* __restrict__ flags)
-{
-    uint64_t k = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (k < m) flags[k] = (k == 0 || keys[k] != keys[k - 1]) ? 1u : 0u;
-}
-
-__global__ __launch_bounds__(kBlock) void k_compact_pairs(const uint64_t* __restrict__ keys,
-                                                          const uint32_t* __restrict__ flags,
-                                                          const uint32_t* __restrict__ pos,
-                                                          uint64_t m, int bbits,
-                                                          int32_t* __restrict__ a,
-                                                          int32_t* __restrict__ b)
-{
-    uint64_t k = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (k < m && flags[k]) {
-        uint64_t v = keys[k];
-        a[pos[k]] = (int32_t)(v >> bbits);
-        b[pos[k]] = (int32_t)(v & ((1ull << bbits) - 1));
-    }
-}
-
 // out[g] = in[perm[g]]: per-id values (a query's tau) moved to sorted positions.
 __global__ __launch_bounds__(kBlock) void k_gather_i32(const int32_t* __restrict__ in,
                                                        const int32_t* __restrict__ perm, int64_t n,
@@ -2436,13 +2110,6 @@ hipError_t launch_emit_segments(const DevSet& S, int tau, const int64_t* ebase_d
     return hipGetLastError();
 }
 
-hipError_t launch_mark_heads(const uint64_t* keys, int64_t E, uint32_t* flags, hipStream_t s)
-{
-    if (E <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mark_heads, dim3(blocks_for(E)), dim3(kBlock), 0, s, keys, E, flags);
-    return hipGetLastError();
-}
-
 hipError_t launch_gather_inline(const DevSet& S, const uint64_t* keys, const uint32_t* vals,
                                 int64_t E, int tau, const int64_t* inl_base, uint8_t* inl,
                                 hipStream_t s)
@@ -2456,15 +2123,6 @@ hipError_t launch_gather_inline(const DevSet& S, const uint64_t* keys, const uin
 hipError_t launch_clear_table(uint4* table, uint64_t slots, hipStream_t s)
 {
     hipLaunchKernelGGL(k_clear_table, dim3(blocks_for(slots)), dim3(kBlock), 0, s, table, slots);
-    return hipGetLastError();
-}
-
-hipError_t launch_scatter_runstart(const uint32_t* flags, const uint32_t* runid, int64_t E,
-                                   uint32_t* runstart, hipStream_t s)
-{
-    if (E <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_scatter_runstart, dim3(blocks_for(E)), dim3(kBlock), 0, s, flags, runid, E,
-                       runstart);
     return hipGetLastError();
 }
 
@@ -2998,17 +2656,17 @@ __global__ __launch_bounds__(kBlock) void k_chunk_starts_dev(const unsigned long
 // One block: the batch's accepted (gx, gy) become (query id << 32 | indexed id) keys, sorted in
 // LDS (bitonic), deduplicated and compacted in order.  More than kGraphSortCap accepted pairs,
 // or more than the accepted buffer held, sets a flag and outputs nothing.
-__global__ __launch_bounds__(kBlock) void k_batch_dedupe(const uint64_t* __restrict__ acc,
-                                                         const unsigned long long* __restrict__ counters,
-                                                         uint64_t acc_cap,
-                                                         const int32_t* __restrict__ xperm,
-                                                         const int32_t* __restrict__ yperm,
-                                                         unsigned long long* __restrict__ bc,
-                                                         uint64_t* __restrict__ out,
-                                                         uint32_t* __restrict__ out_n)
+__global__ __launch_bounds__(1024) void k_batch_dedupe(const uint64_t* __restrict__ acc,
+                                                       const unsigned long long* __restrict__ counters,
+                                                       uint64_t acc_cap,
+                                                       const int32_t* __restrict__ xperm,
+                                                       const int32_t* __restrict__ yperm,
+                                                       unsigned long long* __restrict__ bc,
+                                                       uint64_t* __restrict__ out,
+                                                       uint32_t* __restrict__ out_n)
 {
     __shared__ uint64_t s_k[kGraphSortCap];
-    __shared__ uint32_t s_w[kWaves];
+    __shared__ uint32_t s_w[16];
     const uint64_t m = counters[3];
     if (m > acc_cap || m > (uint64_t)kGraphSortCap) {
         if (threadIdx.x == 0) {
@@ -3017,9 +2675,9 @@ __global__ __launch_bounds__(kBlock) void k_batch_dedupe(const uint64_t* __restr
         }
         return;
     }
-    uint32_t N = 1;
+    uint32_t N = 64;
     while (N < (uint32_t)m) N <<= 1;
-    for (uint32_t k = threadIdx.x; k < N; k += kBlock) {
+    for (uint32_t k = threadIdx.x; k < N; k += 1024) {
         uint64_t key = ~0ull;
         if (k < (uint32_t)m) {
             const uint64_t v = acc[k];
@@ -3030,29 +2688,14 @@ __global__ __launch_bounds__(kBlock) void k_batch_dedupe(const uint64_t* __restr
         s_k[k] = key;
     }
     __syncthreads();
-    for (uint32_t kk = 2; kk <= N; kk <<= 1) {
-        for (uint32_t j = kk >> 1; j > 0; j >>= 1) {
-            for (uint32_t i = threadIdx.x; i < N; i += kBlock) {
-                const uint32_t ixj = i ^ j;
-                if (ixj > i) {
-                    const uint64_t a = s_k[i], b = s_k[ixj];
-                    const bool up = (i & kk) == 0;
-                    if ((a > b) == up) {
-                        s_k[i] = b;
-                        s_k[ixj] = a;
-                    }
-                }
-            }
-            __syncthreads();
-        }
-    }
+    block_bitonic_sort(s_k, N, 1024u);
     uint32_t carry = 0;
-    for (uint32_t base = 0; base < N; base += kBlock) {
+    for (uint32_t base = 0; base < (uint32_t)m; base += 1024) {
         const uint32_t k = base + threadIdx.x;
-        const uint32_t f = (k < (uint32_t)m && (k == 0 || s_k[k] != s_k[k - 1])) ? 1u : 0u;
+        const bool head = k < (uint32_t)m && (k == 0 || s_k[k] != s_k[k - 1]);
         uint32_t tot;
-        const uint32_t ex = block_excl_scan(f, s_w, &tot);
-        if (f) out[carry + ex] = s_k[k];
+        const uint32_t at = carry + block_rank_1024(head, s_w, &tot);
+        if (head) out[at] = s_k[k];
         carry += tot;
     }
     if (threadIdx.x == 0) *out_n = carry;
@@ -3090,7 +2733,7 @@ hipError_t launch_graph_batch(const GraphBatch& G, hipStream_t s)
     else if (w <= 17) graph_verify_short<17>(G, s);
     else if (w <= 33) graph_verify_short<33>(G, s);
     else graph_verify_short<64>(G, s);
-    hipLaunchKernelGGL(k_batch_dedupe, dim3(1), dim3(kBlock), 0, s, G.verify.out,
+    hipLaunchKernelGGL(k_batch_dedupe, dim3(1), dim3(1024), 0, s, G.verify.out,
                        G.verify.counters, G.verify.out_cap, G.xperm, G.yperm, G.bcounts, G.out,
                        G.out_n);
     return hipGetLastError();
@@ -3103,22 +2746,6 @@ hipError_t launch_pairs_to_keys(const uint64_t* acc, uint64_t m, const int32_t* 
     if (m == 0) return hipSuccess;
     hipLaunchKernelGGL(k_pairs_to_keys, dim3(blocks_for(m)), dim3(kBlock), 0, s, acc, m, xperm,
                        yperm, self, bbits, keys);
-    return hipGetLastError();
-}
-
-hipError_t launch_unique_flags(const uint64_t* keys, uint64_t m, uint32_t* flags, hipStream_t s)
-{
-    if (m == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_unique_flags, dim3(blocks_for(m)), dim3(kBlock), 0, s, keys, m, flags);
-    return hipGetLastError();
-}
-
-hipError_t launch_compact_pairs(const uint64_t* keys, const uint32_t* flags, const uint32_t* pos,
-                                uint64_t m, int bbits, int32_t* a, int32_t* b, hipStream_t s)
-{
-    if (m == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_compact_pairs, dim3(blocks_for(m)), dim3(kBlock), 0, s, keys, flags, pos,
-                       m, bbits, a, b);
     return hipGetLastError();
 }
 

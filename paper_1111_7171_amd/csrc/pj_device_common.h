@@ -9,6 +9,102 @@
 
 namespace pj {
 
+// ------------------------------------------------------------------------------------------
+// Wave / block primitives (wave64, 256-thread blocks)
+// ------------------------------------------------------------------------------------------
+
+constexpr int kBlock = 256;
+constexpr int kWaves = kBlock / 64;
+
+template <typename T>
+__device__ inline T wave_incl_scan(T v)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        T t = __shfl_up(v, d, 64);
+        if (lane >= d) v += t;
+    }
+    return v;
+}
+
+template <typename T>
+__device__ inline T wave_sum(T v)
+{
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+    return v;
+}
+
+// Exclusive scan over the 256 threads of a block; *total receives the block sum.
+template <typename T>
+__device__ inline T block_excl_scan(T v, T* s_wave, T* total)
+{
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    T inc = wave_incl_scan(v);
+    if (lane == 63) s_wave[w] = inc;
+    __syncthreads();
+    T off = 0, tot = 0;
+#pragma unroll
+    for (int k = 0; k < kWaves; ++k) {
+        T s = s_wave[k];
+        if (k < w) off += s;
+        tot += s;
+    }
+    __syncthreads();
+    *total = tot;
+    return off + inc - v;
+}
+
+__device__ inline uint64_t lanemask_lt() { return (1ull << (threadIdx.x & 63)) - 1ull; }
+
+// Bitonic sort of N keys (a power of two, at least 64) in LDS by a block of T threads.  A thread
+// takes pair p of a step, so the pairs of a step of stride at most 64 stay inside the 128 keys
+// that the wave's pairs cover: between such steps the wave needs no block barrier.
+__device__ inline void block_bitonic_sort(uint64_t* s_k, uint32_t N, uint32_t T)
+{
+    for (uint32_t kk = 2; kk <= N; kk <<= 1) {
+        for (uint32_t j = kk >> 1; j > 0; j >>= 1) {
+            for (uint32_t p = threadIdx.x; p < N / 2; p += T) {
+                const uint32_t i = ((p & ~(j - 1u)) << 1) | (p & (j - 1u));
+                const uint64_t a = s_k[i], b = s_k[i + j];
+                if ((a > b) == ((i & kk) == 0)) {
+                    s_k[i] = b;
+                    s_k[i + j] = a;
+                }
+            }
+            const uint32_t next = j > 1 ? j >> 1 : kk;
+            if (j > 64 || next > 64) {
+                __syncthreads();
+            } else {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// Rank of the calling thread among the threads with flag set (1024-thread block); s_w: 16 words
+__device__ inline uint32_t block_rank_1024(bool flag, uint32_t* s_w, uint32_t* total)
+{
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint64_t m = __ballot(flag);
+    if (lane == 0) s_w[w] = (uint32_t)__popcll(m);
+    __syncthreads();
+    uint32_t off = 0, tot = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const uint32_t c = s_w[k];
+        if (k < w) off += c;
+        tot += c;
+    }
+    __syncthreads();
+    *total = tot;
+    return off + (uint32_t)__popcll(m & lanemask_lt());
+}
+
 // Division by d <= 64 of l < 2048 by multiply-shift: q = (l * m) >> 21 with m = ceil(2^21 / d)
 // is exact because l * (m - 2^21/d) / 2^21 < 2^-10 < 1/d.
 struct Div {

@@ -457,14 +457,14 @@ void build_set(const pj_strings* S, bool on_device, Alloc& A, const std::string&
     uint32_t* v1 = (uint32_t*)W.get("lensort.v1", sizeof(uint32_t) * (size_t)n);
     size_t tb = radix_tmp_bytes((uint64_t)n);
     void* tmp = W.get("radix.tmp", tb);
+    // the ids start in the buffer from which the passes end in perm
+    const int len_bits = bitlen((uint64_t)std::max(D.lmax, 1));
     uint32_t* v0 = (uint32_t*)D.perm;
+    if (radix_passes(len_bits) & 1) std::swap(v0, v1);
     hip_check(launch_iota_len_keys(d_offs, n, k0, v0, st), "len_keys");
     bool alt = false;
-    hip_check(radix_sort_u32(k0, v0, k1, v1, (uint64_t)n, bitlen((uint64_t)std::max(D.lmax, 1)),
-                             tmp, tb, &alt, st), "radix(len)");
-    if (alt)
-        hip_check(hipMemcpyAsync(D.perm, v1, sizeof(uint32_t) * (size_t)n,
-                                 hipMemcpyDeviceToDevice, st), "perm copy");
+    hip_check(radix_sort_u32(k0, v0, k1, v1, (uint64_t)n, len_bits, tmp, tb, &alt, st),
+              "radix(len)");
     hip_check(launch_pack_arena(d_bytes, d_offs, D.perm, n, D.lenstart, D.gbase, D.sarena, D.slen,
                                 D.lmax, st), "pack_arena");
 }
@@ -526,21 +526,18 @@ void build_index(const DevSet& D, int tau, Alloc& A, const std::string& tag, Dev
     uint32_t* vals = (uint32_t*)A.get(nm("vals").c_str(), sizeof(uint32_t) * (size_t)E);
     uint64_t* keys2 = (uint64_t*)W.get("index.keys2", sizeof(uint64_t) * (size_t)E);
     uint32_t* vals2 = (uint32_t*)W.get("index.vals2", sizeof(uint32_t) * (size_t)E);
-    hip_check(launch_emit_segments(D, tau, d_ebase, g_first, g_count, X.sym, keys, vals, st),
-              "emit");
     uint64_t grp_max = (uint64_t)(D.lmax - T1) * T1 + tau;
     int bits = kHashBits + std::max(1, bitlen(grp_max));
+    // the entries start in the buffers from which the passes end in keys, vals
+    const bool odd = radix_passes(bits) & 1;
+    uint64_t *ka = odd ? keys2 : keys, *kb = odd ? keys : keys2;
+    uint32_t *va = odd ? vals2 : vals, *vb = odd ? vals : vals2;
+    hip_check(launch_emit_segments(D, tau, d_ebase, g_first, g_count, X.sym, ka, va, st), "emit");
     size_t tb = radix_tmp_bytes((uint64_t)E);
     void* tmp = W.get("radix.tmp", tb);
     bool alt = false;
-    hip_check(radix_sort_u64(keys, vals, keys2, vals2, (uint64_t)E, bits, tmp, tb, &alt, st),
+    hip_check(radix_sort_u64(ka, va, kb, vb, (uint64_t)E, bits, tmp, tb, &alt, st),
               "radix(index)");
-    if (alt) {
-        hip_check(hipMemcpyAsync(keys, keys2, sizeof(uint64_t) * (size_t)E,
-                                 hipMemcpyDeviceToDevice, st), "keys copy");
-        hip_check(hipMemcpyAsync(vals, vals2, sizeof(uint32_t) * (size_t)E,
-                                 hipMemcpyDeviceToDevice, st), "vals copy");
-    }
     X.keys = keys;
     X.vals = vals;
     // inline copies of the members' strings (short strings only, and only within the budget):
@@ -562,18 +559,15 @@ void build_index(const DevSet& D, int tau, Alloc& A, const std::string& tag, Dev
         }
     }
     // lists = runs of equal keys
-    uint32_t* flags = (uint32_t*)W.get("index.flags", sizeof(uint32_t) * (size_t)E);
-    uint32_t* runid = (uint32_t*)W.get("index.runid", sizeof(uint32_t) * (size_t)(E + 1));
-    hip_check(launch_mark_heads(keys, E, flags, st), "mark_heads");
+    uint32_t* runstart = (uint32_t*)W.get("index.runstart", sizeof(uint32_t) * (size_t)E);
+    uint32_t* run_count = (uint32_t*)W.get("index.runs", sizeof(uint32_t));
     size_t sb = scan_tmp_bytes((uint64_t)E);
     void* stmp = W.get("scan.tmp", sb);
-    hip_check(scan_u32_to_u32(flags, runid, (uint64_t)E, stmp, sb, st), "scan(runs)");
+    hip_check(launch_run_starts(keys, (uint64_t)E, stmp, sb, runstart, run_count, st), "run_starts");
     uint32_t nruns = 0;
-    readback(&nruns, runid + E, sizeof(uint32_t), st);
+    readback(&nruns, run_count, sizeof(uint32_t), st);
     sync_readback(st);
     X.lists = nruns;
-    uint32_t* runstart = (uint32_t*)W.get("index.runstart", sizeof(uint32_t) * (size_t)(nruns + 1));
-    hip_check(launch_scatter_runstart(flags, runid, E, runstart, st), "runstart");
     uint64_t slots = 1024;
     while (slots < 2ull * nruns) slots <<= 1;
     X.mask = slots - 1;
@@ -1051,29 +1045,30 @@ uint64_t finish_pairs(const DevSet& P, const DevSet& Y, bool self, const uint64_
     Workspace& W = thread_workspace();
     if (m >= (uint64_t)UINT32_MAX) throw Error(PJ_ERANGE, "too many accepted candidates");
     int bbits = std::max(1, bitlen((uint64_t)std::max<int64_t>(std::max(P.n, Y.n) - 1, 1)));
-    uint64_t* k0 = (uint64_t*)W.get("out.k0", sizeof(uint64_t) * (size_t)std::max<uint64_t>(m, 1));
-    uint64_t* k1 = (uint64_t*)W.get("out.k1", sizeof(uint64_t) * (size_t)std::max<uint64_t>(m, 1));
     int32_t* a = (int32_t*)W.get("out.a", sizeof(int32_t) * (size_t)std::max<uint64_t>(m, 1));
     int32_t* b = (int32_t*)W.get("out.b", sizeof(int32_t) * (size_t)std::max<uint64_t>(m, 1));
     *a_out = a;
     *b_out = b;
     if (m == 0) return 0;
-    hip_check(launch_pairs_to_keys(acc, m, P.perm, Y.perm, self ? 1 : 0, bbits, k0, st), "keys");
-    size_t tb = radix_tmp_bytes(m);
-    void* tmp = W.get("radix.tmp", tb);
-    bool alt = false;
-    hip_check(radix_sort_u64(k0, nullptr, k1, nullptr, m, 2 * bbits, tmp, tb, &alt, st),
-              "radix(pairs)");
-    uint64_t* ks = alt ? k1 : k0;
-    uint32_t* flags = (uint32_t*)W.get("out.flags", sizeof(uint32_t) * (size_t)m);
-    uint32_t* pos = (uint32_t*)W.get("out.pos", sizeof(uint32_t) * (size_t)(m + 1));
-    hip_check(launch_unique_flags(ks, m, flags, st), "unique");
-    size_t sb = scan_tmp_bytes(m);
-    void* stmp = W.get("scan.tmp", sb);
-    hip_check(scan_u32_to_u32(flags, pos, m, stmp, sb, st), "scan(unique)");
-    hip_check(launch_compact_pairs(ks, flags, pos, m, bbits, a, b, st), "compact");
+    uint32_t* count = (uint32_t*)W.get("out.count", sizeof(uint32_t));
+    if (m <= (uint64_t)kSmallPairs) {
+        hip_check(launch_small_pairs(acc, m, P.perm, Y.perm, self ? 1 : 0, bbits, a, b, count, st),
+                  "small_pairs");
+    } else {
+        uint64_t* k0 = (uint64_t*)W.get("out.k0", sizeof(uint64_t) * (size_t)m);
+        uint64_t* k1 = (uint64_t*)W.get("out.k1", sizeof(uint64_t) * (size_t)m);
+        hip_check(launch_pairs_to_keys(acc, m, P.perm, Y.perm, self ? 1 : 0, bbits, k0, st), "keys");
+        size_t tb = radix_tmp_bytes(m);
+        void* tmp = W.get("radix.tmp", tb);
+        bool alt = false;
+        hip_check(radix_sort_u64(k0, nullptr, k1, nullptr, m, 2 * bbits, tmp, tb, &alt, st),
+                  "radix(pairs)");
+        size_t sb = scan_tmp_bytes(m);
+        void* stmp = W.get("scan.tmp", sb);
+        hip_check(launch_unique_pairs(alt ? k1 : k0, m, bbits, stmp, sb, a, b, count, st), "unique");
+    }
     uint32_t M = 0;
-    readback(&M, pos + m, sizeof(uint32_t), st);
+    readback(&M, count, sizeof(uint32_t), st);
     sync_readback(st);
     return M;
 }

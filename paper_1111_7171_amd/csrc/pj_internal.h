@@ -205,9 +205,6 @@ hipError_t launch_emit_segments(const DevSet& S, int tau, const int64_t* ebase_d
 hipError_t launch_gather_inline(const DevSet& S, const uint64_t* keys, const uint32_t* vals,
                                 int64_t E, int tau, const int64_t* inl_base, uint8_t* inl,
                                 hipStream_t s);
-hipError_t launch_mark_heads(const uint64_t* keys, int64_t E, uint32_t* flags, hipStream_t s);
-hipError_t launch_scatter_runstart(const uint32_t* flags, const uint32_t* runid, int64_t E,
-                                   uint32_t* runstart, hipStream_t s);
 hipError_t launch_clear_table(uint4* table, uint64_t slots, hipStream_t s);
 hipError_t launch_insert_runs(const uint64_t* keys, const uint32_t* runstart, uint32_t nruns,
                               uint32_t E, uint4* table, uint64_t mask, hipStream_t s);
@@ -306,9 +303,12 @@ hipError_t launch_short_path(const DevSet& P, const DevSet& Y, int tau, int self
 hipError_t launch_pairs_to_keys(const uint64_t* acc, uint64_t m, const int32_t* xperm,
                                 const int32_t* yperm, int self, int bbits, uint64_t* keys,
                                 hipStream_t s);
-hipError_t launch_unique_flags(const uint64_t* keys, uint64_t m, uint32_t* flags, hipStream_t s);
-hipError_t launch_compact_pairs(const uint64_t* keys, const uint32_t* flags, const uint32_t* pos,
-                                uint64_t m, int bbits, int32_t* a, int32_t* b, hipStream_t s);
+// at most kSmallPairs accepted (gx, gy) -> sorted distinct id pairs a, b and their number, in one
+// block
+constexpr int kSmallPairs = 4096;
+hipError_t launch_small_pairs(const uint64_t* acc, uint64_t m, const int32_t* xperm,
+                              const int32_t* yperm, int self, int bbits, int32_t* a, int32_t* b,
+                              uint32_t* count, hipStream_t s);
 
 // streamed self-joins: window pairs -> global keys (halo-only pairs as a counted sentinel that
 // sorts last); sorted keys -> pair arrays
@@ -325,6 +325,7 @@ hipError_t launch_set_checksum(const int32_t* offs, int64_t n, const uint8_t* by
 hipError_t launch_gather_i32(const int32_t* in, const int32_t* perm, int64_t n, int32_t* out,
                              hipStream_t s);
 
+// ---- device-wide primitives (pj_sort.hip) ----
 // Exclusive scans; out has n + 1 entries (out[n] = total).
 hipError_t scan_u32_to_u32(const uint32_t* in, uint32_t* out, uint64_t n, void* tmp,
                            size_t tmp_bytes, hipStream_t s);
@@ -333,13 +334,23 @@ hipError_t scan_u32_to_u64(const uint32_t* in, unsigned long long* out, uint64_t
 size_t scan_tmp_bytes(uint64_t n);
 
 // Stable LSD radix sort by the low `bits` bits of the keys, 8 bits per pass.  Buffers ping-pong;
-// returns in *result_in_alt whether the sorted data ended in the alternate buffers.
+// returns in *result_in_alt whether the sorted data ended in the alternate buffers (it does when
+// radix_passes(bits) is odd).
 hipError_t radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt,
                           uint32_t* vals_alt, uint64_t n, int bits, void* tmp, size_t tmp_bytes,
                           bool* result_in_alt, hipStream_t s);
 hipError_t radix_sort_u32(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt,
                           uint32_t* vals_alt, uint64_t n, int bits, void* tmp, size_t tmp_bytes,
                           bool* result_in_alt, hipStream_t s);
+int radix_passes(int bits);
 size_t radix_tmp_bytes(uint64_t n);
+
+// Heads of runs of equal keys, in order (tmp: scan_tmp_bytes(n)): the first entry of every run;
+// the distinct sorted pair keys as id columns.  *count = their number.
+hipError_t launch_run_starts(const uint64_t* keys, uint64_t n, void* tmp, size_t tmp_bytes,
+                             uint32_t* runstart, uint32_t* count, hipStream_t s);
+hipError_t launch_unique_pairs(const uint64_t* keys, uint64_t n, int bbits, void* tmp,
+                               size_t tmp_bytes, int32_t* a, int32_t* b, uint32_t* count,
+                               hipStream_t s);
 
 }  // namespace pj
