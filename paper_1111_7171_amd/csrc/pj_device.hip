@@ -214,84 +214,75 @@ __global__ __launch_bounds__(kBlock) void k_gather_inline(
     for (int q = 0; q < (int)(st >> 4); ++q) dst[q] = src[q];
 }
 
-__global__ __launch_bounds__(kBlock) void k_clear_table(uint4* __restrict__ table, uint64_t slots)
-{
-    uint64_t k = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (k < slots) table[k] = make_uint4(0xffffffffu, 0xffffffffu, 0u, 0u);
-}
-
-// One thread per list: inserts key -> (start, count) into the table by linear probing.
-__global__ __launch_bounds__(kBlock) void k_insert_runs(const uint64_t* __restrict__ keys,
-                                                        const uint32_t* __restrict__ runstart,
-                                                        uint32_t nruns, uint32_t E,
-                                                        uint4* __restrict__ table, uint64_t mask)
-{
-    uint32_t r = blockIdx.x * kBlock + threadIdx.x;
-    if (r >= nruns) return;
-    uint32_t start = runstart[r];
-    uint32_t end = (r + 1 < nruns) ? runstart[r + 1] : E;
-    uint64_t key = keys[start];
-    uint64_t slot = table_slot(key) & mask;
-    while (true) {
-        unsigned long long* kp = reinterpret_cast<unsigned long long*>(&table[slot]);
-        unsigned long long prev = atomicCAS(kp, (unsigned long long)kEmptyKey,
-                                            (unsigned long long)key);
-        if (prev == (unsigned long long)kEmptyKey) {
-            table[slot].z = start;
-            table[slot].w = end - start;
-            return;
-        }
-        slot = (slot + 1) & mask;
-    }
-}
-
-// Key filter, blocked by (l, i) group.  First and one-past-last list of each (l, i) group (the arrays zeroed by the caller): lists are
-// in key order and the group is the key's top bits, so a group's lists are consecutive
-__global__ __launch_bounds__(kBlock) void k_filter_group_bounds(const uint64_t* __restrict__ keys,
-                                                                const uint32_t* __restrict__ runstart,
-                                                                uint32_t nruns,
-                                                                uint32_t* __restrict__ gfirst,
-                                                                uint32_t* __restrict__ gend)
+// One thread per list (and one more): its record, and the first and one-past-last list of each
+// (l, i) group in bounds[g], bounds[ngroups + g] (zeroed by the caller): lists are in key order and
+// the group is the key's top bits, so a group's lists are consecutive.
+__global__ __launch_bounds__(kBlock) void k_list_records(const uint64_t* __restrict__ keys,
+                                                         const uint32_t* __restrict__ runstart,
+                                                         uint32_t nruns, uint32_t E,
+                                                         uint32_t ngroups, uint4* __restrict__ recs,
+                                                         uint32_t* __restrict__ bounds)
 {
     const uint32_t r = blockIdx.x * kBlock + threadIdx.x;
-    if (r >= nruns) return;
-    const uint64_t g = keys[runstart[r]] >> kHashBits;
-    if (r == 0 || (keys[runstart[r - 1]] >> kHashBits) != g) gfirst[g] = r;
-    if (r + 1 == nruns || (keys[runstart[r + 1]] >> kHashBits) != g) gend[g] = r + 1;
+    if (r > nruns) return;
+    if (r == nruns) {
+        recs[r] = make_uint4(~0u, ~0u, 0u, 0u);
+        return;
+    }
+    const uint32_t start = runstart[r];
+    const uint32_t end = r + 1 < nruns ? runstart[r + 1] : E;
+    const uint64_t key = keys[start];
+    recs[r] = make_uint4((uint32_t)key, (uint32_t)(key >> 32), start, end - start);
+    const uint32_t g = (uint32_t)(key >> kHashBits);
+    if (r == 0 || (uint32_t)(keys[start - 1] >> kHashBits) != g) bounds[g] = r;
+    if (r + 1 == nruns || (uint32_t)(keys[end] >> kHashBits) != g) bounds[ngroups + g] = r + 1;
 }
 
-// words of each group's block: a power of two >= lists / 2 (16 bits per list), at least one
-__global__ __launch_bounds__(kBlock) void k_filter_block_words(const uint32_t* __restrict__ gfirst,
-                                                               const uint32_t* __restrict__ gend,
-                                                               uint32_t ngroups,
-                                                               uint32_t* __restrict__ words)
+// entries of each group: the least power of two that is at least half its lists
+__global__ __launch_bounds__(kBlock) void k_dir_words(const uint32_t* __restrict__ bounds,
+                                                      uint32_t ngroups,
+                                                      uint32_t* __restrict__ words)
 {
     const uint32_t g = blockIdx.x * kBlock + threadIdx.x;
     if (g >= ngroups) return;
-    const uint32_t need = (gend[g] - gfirst[g] + 1) >> 1;
+    const uint32_t need = (bounds[ngroups + g] - bounds[g] + 1) >> 1;
     uint32_t w = 1;
     while (w < need) w <<= 1;
     words[g] = w;
 }
 
-// sets the filter bits of every list's key in its group's block (filter zeroed by the caller)
-__global__ __launch_bounds__(kBlock) void k_filter_keys(const uint64_t* __restrict__ keys,
-                                                        const uint32_t* __restrict__ runstart,
-                                                        uint32_t nruns,
-                                                        const uint32_t* __restrict__ dir,
-                                                        uint32_t* __restrict__ filter)
+// One thread per list: the first list of a directory entry writes it, with the bits of all of
+// them (one or two on average); entries without a list stay zero.  Lists in key order make both
+// streaming writes: for 10^6 short strings at tau = 1 records, group sizes and directory take 31 us,
+// where a hash table and a key filter filled by atomics took 242 (random 16-byte slots).
+__global__ __launch_bounds__(kBlock) void k_dir_fill(const uint4* __restrict__ recs, uint32_t nruns,
+                                                     const uint32_t* __restrict__ gdir,
+                                                     uint2* __restrict__ dir)
 {
     const uint32_t r = blockIdx.x * kBlock + threadIdx.x;
     if (r >= nruns) return;
-    const uint64_t key = keys[runstart[r]];
-    const uint64_t h = table_slot(key);
-    const uint64_t g = key >> kHashBits;
-    const uint32_t base = dir[g];
-    atomicOr(&filter[base + filter_word_in(h, dir[g + 1] - base - 1u)], filter_bits(h));
+    auto key_of = [&](uint32_t q) {
+        return *reinterpret_cast<const uint64_t*>(recs + q);   // a record starts with its key
+    };
+    const uint64_t key = key_of(r), g = key >> kHashBits;
+    const uint32_t first = gdir[g];
+    const uint32_t k = dir_bits(first, gdir[g + 1]);
+    const uint32_t e = dir_entry(key, k);
+    if (r > 0) {
+        const uint64_t before = key_of(r - 1);
+        if ((before >> kHashBits) == g && dir_entry(before, k) == e) return;
+    }
+    uint32_t map = 1u << dir_bit(key, k);
+    for (uint32_t q = r + 1; q < nruns; ++q) {
+        const uint64_t next = key_of(q);
+        if ((next >> kHashBits) != g || dir_entry(next, k) != e) break;
+        map |= 1u << dir_bit(next, k);
+    }
+    dir[first + e] = make_uint2(map, r);
 }
 
 // ------------------------------------------------------------------------------------------
-// Probe: multi-match substring selection + bucket lookup (Sec. 4.2, Algorithm 2)
+// Probe: multi-match substring selection + list lookup (Sec. 4.2, Algorithm 2)
 // ------------------------------------------------------------------------------------------
 
 // One thread per (probe string x, probed length l, slot i).  The thread walks the window
@@ -374,11 +365,10 @@ __global__ __launch_bounds__(kBlock) void k_probe(ProbeParams P, Div div)
         uint32_t gx = 0;
         Seg sg{1, 0};
         const uint8_t* x = nullptr;
-        const uint4* table = P.table;
+        const uint4* recs = P.recs;
         const uint32_t* vals = P.vals;
-        uint64_t mask = P.mask;
-        const uint32_t* filter = P.filter;
-        const uint32_t* fdir = P.filter_dir;
+        const uint2* dir = P.dir;
+        const uint32_t* gdir = P.gdir;
         if (valid) {
             gx = gx_t;
             const uint32_t rem = P.order ? (uint32_t)P.order[r0] : r0;
@@ -389,11 +379,10 @@ __global__ __launch_bounds__(kBlock) void k_probe(ProbeParams P, Div div)
             if (P.q_tau) {                       // mixed-tau batch: this probe string's own tau
                 tau = P.q_tau[gx];
                 const IndexRef ref = P.refs[tau];
-                table = ref.table;
+                recs = ref.recs;
                 vals = ref.vals;
-                mask = ref.mask;
-                filter = ref.filter;
-                fdir = ref.filter_dir;
+                dir = ref.dir;
+                gdir = ref.gdir;
                 dv.d = (uint32_t)(tau + 1);
                 dv.m = ref.div_m;
             }
@@ -420,21 +409,19 @@ __global__ __launch_bounds__(kBlock) void k_probe(ProbeParams P, Div div)
         auto rd = [&](int k) -> uint8_t { return staged ? xs[k] : x[k]; };
         uint64_t h = 0, top = 0;
         if (valid && lo <= hi) top = pow_hash(sg.len);   // HB^(len-1)
-        // the (l, i) group's filter block
-        const bool use_filter = valid && lo <= hi && filter &&
-                                (sg.len > exact_len || sg.len * sym_bits >= kFilterMinBits);
-        uint32_t fb = 0, fm = 0;
-        if (use_filter) {
+        // the (l, i) group's directory entries
+        uint32_t dk = 0;
+        if (valid && lo <= hi) {
             const uint32_t g = (uint32_t)((l - (tau + 1)) * (tau + 1) + (i - 1));
-            fb = fdir[g];
-            fm = fdir[g + 1] - fb - 1u;
+            const uint32_t first = gdir[g];
+            dk = dir_bits(first, gdir[g + 1]);
+            dir += first;
         }
         // the window has at most tau+1 positions for multi-match, more for the other methods;
         // the loop ends when no lane of the wave has a position left.  kProbeStep positions per
-        // step: their bytes are read first, then their keys computed, then their filter words
-        // (or, without a filter, their first table slots) read together, so a step waits on one
-        // round trip per kind of read instead of one per position; hits are appended in position
-        // order as before.
+        // step: their bytes are read first, then their keys computed, then their directory
+        // entries and the records these lead to read together, so a step waits on one round trip
+        // per kind of read instead of one per position; hits are appended in position order.
         for (int s0 = 0;; s0 += kProbeStep) {
             if (__ballot(valid && lo + s0 <= hi) == 0) break;
             bool act[kProbeStep];
@@ -450,11 +437,10 @@ __global__ __launch_bounds__(kBlock) void k_probe(ProbeParams P, Div div)
                     inb[u] = rd(p - 2 + sg.len);
                 }
             }
-            uint64_t key[kProbeStep], hs[kProbeStep];
+            uint64_t key[kProbeStep];
 #pragma unroll
             for (int u = 0; u < kProbeStep; ++u) {
                 key[u] = 0;
-                hs[u] = 0;
                 if (act[u]) {
                     if (s0 + u == 0) {
                         const int w0 = lo - 1;
@@ -468,41 +454,31 @@ __global__ __launch_bounds__(kBlock) void k_probe(ProbeParams P, Div div)
                                       sym_bits, exact_len);
                     }
                     key[u] = make_key(l, i, tau, sg.len, h, exact_len);
-                    hs[u] = table_slot(key[u]);
                 }
             }
-            // hashed segments and long exact codes rarely match: the group's filter block (one
-            // cache line for a group of up to 64 lists, read again by the lane at every position
-            // of its window) turns most of those lookups away before the table read
-            uint32_t fw[kProbeStep];
+            // one directory entry turns most absent segments away before a record is read
+            uint2 de[kProbeStep];
 #pragma unroll
             for (int u = 0; u < kProbeStep; ++u) {
-                fw[u] = 0;
-                if (act[u] && use_filter) fw[u] = filter[fb + filter_word_in(hs[u], fm)];
+                de[u] = make_uint2(0u, 0u);
+                if (act[u]) de[u] = dir[dir_entry(key[u], dk)];
             }
             bool maybe[kProbeStep];
-            uint4 tv[kProbeStep];
+            uint4 rv[kProbeStep];
+            uint32_t rn[kProbeStep];
 #pragma unroll
             for (int u = 0; u < kProbeStep; ++u) {
-                const uint32_t fbits = filter_bits(hs[u]);
-                maybe[u] = act[u] && (!use_filter || (fw[u] & fbits) == fbits);
-                tv[u] = make_uint4(0u, 0u, 0u, 0u);
-                if (maybe[u]) tv[u] = table[hs[u] & mask];
+                const uint32_t bit = dir_bit(key[u], dk);
+                maybe[u] = (de[u].x >> bit) & 1u;
+                rn[u] = de[u].y + (uint32_t)__popc(de[u].x & ((1u << bit) - 1u));
+                rv[u] = make_uint4(0u, 0u, 0u, 0u);
+                if (maybe[u]) rv[u] = recs[rn[u]];
             }
 #pragma unroll
             for (int u = 0; u < kProbeStep; ++u) {
                 uint32_t start = 0, count = 0;
                 if (maybe[u]) {
-                    const uint64_t k = (uint64_t)tv[u].x | ((uint64_t)tv[u].y << 32);
-                    bool hit = false;
-                    if (k == key[u]) {
-                        start = tv[u].z;
-                        count = tv[u].w;
-                        hit = true;
-                    } else if (k != kEmptyKey) {
-                        hit = table_lookup_from(table, mask, key[u], ((hs[u] & mask) + 1) & mask,
-                                                &start, &count);
-                    }
+                    const bool hit = find_record(recs, rn[u], key[u], rv[u], &start, &count);
                     if (hit && P.self && l == n) {
                         // keep members with g < gx (lists are ascending in g)
                         uint32_t a = 0, b = count;
@@ -2120,37 +2096,20 @@ hipError_t launch_gather_inline(const DevSet& S, const uint64_t* keys, const uin
     return hipGetLastError();
 }
 
-hipError_t launch_clear_table(uint4* table, uint64_t slots, hipStream_t s)
+hipError_t launch_list_dir(const uint64_t* keys, const uint32_t* runstart, uint32_t nruns, uint32_t E,
+                           uint32_t ngroups, uint32_t* bounds, uint32_t* words, void* scan_tmp,
+                           size_t scan_bytes, uint4* recs, uint32_t* gdir, uint2* dir,
+                           hipStream_t s)
 {
-    hipLaunchKernelGGL(k_clear_table, dim3(blocks_for(slots)), dim3(kBlock), 0, s, table, slots);
-    return hipGetLastError();
-}
-
-hipError_t launch_filter_build(const uint64_t* keys, const uint32_t* runstart, uint32_t nruns,
-                               uint32_t ngroups, uint32_t* gfirst, uint32_t* gend, uint32_t* words,
-                               void* scan_tmp, size_t scan_bytes, uint32_t* filter_dir,
-                               uint32_t* filter, hipStream_t s)
-{
-    if (ngroups == 0) return hipSuccess;
-    if (nruns > 0)
-        hipLaunchKernelGGL(k_filter_group_bounds, dim3(blocks_for(nruns)), dim3(kBlock), 0, s, keys,
-                           runstart, nruns, gfirst, gend);
-    hipLaunchKernelGGL(k_filter_block_words, dim3(blocks_for(ngroups)), dim3(kBlock), 0, s, gfirst,
-                       gend, ngroups, words);
-    hipError_t e = scan_u32_to_u32(words, filter_dir, ngroups, scan_tmp, scan_bytes, s);
+    if (ngroups == 0 || nruns == 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_list_records, dim3(blocks_for((uint64_t)nruns + 1)), dim3(kBlock), 0, s,
+                       keys, runstart, nruns, E, ngroups, recs, bounds);
+    hipLaunchKernelGGL(k_dir_words, dim3(blocks_for(ngroups)), dim3(kBlock), 0, s, bounds, ngroups,
+                       words);
+    hipError_t e = scan_u32_to_u32(words, gdir, ngroups, scan_tmp, scan_bytes, s);
     if (e != hipSuccess) return e;
-    if (nruns > 0)
-        hipLaunchKernelGGL(k_filter_keys, dim3(blocks_for(nruns)), dim3(kBlock), 0, s, keys,
-                           runstart, nruns, filter_dir, filter);
-    return hipGetLastError();
-}
-
-hipError_t launch_insert_runs(const uint64_t* keys, const uint32_t* runstart, uint32_t nruns,
-                              uint32_t E, uint4* table, uint64_t mask, hipStream_t s)
-{
-    if (nruns == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_insert_runs, dim3(blocks_for(nruns)), dim3(kBlock), 0, s, keys, runstart,
-                       nruns, E, table, mask);
+    hipLaunchKernelGGL(k_dir_fill, dim3(blocks_for(nruns)), dim3(kBlock), 0, s, recs, nruns, gdir,
+                       dir);
     return hipGetLastError();
 }
 

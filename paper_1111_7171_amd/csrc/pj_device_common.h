@@ -257,62 +257,56 @@ __device__ inline uint64_t roll_code(uint64_t h, int len, uint8_t out, uint8_t i
     return roll_hash(h, out, in, top);
 }
 
+// Index key: group(l, i) above a 40-bit code that is spread over its range whatever the segments
+// are: a hashed segment's finalised hash, or a packed code times an odd constant modulo 2^40 (one
+// to one, so exact keys stay exact).
+constexpr uint64_t kCodeMul = 0x9E3779B97F4A7C15ull << (64 - kHashBits);
+
+__device__ inline uint64_t spread_code(int len, uint64_t code, int exact_len)
+{
+    return (len <= exact_len ? code * kCodeMul : mix64(code)) >> (64 - kHashBits);
+}
+
 __device__ inline uint64_t make_key(int l, int i, int tau, int len, uint64_t code, int exact_len)
 {
     const uint64_t grp = (uint64_t)(l - (tau + 1)) * (uint64_t)(tau + 1) + (uint64_t)(i - 1);
-    const uint64_t c = (len <= exact_len) ? code : (mix64(code) >> (64 - kHashBits));
-    return (grp << kHashBits) | c;
+    return (grp << kHashBits) | spread_code(len, code, exact_len);
 }
 
-__device__ inline uint64_t table_slot(uint64_t key) { return mix64(key ^ 0x5851F42D4C957F2Dull); }
-
-// Key filter, blocked by (l, i) group: group g owns the words [dir[g], dir[g+1]) of the filter,
-// a power of two of them (about 16 bits per list of the group, at least one word), so the keys
-// a wave looks up for one probe string and a few (l, i) share one or two cache lines.  A key
-// sets two bits of one word of its group's block, all from the slot hash's bits 30.. (the table
-// uses the low bits): the word (h >> 45) & (block words - 1), the bits below.
-__device__ inline uint32_t filter_bits(uint64_t h)
+// Directory of the lists, blocked by (l, i) group.  Group g owns the entries [gdir[g],
+// gdir[g + 1]), 2^k of them (the least power of two that is at least half its lists, so an entry
+// has one or two lists on average).  The top k bits of a code pick the entry and the next five a
+// bit of its map: entry = {map of the bits its lists set, record number of its first list}.  The
+// lists' records {key, start, count} are in key order, codes are spread evenly, so an entry's
+// lists are consecutive and the set bits below a code's own tell how far in its list begins.  One
+// 8-byte read turns most absent codes away (a probe walks one group at a time, whose entries are a
+// few cache lines) and leads a present one to its record.
+__device__ inline uint32_t dir_bits(uint32_t first, uint32_t next)      // k
 {
-    return (1u << ((uint32_t)(h >> 35) & 31u)) | (1u << ((uint32_t)(h >> 30) & 31u));
+    return 31u - (uint32_t)__clz((int)(next - first));
 }
-__device__ inline uint32_t filter_word_in(uint64_t h, uint32_t block_mask)
+__device__ inline uint32_t dir_entry(uint64_t key, uint32_t k)          // within the group
 {
-    return (uint32_t)(h >> 45) & block_mask;
+    return (uint32_t)((key & ((1ull << kHashBits) - 1ull)) >> (kHashBits - k));
+}
+__device__ inline uint32_t dir_bit(uint64_t key, uint32_t k)
+{
+    return (uint32_t)(key >> (kHashBits - 5 - k)) & 31u;
 }
 
-// The open-addressing lookup from a given slot on (linear probing).
-__device__ inline bool table_lookup_from(const uint4* __restrict__ table, uint64_t mask,
-                                         uint64_t key, uint64_t slot, uint32_t* start,
-                                         uint32_t* count)
+// The record of `key` from record r on, the first whose key is not smaller (the records end with
+// one of the largest key): lists before it in its entry that share its bit are passed over.
+__device__ inline bool find_record(const uint4* __restrict__ recs, uint32_t r, uint64_t key,
+                                   uint4 v, uint32_t* start, uint32_t* count)
 {
-    while (true) {
-        const uint4 v = table[slot];
-        const uint64_t k = (uint64_t)v.x | ((uint64_t)v.y << 32);
-        if (k == key) {
-            *start = v.z;
-            *count = v.w;
-            return true;
-        }
-        if (k == kEmptyKey) return false;
-        slot = (slot + 1) & mask;
+    uint64_t k = (uint64_t)v.x | ((uint64_t)v.y << 32);
+    while (k < key) {
+        v = recs[++r];
+        k = (uint64_t)v.x | ((uint64_t)v.y << 32);
     }
-}
-
-__device__ inline bool table_lookup(const uint4* __restrict__ table, uint64_t mask, uint64_t key,
-                                    uint32_t* start, uint32_t* count)
-{
-    uint64_t slot = table_slot(key) & mask;
-    while (true) {
-        const uint4 v = table[slot];
-        const uint64_t k = (uint64_t)v.x | ((uint64_t)v.y << 32);
-        if (k == key) {
-            *start = v.z;
-            *count = v.w;
-            return true;
-        }
-        if (k == kEmptyKey) return false;
-        slot = (slot + 1) & mask;
-    }
+    *start = v.z;
+    *count = v.w;
+    return k == key;
 }
 
 // VerifyStringPair (Sec. 5.1; function of Algorithm 3): min(t+1, ED(r, s)) with the length-aware

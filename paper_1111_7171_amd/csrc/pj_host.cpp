@@ -507,9 +507,10 @@ void build_index(const DevSet& D, int tau, Alloc& A, const std::string& tag, Dev
     if (E == 0) {
         X.keys = (uint64_t*)A.get(nm("keys").c_str(), 16);
         X.vals = (uint32_t*)A.get(nm("vals").c_str(), 16);
-        X.mask = 1023;
-        X.table = (uint4*)A.get(nm("table").c_str(), sizeof(uint4) * 1024);
-        hip_check(launch_clear_table(X.table, 1024, st), "clear_table");
+        // no list and no group: nothing reads the directory
+        X.recs = (uint4*)A.get(nm("recs").c_str(), sizeof(uint4));
+        X.dir = (uint2*)A.get(nm("dir").c_str(), sizeof(uint2));
+        X.gdir = (uint32_t*)A.get(nm("gdir").c_str(), sizeof(uint32_t));
         X.lists = 0;
         return;
     }
@@ -568,34 +569,21 @@ void build_index(const DevSet& D, int tau, Alloc& A, const std::string& tag, Dev
     readback(&nruns, run_count, sizeof(uint32_t), st);
     sync_readback(st);
     X.lists = nruns;
-    uint64_t slots = 1024;
-    while (slots < 2ull * nruns) slots <<= 1;
-    X.mask = slots - 1;
-    X.table = (uint4*)A.get(nm("table").c_str(), sizeof(uint4) * (size_t)slots);
-    hip_check(launch_clear_table(X.table, slots, st), "clear_table");
-    hip_check(launch_insert_runs(keys, runstart, nruns, (uint32_t)E, X.table, X.mask, st),
-              "insert_runs");
-    // the longest segment (even partition: lengths floor(l / (tau+1)) or one more)
-    const int max_seg = (D.lmax + T1 - 1) / T1;
-    if (max_seg > X.sym.exact_len || max_seg * X.sym.bits >= kFilterMinBits) {
-        // key filter for hashed segments and long exact codes, blocked by (l, i) group (16 bits
-        // per list)
-        const uint32_t ngroups = (uint32_t)((D.lmax - T1 + 1) * T1);
-        const uint64_t fwords = (uint64_t)nruns + 2ull * ngroups;
-        X.filter = (uint32_t*)A.get(nm("filter").c_str(), sizeof(uint32_t) * (size_t)fwords);
-        X.filter_dir = (uint32_t*)A.get(nm("filter_dir").c_str(),
-                                        sizeof(uint32_t) * (size_t)(ngroups + 1));
-        uint32_t* gfirst = (uint32_t*)W.get("index.gfirst", sizeof(uint32_t) * (size_t)ngroups);
-        uint32_t* gend = (uint32_t*)W.get("index.gend", sizeof(uint32_t) * (size_t)ngroups);
-        uint32_t* words = (uint32_t*)W.get("index.fwords", sizeof(uint32_t) * (size_t)ngroups);
-        zero_words(gfirst, sizeof(uint32_t) * (size_t)ngroups, st);
-        zero_words(gend, sizeof(uint32_t) * (size_t)ngroups, st);
-        zero_words(X.filter, sizeof(uint32_t) * (size_t)fwords, st);
-        const size_t fsb = scan_tmp_bytes(ngroups);
-        void* fst = W.get("scan.tmp", std::max(fsb, sb));
-        hip_check(launch_filter_build(keys, runstart, nruns, ngroups, gfirst, gend, words, fst, fsb,
-                                      X.filter_dir, X.filter, st), "filter");
-    }
+    // records and directory of the lists: an entry for every one or two lists of a group, at
+    // least one a group
+    const uint32_t ngroups = (uint32_t)((D.lmax - T1 + 1) * T1);
+    const size_t entries = (size_t)nruns + ngroups;
+    X.recs = (uint4*)A.get(nm("recs").c_str(), sizeof(uint4) * ((size_t)nruns + 1));
+    X.dir = (uint2*)A.get(nm("dir").c_str(), sizeof(uint2) * entries);
+    X.gdir = (uint32_t*)A.get(nm("gdir").c_str(), sizeof(uint32_t) * (size_t)(ngroups + 1));
+    uint32_t* bounds = (uint32_t*)W.get("index.bounds", sizeof(uint32_t) * 2 * (size_t)ngroups);
+    uint32_t* words = (uint32_t*)W.get("index.words", sizeof(uint32_t) * (size_t)ngroups);
+    zero_words(bounds, sizeof(uint32_t) * 2 * (size_t)ngroups, st);
+    zero_words(X.dir, sizeof(uint2) * entries, st);
+    const size_t dsb = scan_tmp_bytes(ngroups);
+    void* dst = W.get("scan.tmp", std::max(dsb, sb));
+    hip_check(launch_list_dir(keys, runstart, nruns, (uint32_t)E, ngroups, bounds, words, dst, dsb,
+                              X.recs, X.gdir, X.dir, st), "list_dir");
     if (with_share) {
         // content order of every list (shared-prefix verification, Sec. 5.3): entries sorted by
         // (key, first 8 bytes of the string, g) -- by the bytes first, then stably by the key
@@ -709,10 +697,10 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
         pp.refs = spec.refs;
         pp.y_lenstart = Y.lenstart;
         if (spec.X) {
-            pp.keys = spec.X->keys; pp.vals = spec.X->vals; pp.table = spec.X->table;
-            pp.mask = spec.X->mask;
-            pp.filter = spec.X->filter;
-            pp.filter_dir = spec.X->filter_dir;
+            pp.vals = spec.X->vals;
+            pp.recs = spec.X->recs;
+            pp.dir = spec.X->dir;
+            pp.gdir = spec.X->gdir;
         }
         pp.tau = tau;
         pp.ymin = Y.lmin; pp.ymax = Y.lmax;

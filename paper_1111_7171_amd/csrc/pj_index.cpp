@@ -1,7 +1,8 @@
 // pj_index.cpp -- device-resident indices (one per tau of a range) and per-query-tau probing.
 //
 // pj_build_index keeps the length-sorted arena of S and, for each tau in [tau_min, tau_max], the
-// sorted (key, g) entries and the bucket table of the even-partition segments (Sec. 3.1, 3.2).
+// sorted (key, g) entries, list records and directory of the even-partition segments (Sec. 3.1,
+// 3.2).
 // pj_query groups the queries by their threshold and runs the two-set join of Sec. 3.2 of each
 // group against the index of that threshold.
 #include <hip/hip_runtime.h>
@@ -181,9 +182,9 @@ int pj_build_index(const pj_strings* S, int32_t tau_min, int32_t tau_max, const 
             DevIndex& X = idx->X[(size_t)(t - tau_min)];
             build_index(idx->S, t, idx->mem, "I.t" + std::to_string(t), X, st);
             entries += X.entries;
-            refs[(size_t)t] = IndexRef{X.table, X.vals, X.mask,
-                                       (uint32_t)(((1u << 21) + (uint32_t)t) / (uint32_t)(t + 1)), 1u,
-                                       X.filter, X.filter_dir};
+            refs[(size_t)t] = IndexRef{X.recs, X.vals, X.dir, X.gdir,
+                                       (uint32_t)(((1u << 21) + (uint32_t)t) / (uint32_t)(t + 1)),
+                                       1u};
         }
         idx->has_entries = entries > 0;
         idx->refs = (IndexRef*)idx->mem.get("I.refs", sizeof(IndexRef) * (kTauMax + 1));

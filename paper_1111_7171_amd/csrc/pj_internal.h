@@ -10,7 +10,8 @@
 //     group(l, i) = (l - (tau+1)) * (tau+1) + (i-1), code = the segment's bytes when it has at
 //     most 5 (exact) or the top 40 bits of a mixed polynomial hash otherwise; equal keys form one
 //     inverted list L_l^i(w) whose members are in ascending g (Sec. 3.2);
-//   * bucket table: open-addressing hash table key -> (start, count) of the list.
+//   * list records {key, start, count} in key order, and a directory into them by (l, i) group and
+//     leading code bits.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -22,7 +23,6 @@ constexpr int kLenMax = 2047;          // PJ_LEN_MAX
 constexpr int kLenTab = kLenMax + 2;   // per-length tables are indexed 0 .. kLenMax + 1
 constexpr int kTauMax = 63;            // PJ_TAU_MAX
 constexpr int kHashBits = 40;          // hash bits kept in an index key
-constexpr uint64_t kEmptyKey = ~0ull;  // keys use at most 57 bits, so this never collides
 
 __host__ __device__ inline int64_t stride_of(int l) { return (int64_t)((l + 15) & ~15); }
 constexpr int kBatchedRoundsMax = 16;   // rounds of 64 candidates per batched-verify wave chunk
@@ -52,10 +52,6 @@ inline int class_maxlen(int c, int ymax)
 // floor(kHashBits / bits) bytes is keyed by its packed codes (exact: no byte guard); a longer
 // one by a hash of its bytes.  A probe segment with an absent byte packs a 0 code, which no
 // indexed key has.
-// Exact keys of at least this many code bits are also tested against the key filter: their
-// (l, i) groups hold few of the possible codes, so most lookups miss.
-constexpr int kFilterMinBits = 24;
-
 struct SymMap {
     const uint16_t* code = nullptr;   // device [256]
     int bits = 9;
@@ -85,15 +81,12 @@ struct DevIndex {
     int64_t lists = 0;                  // distinct keys (inverted lists)
     uint64_t* keys = nullptr;           // [entries] sorted
     uint32_t* vals = nullptr;           // [entries] sorted position g of the string
-    uint4* table = nullptr;             // [mask + 1] {key lo, key hi, start, count}
-    uint64_t mask = 0;
-    // membership filter of the keys, blocked by (l, i) group: group g = key >> 40 owns the
-    // words [filter_dir[g], filter_dir[g + 1]) (a power of two of them), in which each of its
-    // keys sets two bits; a clear bit proves a key absent without reading the table (long,
-    // hashed segments and long exact codes rarely match).  nullptr when every segment is
-    // keyed exactly in fewer than kFilterMinBits bits.
-    uint32_t* filter = nullptr;
-    uint32_t* filter_dir = nullptr;     // [(lmax - tau) * (tau + 1) + 1]
+    // the lists' records {key lo, key hi, start, count} in key order, closed by one of the
+    // largest key; the directory into them: group g = key >> 40 owns the entries
+    // [gdir[g], gdir[g + 1]) of dir, each {bit map, first record} (pj_device_common.h)
+    uint4* recs = nullptr;              // [lists + 1]
+    uint2* dir = nullptr;
+    uint32_t* gdir = nullptr;           // [(lmax - tau) * (tau + 1) + 1]
     // inline copies of the members' strings in index order (strings of at most kInlineMaxLen
     // bytes; nullptr otherwise): entry j of length l at inl + inl_base[l] + j * stride_of(l)
     uint8_t* inl = nullptr;
@@ -105,16 +98,15 @@ struct DevIndex {
     uint32_t* runlen = nullptr;         // [entries]
 };
 
-// Per-threshold view of a multi-tau index (serving): the bucket table and list entries of the
-// index built for tau, and the divisor for tau+1.  Indexed by tau.
+// Per-threshold view of a multi-tau index (serving): the records, directory and list entries of
+// the index built for tau, and the divisor for tau+1.  Indexed by tau.
 struct IndexRef {
-    const uint4* table;
+    const uint4* recs;
     const uint32_t* vals;
-    uint64_t mask;
+    const uint2* dir;
+    const uint32_t* gdir;
     uint32_t div_m;     // ceil(2^21 / (tau + 1)), see Div
     uint32_t present;   // 1 if an index for this tau exists
-    const uint32_t* filter;       // DevIndex::filter / filter_dir
-    const uint32_t* filter_dir;
 };
 
 // One selected substring that found a non-empty list: candidates (vals[start + m], x, i, p).
@@ -137,8 +129,7 @@ struct ProbeParams {
     const IndexRef* refs;       // [kTauMax + 1] when q_tau is set
     // index side
     const int32_t* y_lenstart;  // to know which lengths are present
-    const uint64_t* keys; const uint32_t* vals; const uint4* table; uint64_t mask;
-    const uint32_t* filter; const uint32_t* filter_dir;   // key filter (nullptr: none)
+    const uint32_t* vals; const uint4* recs; const uint2* dir; const uint32_t* gdir;
     int tau;                    // uniform tau, or the largest tau of a mixed batch
     int ymin, ymax;             // indexed lengths present
     // output
@@ -205,16 +196,14 @@ hipError_t launch_emit_segments(const DevSet& S, int tau, const int64_t* ebase_d
 hipError_t launch_gather_inline(const DevSet& S, const uint64_t* keys, const uint32_t* vals,
                                 int64_t E, int tau, const int64_t* inl_base, uint8_t* inl,
                                 hipStream_t s);
-hipError_t launch_clear_table(uint4* table, uint64_t slots, hipStream_t s);
-hipError_t launch_insert_runs(const uint64_t* keys, const uint32_t* runstart, uint32_t nruns,
-                              uint32_t E, uint4* table, uint64_t mask, hipStream_t s);
-// builds the (l, i)-blocked key filter of ngroups groups: filter_dir[0 .. ngroups] and the bits
-// of every list's key in filter (at most nruns + 2 * ngroups words, zeroed by the caller);
-// gfirst, gend, words: ngroups-entry scratch (gfirst and gend zeroed by the caller)
-hipError_t launch_filter_build(const uint64_t* keys, const uint32_t* runstart, uint32_t nruns,
-                               uint32_t ngroups, uint32_t* gfirst, uint32_t* gend, uint32_t* words,
-                               void* scan_tmp, size_t scan_bytes, uint32_t* filter_dir,
-                               uint32_t* filter, hipStream_t s);hipError_t launch_probe(const ProbeParams& P, int max_blocks, hipStream_t s);
+// the lists' records and directory: recs[0 .. nruns], gdir[0 .. ngroups] and the entries of dir
+// (at most nruns + ngroups, zeroed by the caller); bounds: 2 * ngroups words of scratch (zeroed by
+// the caller), words: ngroups
+hipError_t launch_list_dir(const uint64_t* keys, const uint32_t* runstart, uint32_t nruns, uint32_t E,
+                           uint32_t ngroups, uint32_t* bounds, uint32_t* words, void* scan_tmp,
+                           size_t scan_bytes, uint4* recs, uint32_t* gdir, uint2* dir,
+                           hipStream_t s);
+hipError_t launch_probe(const ProbeParams& P, int max_blocks, hipStream_t s);
 // order[0 .. nl * (tau+1)): the (length, slot) pairs r = dl * (tau+1) + (i-1) of a probe string
 // by decreasing multi-match window size (any order within a size)
 hipError_t launch_probe_order(int tau, int nl, int self, uint16_t* order, hipStream_t s);
