@@ -294,10 +294,11 @@ int pj_server_stop(pj_server* srv);
  * lane verifies at once. */
 typedef struct {
     int32_t verify_waves_per_cu;   /* 8, 16, 32, ..., 1024, powers of two (default 32) */
-    int32_t seg_chunk;             /* 1, 2, 4, ..., 2048, powers of two (default 4) */
+    int32_t seg_chunk;             /* 1, 2, 4, ..., 2048, powers of two (default 4; calls without
+                                      a tuned setting choose it by the number of segments) */
     int32_t big_list;              /* 16, 32, 64 or 128 (default 32) */
     int32_t probe_blocks_per_cu;   /* 4, 8 or 16 (default 8) */
-    int32_t lane_cands;            /* list-segment candidates per lane: 1 or 2 (default 2) */
+    int32_t lane_cands;            /* list-segment candidates per lane: 1 or 2 (default 1) */
     int32_t probe_map;             /* probe threads: 0 a wave over consecutive (length, slot)
                                       pairs of a few probe strings, 1 a wave over 64 probe
                                       strings with one pair (default 0) */

@@ -52,6 +52,55 @@ struct WaveAppender {
 
 constexpr int kAppendCap = 256;
 
+// End of a kernel: what the block's waves still hold, with one atomic for the block.  An atomic on
+// one address from every XCD takes about 6 ns whatever else runs, so a kernel of 8,192 waves that
+// ended with three of them each spent 150 us there; every thread of the block calls this.
+template <typename T, int CAP>
+__device__ inline void block_flush(WaveAppender<T, CAP>& app, T* out, uint64_t cap,
+                                   unsigned long long* counter)
+{
+    __shared__ uint32_t s_fill[kWaves];
+    __shared__ unsigned long long s_base;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (lane == 0) s_fill[w] = (uint32_t)app.fill;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t total = 0;
+        for (int k = 0; k < kWaves; ++k) total += s_fill[k];
+        s_base = total ? atomicAdd(counter, (unsigned long long)total) : 0ull;
+    }
+    __syncthreads();
+    unsigned long long base = s_base;
+    for (int k = 0; k < w; ++k) base += s_fill[k];
+    for (int k = lane; k < app.fill; k += 64)
+        if (base + (uint64_t)k < cap) out[base + k] = app.buf[k];
+    app.fill = 0;
+    __syncthreads();
+}
+
+// The line of statistics the calling block adds to: one of kStatShards, so that blocks do not wait
+// for each other on one address (the host adds the lines up), or with shards == 0 (a captured
+// batch: few blocks) the counters themselves.
+__device__ inline unsigned long long* stat_line(unsigned long long* counters, int shards)
+{
+    return shards ? counters + kCounterLine * (1 + (int)(blockIdx.x % (unsigned)shards)) : counters;
+}
+
+// adds the block's sum of v to *counter; every thread of the block calls this
+__device__ inline void block_add(unsigned long long* counter, uint64_t v)
+{
+    __shared__ uint64_t s_sum[kWaves];
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint64_t t = 0;
+        for (int k = 0; k < kWaves; ++k) t += s_sum[k];
+        if (t) atomicAdd(counter, (unsigned long long)t);
+    }
+    __syncthreads();
+}
+
 // ------------------------------------------------------------------------------------------
 // String arena: length histogram + validation, (length, id) keys, packing
 // ------------------------------------------------------------------------------------------
@@ -500,13 +549,10 @@ __global__ __launch_bounds__(kBlock) void k_probe(ProbeParams P, Div div)
             }
         }
     }
-    app.flush(P.hits, P.hit_cap, &P.counters[0]);
-    my_cand = wave_sum(my_cand);
-    my_sel = wave_sum(my_sel);
-    if (lane == 0) {
-        if (my_cand) atomicAdd(&P.counters[1], (unsigned long long)my_cand);
-        if (my_sel) atomicAdd(&P.counters[2], (unsigned long long)my_sel);
-    }
+    block_flush(app, P.hits, P.hit_cap, &P.counters[0]);
+    unsigned long long* line = stat_line(P.counters, P.shards);
+    block_add(&line[1], my_cand);
+    block_add(&line[2], my_sel);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -604,12 +650,9 @@ __global__ __launch_bounds__(kBlock) void k_verify(VerifyParams V, Div div)
         }
         __syncthreads();
     }
-    my_cells = wave_sum(my_cells);
-    my_miss = wave_sum(my_miss);
-    if (lane == 0) {
-        if (my_cells) atomicAdd(&V.counters[4], (unsigned long long)my_cells);
-        if (my_miss) atomicAdd(&V.counters[5], (unsigned long long)my_miss);
-    }
+    unsigned long long* line = stat_line(V.counters, V.shards);
+    block_add(&line[4], my_cells);
+    block_add(&line[5], my_miss);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -883,13 +926,10 @@ __attribute__((amdgpu_waves_per_eu(STG == 2 ? 5 : (STG || GMAXW <= 9) ? 4 : 1)))
             }
         }
     }
-    acc.flush(V.out, V.out_cap, &V.counters[3]);
-    my_cells = wave_sum(my_cells);
-    my_miss = wave_sum(my_miss);
-    if (lane == 0) {
-        if (my_cells) atomicAdd(&V.counters[4], (unsigned long long)my_cells);
-        if (my_miss) atomicAdd(&V.counters[5], (unsigned long long)my_miss);
-    }
+    block_flush(acc, V.out, V.out_cap, &V.counters[3]);
+    unsigned long long* line = stat_line(V.counters, V.shards);
+    block_add(&line[4], my_cells);
+    block_add(&line[5], my_miss);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1030,7 +1070,8 @@ void k_verify_segs(VerifyParams V, Div div,
                                                         uint64_t /* hits (unused) */,
                                                         uint64_t nseg,
                                                         const uint32_t* __restrict__ first,
-                                                        uint64_t nchunks, uint32_t seg_chunk)
+                                                        uint64_t nchunks, uint32_t seg_chunk,
+                                                        unsigned long long* ticket)
 {
     // NC candidates per lane: a list segment has 64 * NC members
     constexpr int NC = (REGY > 0 && GMAXW <= 9) ? NCT : 1;
@@ -1076,7 +1117,10 @@ void k_verify_segs(VerifyParams V, Div div,
                           (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint64_t nwaves = (uint64_t)gridDim.x * kWaves;
     uint64_t my_cells = 0, my_miss = 0;
-    for (uint64_t ch = wave; ch < nchunks; ch += nwaves) {
+    // a wave's first chunk is its own, the others are taken as waves come free: lists differ in
+    // work far more than chunks do in number
+    uint64_t ch = wave;
+    while (ch < nchunks) {
         uint64_t sg_i = ch * seg_chunk;
         const uint64_t sg_end = (sg_i + seg_chunk < nseg) ? sg_i + seg_chunk : nseg;
         uint32_t h = uniform_load(first + ch);
@@ -1313,14 +1357,15 @@ void k_verify_segs(VerifyParams V, Div div,
             ++h;
             sidx = 0;
         }
+        unsigned long long t = 0;
+        if (lane == 0) t = atomicAdd(ticket, 1ull);
+        ch = nwaves + ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)t) |
+                       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(t >> 32)) << 32);
     }
-    acc.flush(V.out, V.out_cap, &V.counters[3]);
-    my_cells = wave_sum(my_cells);
-    my_miss = wave_sum(my_miss);
-    if (lane == 0) {
-        if (my_cells) atomicAdd(&V.counters[7], (unsigned long long)my_cells);
-        if (my_miss) atomicAdd(&V.counters[5], (unsigned long long)my_miss);
-    }
+    block_flush(acc, V.out, V.out_cap, &V.counters[3]);
+    unsigned long long* line = stat_line(V.counters, V.shards);
+    block_add(&line[7], my_cells);
+    block_add(&line[5], my_miss);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1440,17 +1485,12 @@ __global__ __launch_bounds__(kBlock) void k_verify_chains(VerifyParams V, Div di
             acc.push(pass, ((uint64_t)hit.gx << 32) | gy, V.out, V.out_cap, &V.counters[3]);
         }
     }
-    acc.flush(V.out, V.out_cap, &V.counters[3]);
-    my_cells = wave_sum(my_cells);
-    my_miss = wave_sum(my_miss);
-    my_srows = wave_sum(my_srows);
-    my_scells = wave_sum(my_scells);
-    if (lane == 0) {
-        if (my_cells) atomicAdd(&V.counters[4], (unsigned long long)my_cells);
-        if (my_miss) atomicAdd(&V.counters[5], (unsigned long long)my_miss);
-        if (my_srows) atomicAdd(&V.counters[8], (unsigned long long)my_srows);
-        if (my_scells) atomicAdd(&V.counters[9], (unsigned long long)my_scells);
-    }
+    block_flush(acc, V.out, V.out_cap, &V.counters[3]);
+    unsigned long long* line = stat_line(V.counters, V.shards);
+    block_add(&line[4], my_cells);
+    block_add(&line[5], my_miss);
+    block_add(&line[8], my_srows);
+    block_add(&line[9], my_scells);
 }
 
 // Content order of the index entries: the first 8 bytes of each entry's string, big-endian,
@@ -1925,8 +1965,9 @@ __global__ __launch_bounds__(64) void k_verify_cont(VerifyParams V, Div div, Con
     my_cells = wave_sum(my_cells);
     my_miss = wave_sum(my_miss);
     if (lane == 0) {
-        if (my_cells) atomicAdd(&V.counters[4], (unsigned long long)my_cells);
-        if (my_miss) atomicAdd(&V.counters[5], (unsigned long long)my_miss);
+        unsigned long long* line = stat_line(V.counters, V.shards);
+        if (my_cells) atomicAdd(&line[4], (unsigned long long)my_cells);
+        if (my_miss) atomicAdd(&line[5], (unsigned long long)my_miss);
     }
 }
 
@@ -1948,10 +1989,11 @@ __global__ __launch_bounds__(kBlock) void k_short(const uint8_t* __restrict__ x_
                                                   uint32_t y_first, uint32_t y_count, int tau,
                                                   int self, const int32_t* __restrict__ q_tau,
                                                   uint64_t* __restrict__ out,
-                                                  uint64_t out_cap,
+                                                  uint64_t out_cap, int shards,
                                                   unsigned long long* __restrict__ counters)
 {
     const int lane = threadIdx.x & 63;
+    uint64_t examined = 0;
     for (uint32_t yi = blockIdx.x; yi < y_count; yi += gridDim.x) {
         const uint32_t gy = y_first + yi;
         const int ly = y_slen[gy];
@@ -1961,7 +2003,6 @@ __global__ __launch_bounds__(kBlock) void k_short(const uint8_t* __restrict__ x_
         if (hi_len > x_lmax) hi_len = x_lmax;
         if (hi_len < lo_len) continue;
         const uint32_t g0 = (uint32_t)x_lenstart[lo_len], g1 = (uint32_t)x_lenstart[hi_len + 1];
-        uint64_t examined = 0;
         for (uint32_t base = g0; base < g1; base += kBlock) {
             uint32_t gx = base + threadIdx.x;
             bool pass = false;
@@ -1990,9 +2031,8 @@ __global__ __launch_bounds__(kBlock) void k_short(const uint8_t* __restrict__ x_
                 }
             }
         }
-        examined = wave_sum(examined);
-        if (lane == 0 && examined) atomicAdd(&counters[6], (unsigned long long)examined);
     }
+    block_add(&stat_line(counters, shards)[6], examined);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2244,37 +2284,38 @@ hipError_t launch_slot_bucket(const Hit* hits, const unsigned long long* nh_dev,
 template <int W, int NC>
 static void verify_segs_wn(const VerifyParams& V, const Hit* big, const uint32_t* segp,
                            uint64_t nbig, uint64_t nseg, const uint32_t* first, uint64_t nchunks,
-                           uint32_t chunk, int grid, hipStream_t s)
+                           uint32_t chunk, int grid, unsigned long long* ticket, hipStream_t s)
 {
     // one candidate per lane with strings of at most 40 bytes: 44-byte lane slots, so that 8
     // blocks fit a CU's LDS
     if (NC == 1 && W <= 9 && V.y_maxlen <= 40)
         hipLaunchKernelGGL((k_verify_segs<W, (NC == 1 && W <= 9) ? 40 : 48, NC>), dim3(grid),
                            dim3(kBlock), 0, s, V, make_div(V.tau + 1), big, segp, nbig, nseg,
-                           first, nchunks, chunk);
+                           first, nchunks, chunk, ticket);
     else if (V.y_maxlen <= 48)
         hipLaunchKernelGGL((k_verify_segs<W, 48, NC>), dim3(grid), dim3(kBlock), 0, s, V,
-                           make_div(V.tau + 1), big, segp, nbig, nseg, first, nchunks, chunk);
+                           make_div(V.tau + 1), big, segp, nbig, nseg, first, nchunks, chunk, ticket);
     else if (V.y_maxlen <= 64)
         hipLaunchKernelGGL((k_verify_segs<W, 64, NC>), dim3(grid), dim3(kBlock), 0, s, V,
-                           make_div(V.tau + 1), big, segp, nbig, nseg, first, nchunks, chunk);
+                           make_div(V.tau + 1), big, segp, nbig, nseg, first, nchunks, chunk, ticket);
     else
         hipLaunchKernelGGL((k_verify_segs<W, 0, 1>), dim3(grid), dim3(kBlock), 0, s, V,
-                           make_div(V.tau + 1), big, segp, nbig, nseg, first, nchunks, chunk);
+                           make_div(V.tau + 1), big, segp, nbig, nseg, first, nchunks, chunk, ticket);
 }
 
 template <int W>
 static void verify_segs_w(const VerifyParams& V, const Hit* big, const uint32_t* segp,
                           uint64_t nbig, uint64_t nseg, const uint32_t* first, uint64_t nchunks,
-                          uint32_t chunk, int lane_cands, int grid, hipStream_t s)
+                          uint32_t chunk, int lane_cands, int grid, unsigned long long* ticket,
+                          hipStream_t s)
 {
     if constexpr (W <= 9) {
         if (lane_cands == 2) {
-            verify_segs_wn<W, 2>(V, big, segp, nbig, nseg, first, nchunks, chunk, grid, s);
+            verify_segs_wn<W, 2>(V, big, segp, nbig, nseg, first, nchunks, chunk, grid, ticket, s);
             return;
         }
     }
-    verify_segs_wn<W, 1>(V, big, segp, nbig, nseg, first, nchunks, chunk, grid, s);
+    verify_segs_wn<W, 1>(V, big, segp, nbig, nseg, first, nchunks, chunk, grid, ticket, s);
 }
 
 uint64_t seg_chunks(uint64_t nseg, int chunk) { return (nseg + (uint64_t)chunk - 1) / (uint64_t)chunk; }
@@ -2297,7 +2338,7 @@ hipError_t launch_seg_counts(const Hit* big, uint64_t nbig, int members, uint32_
 
 hipError_t launch_verify_segs(const VerifyParams& V, const Hit* big, const uint32_t* segp,
                               uint64_t nbig, uint64_t nseg, uint32_t* first, int chunk,
-                              int lane_cands, int grid, hipStream_t s)
+                              int lane_cands, int grid, unsigned long long* ticket, hipStream_t s)
 {
     if (nbig == 0 || nseg == 0) return hipSuccess;
     if (chunk < 1 || grid < 1 || lane_cands < 1 || lane_cands > 2) return hipErrorInvalidValue;
@@ -2307,11 +2348,11 @@ hipError_t launch_verify_segs(const VerifyParams& V, const Hit* big, const uint3
                        nbig, nchunks, c, first);
     const int w = V.tau + 1;
     const int lc = lane_cands;
-    if (w <= 5) verify_segs_w<5>(V, big, segp, nbig, nseg, first, nchunks, c, lc, grid, s);
-    else if (w <= 9) verify_segs_w<9>(V, big, segp, nbig, nseg, first, nchunks, c, lc, grid, s);
-    else if (w <= 17) verify_segs_w<17>(V, big, segp, nbig, nseg, first, nchunks, c, lc, grid, s);
-    else if (w <= 33) verify_segs_w<33>(V, big, segp, nbig, nseg, first, nchunks, c, lc, grid, s);
-    else verify_segs_w<64>(V, big, segp, nbig, nseg, first, nchunks, c, lc, grid, s);
+    if (w <= 5) verify_segs_w<5>(V, big, segp, nbig, nseg, first, nchunks, c, lc, grid, ticket, s);
+    else if (w <= 9) verify_segs_w<9>(V, big, segp, nbig, nseg, first, nchunks, c, lc, grid, ticket, s);
+    else if (w <= 17) verify_segs_w<17>(V, big, segp, nbig, nseg, first, nchunks, c, lc, grid, ticket, s);
+    else if (w <= 33) verify_segs_w<33>(V, big, segp, nbig, nseg, first, nchunks, c, lc, grid, ticket, s);
+    else verify_segs_w<64>(V, big, segp, nbig, nseg, first, nchunks, c, lc, grid, ticket, s);
     return hipGetLastError();
 }
 
@@ -2521,7 +2562,7 @@ static void short_w(const DevSet& P, const DevSet& Y, int tau, int self, const i
     unsigned grid = y_count < 65536 ? y_count : 65536;
     hipLaunchKernelGGL((k_short<W>), dim3(grid), dim3(kBlock), 0, s, P.sarena, P.slen, P.lenstart,
                        P.gbase, P.lmax, Y.sarena, Y.slen, Y.lenstart, Y.gbase, y_first, y_count,
-                       tau, self, q_tau, out, cap, ctr);
+                       tau, self, q_tau, out, cap, kStatShards, ctr);
 }
 
 hipError_t launch_short_path(const DevSet& P, const DevSet& Y, int tau, int self,
@@ -2670,7 +2711,7 @@ static void graph_verify_short(const GraphBatch& G, hipStream_t s)
         hipLaunchKernelGGL((k_short<W>), dim3(grid), dim3(kBlock), 0, s, P.x_arena, P.x_slen,
                            P.x_lenstart, P.x_gbase, kLenMax, G.y_arena, G.y_slen, G.y_lenstart,
                            G.y_gbase, G.y_first, G.y_count, P.tau, 0, P.q_tau, G.verify.out,
-                           G.verify.out_cap, G.verify.counters);
+                           G.verify.out_cap, 0, G.verify.counters);
     }
 }
 

@@ -32,6 +32,16 @@ constexpr size_t kPinnedOutputMin = 1u << 20;
 // Below this many candidates the batched path verifies the hits in probe order, in one launch.
 constexpr uint64_t kBucketMinCandidates = 1ull << 20;
 
+// List segments per wave chunk without a tuned setting.  A chunk sets a hit up anew where it begins
+// inside one, and its ticket is an atomic on one address (6 ns each, one after another), so chunks
+// are as long as the balance between some 8,192 waves allows: at least four a wave, at most 256
+// segments.  Measured on short strings, list kernel: 10^6 at tau = 4 (1.6x10^8 segments) 80 ms with
+// 4, 50 with 32, 48 with 128-256; 10^5 at tau = 3 (3x10^5) 0.24, 0.19 and 0.37 ms.
+static int auto_seg_chunk(uint64_t nseg)
+{
+    return (int)std::max<uint64_t>(1, std::min<uint64_t>(nseg / 32768, 256));
+}
+
 // ------------------------------------------------------------------------------------------
 // Errors and per-thread state
 // ------------------------------------------------------------------------------------------
@@ -663,6 +673,11 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
     const bool entries = spec.q_tau ? spec.has_entries : (spec.X && spec.X->entries > 0);
     int t_probe0 = tm.mark();
     unsigned long long c[kJoinCounters];
+    // c[0 .. kCounterLine): the counters, each with its statistics lines added
+    auto add_lines = [&]() {
+        for (int k = 0; k < kCounterLine; ++k)
+            for (int l = 1; l <= kStatShards; ++l) c[k] += c[l * kCounterLine + k];
+    };
     for (int attempt = 0; attempt < 2; ++attempt) {
     J.hits = (Hit*)W.get("join.hits", sizeof(Hit) * (size_t)hit_cap);
     if (attempt > 0)
@@ -716,6 +731,7 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
         }
         pp.hits = J.hits; pp.hit_cap = hit_cap;
         pp.counters = J.counters;
+        pp.shards = kStatShards;
         int k0 = tm.mark();
         hip_check(launch_probe(pp, device_cus() * J.tp.probe_blocks_per_cu, st), "probe");
         int k1 = tm.mark();
@@ -723,6 +739,7 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
     }
     readback(c, J.counters, sizeof c, st);
     sync_readback(st);
+    add_lines();
     if (c[0] <= hit_cap) break;
     hit_cap = c[0];
     J.kernel_marks.clear();
@@ -884,6 +901,7 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
             vp.exact_len = spec.sym.exact_len;
             vp.out = J.out; vp.out_cap = cap;
             vp.counters = J.counters;
+            vp.shards = kStatShards;
             int k0 = tm.mark();
             if (batched) {
                 // small lists, one launch per length class: long strings by row blocks with
@@ -958,10 +976,14 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
                     stats.verify_launches += 1;
                     stats.list_launches += 1;
                 }
+                int chunk_c[kLenClasses] = {};
                 uint64_t max_seg_chunks = 0;
-                for (int c = 0; c < kLenClasses; ++c)
+                for (int c = 0; c < kLenClasses; ++c) {
+                    if (cls_nseg[c] == 0) continue;
+                    chunk_c[c] = J.tp.tuned ? J.tp.seg_chunk : auto_seg_chunk(cls_nseg[c]);
                     max_seg_chunks = std::max<uint64_t>(max_seg_chunks,
-                                                        seg_chunks(cls_nseg[c], J.tp.seg_chunk));
+                                                        seg_chunks(cls_nseg[c], chunk_c[c]));
+                }
                 uint32_t* first2 = max_seg_chunks
                     ? (uint32_t*)W.get("join.first2", sizeof(uint32_t) * (size_t)max_seg_chunks)
                     : nullptr;
@@ -969,15 +991,16 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
                     const uint64_t nseg = cls_nseg[c];
                     if (nseg == 0) continue;
                     const uint64_t o = cls_off[c], nb = cls_off[c + 1] - o;
-                    const uint64_t nchunks = seg_chunks(nseg, J.tp.seg_chunk);
+                    const uint64_t nchunks = seg_chunks(nseg, chunk_c[c]);
                     const uint64_t waves = std::min<uint64_t>(
                         nchunks, (uint64_t)device_cus() * J.tp.verify_waves_per_cu);
                     VerifyParams vc = vp;
                     vc.y_maxlen = class_maxlen(c, Y.lmax);
                     const int s0 = tm.mark();
                     hip_check(launch_verify_segs(vc, bigp + o, segp + o + c, nb, nseg, first2,
-                                                 J.tp.seg_chunk, J.tp.lane_cands,
-                                                 (int)((waves + 3) / 4), st),
+                                                 chunk_c[c], J.tp.lane_cands,
+                                                 (int)((waves + 3) / 4),
+                                                 J.counters + kTicketWord + c, st),
                               "verify_segs");
                     const int s1 = tm.mark();
                     J.kernel_marks.push_back({s0, s1, 2});
@@ -997,6 +1020,7 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
                                     st), "short_path");
         readback(c, J.counters, sizeof c, st);
         sync_readback(st);
+        add_lines();
         if (c[3] <= cap) break;
         cap = c[3];
     }

@@ -135,6 +135,7 @@ struct ProbeParams {
     // output
     Hit* hits; uint64_t hit_cap;
     unsigned long long* counters;   // [0] hits, [1] candidates, [2] selected
+    int shards;                     // statistics lines after them (0: none)
     // device-resident probe count (captured batches): threads = *nx_dev * nl * (tau + 1)
     const uint32_t* nx_dev;
     SymMap sym;                 // the indexed set's symbol map (keys)
@@ -164,6 +165,7 @@ struct VerifyParams {
     const IndexRef* refs;                                 // [kTauMax + 1] when q_tau is set
     uint64_t* out; uint64_t out_cap;                      // accepted (gx << 32 | gy)
     unsigned long long* counters;    // [3] accepted, [4] cells, [5] guard misses, [7] list-segment cells
+    int shards;                      // statistics lines after them (0: none)
     // device-resident sizes (captured batches): [0] hits, [1] candidates, [2] wave chunks;
     // when set they replace nhits, ncand and the launch's chunk count
     const unsigned long long* dev_counts;
@@ -176,9 +178,13 @@ struct VerifyParams {
     const uint32_t* runlen;
     int self;
 };
-// counters [8] rows and [9] cells that shared-prefix verification took from an earlier
-// member's DP instead of computing them
-constexpr int kJoinCounters = 12;
+// Join counters: a line of kCounterLine words ([0] hits, [3] accepted: positions that blocks
+// reserve; [10 + c] the chunk ticket of length class c's list kernel), then kStatShards lines of
+// statistics in the same places, which the host adds up.  [8] rows and [9] cells that shared-prefix
+// verification took from an earlier member's DP instead of computing them.
+constexpr int kCounterLine = 16, kStatShards = 32;
+constexpr int kTicketWord = 10;
+constexpr int kJoinCounters = kCounterLine * (1 + kStatShards);
 
 // ---- launchers (pj_device.hip) ----
 hipError_t launch_length_hist(const int32_t* offs, int64_t n, int32_t* lcount, int32_t* err,
@@ -221,14 +227,15 @@ hipError_t launch_slot_bucket(const Hit* hits, const unsigned long long* nh_dev,
                               size_t scan_bytes, Hit* out, hipStream_t s);
 // list-segment verification of the lists with >= big candidates (hits big[0 .. nbig), segp =
 // exclusive scan of ceil(count / seg_members), nseg segments, `chunk` segments per wave chunk; first:
-// seg_chunks(nseg, chunk) u32 of scratch)
+// seg_chunks(nseg, chunk) u32 of scratch; ticket: a zeroed word)
 // list segments of `members` candidates each (seg_members: what k_verify_segs expects)
 int seg_members(int y_maxlen, int tau, int lane_cands);
 hipError_t launch_seg_counts(const Hit* big, uint64_t nbig, int members, uint32_t* segs,
                              hipStream_t s);
 hipError_t launch_verify_segs(const VerifyParams& V, const Hit* big, const uint32_t* segp,
                               uint64_t nbig, uint64_t nseg, uint32_t* first, int chunk,
-                              int lane_cands, int grid, hipStream_t s);
+                              int lane_cands, int grid, unsigned long long* ticket,
+                              hipStream_t s);
 uint64_t seg_chunks(uint64_t nseg, int chunk);
 // shared-prefix verification (Sec. 5.3) of the big lists: a lane takes a chain of up to
 // kChainMembers consecutive members of a content-ordered list.  chains: per big hit, its chain

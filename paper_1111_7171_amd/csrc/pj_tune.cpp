@@ -106,6 +106,7 @@ void parse_file(const char* path, std::map<Key, Entry>& table)
         char arch[128];
         int tau, lb;
         Entry e;
+        e.p.tuned = true;
         const int got = sscanf(line, "%127s %d %d %d %d %d %d %d %d %lf", arch, &tau, &lb,
                                &e.p.verify_waves_per_cu, &e.p.seg_chunk, &e.p.big_list,
                                &e.p.probe_blocks_per_cu, &e.p.lane_cands, &e.p.probe_map, &e.ms);
@@ -222,6 +223,7 @@ int pj_tune(const pj_strings* S, int32_t tau, const pj_options* opt, pj_tune_res
             return best;
         };
         TuneParams cur;
+        cur.tuned = true;
         (void)measure(cur);                  // warm-up: allocations, code objects, caches
         const double ms_default = measure(cur);
         double ms_best = ms_default;
