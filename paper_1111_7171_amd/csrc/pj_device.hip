@@ -50,6 +50,13 @@ struct WaveAppender {
     }
 };
 
+// a wave-uniform load through the scalar cache (read-only data)
+template <typename T>
+__device__ inline T uniform_load(const T* p)
+{
+    return *(const __attribute__((address_space(4))) T*)p;
+}
+
 constexpr int kAppendCap = 256;
 
 // End of a kernel: what the block's waves still hold, with one atomic for the block.  An atomic on
@@ -334,20 +341,28 @@ __global__ __launch_bounds__(kBlock) void k_dir_fill(const uint4* __restrict__ r
 // Probe: multi-match substring selection + list lookup (Sec. 4.2, Algorithm 2)
 // ------------------------------------------------------------------------------------------
 
-// One thread per (probe string x, probed length l, slot i).  The thread walks the window
-// [bot_i, top_i] with a rolling hash of x[p, l_i], looks each substring up, trims the list to
-// the members visited before x (self-join, l == |x|), and appends non-empty lookups as hits.
-// Threads map to triples string-major (a wave covers consecutive (l, i) pairs of one or a few
-// probe strings) or, with XMAJ, pair-major over blocks of 64 probe strings (a wave's lanes are
-// 64 consecutive probe strings with one (l, i) pair: windows of one size when the strings have
-// a few pairs each).
+// One thread per (probe string x, probed length l, slot i), a wave over consecutive (l, i) pairs of
+// one or a few probe strings.  The thread walks the window [bot_i, top_i] with a rolling code of
+// x[p, l_i], looks each substring up, trims the list to the members visited before x (self-join,
+// l == |x|), and appends non-empty lookups as hits.  Used for query batches (every string with a
+// threshold of its own), in plain mode and where the autotuner asks for it.
 constexpr int kProbeStep = 2;      // window positions a probe thread takes per step
 
-template <bool XMAJ>
+// Members of the list [start, start + count) visited before gx (lists are in ascending g).
+__device__ inline uint32_t members_before(const uint32_t* __restrict__ vals, uint32_t start,
+                                          uint32_t count, uint32_t gx)
+{
+    uint32_t a = 0, b = count;
+    while (a < b) {
+        const uint32_t m = (a + b) >> 1;
+        if (vals[start + m] < gx) a = m + 1; else b = m;
+    }
+    return a;
+}
+
 __global__ __launch_bounds__(kBlock) void k_probe(ProbeParams P, Div div)
 {
-    // bytes of probe strings a wave stages in LDS
-    constexpr int kProbeStage = XMAJ ? 4096 : 2048;
+    constexpr int kProbeStage = 2048;      // bytes of probe strings a wave stages in LDS
     __shared__ Hit s_hits[kWaves][kAppendCap];
     __shared__ uint4 s_xs[kWaves][kProbeStage / 16];
     __shared__ uint16_t s_sym[256];
@@ -375,27 +390,12 @@ __global__ __launch_bounds__(kBlock) void k_probe(ProbeParams P, Div div)
         const uint64_t tw = t0 + (threadIdx.x & ~63u);
         uint32_t g_first = 0;
         bool staged = false;
-        // XMAJ: threads t = block * 64 * per + pair * 64 + lane, string g_begin + block*64 + lane
-        uint32_t gx_t = 0, r0 = 0;
-        if constexpr (XMAJ) {
-            const uint64_t b = t / (64 * per), q = t % (64 * per);
-            gx_t = P.g_begin + (uint32_t)(b * 64 + q % 64);
-            r0 = (uint32_t)(q / 64);
-            valid = valid && gx_t < P.g_begin + P.nx;
-        } else {
-            gx_t = P.g_begin + (uint32_t)(t / per);
-            r0 = (uint32_t)(t % per);
-        }
+        const uint32_t gx_t = P.g_begin + (uint32_t)(t / per);
+        const uint32_t r0 = (uint32_t)(t % per);
         if (tw < nthreads) {
-            uint32_t g_last;
-            if constexpr (XMAJ) {
-                g_first = P.g_begin + (uint32_t)(tw / (64 * per)) * 64u;
-                g_last = min(g_first + 63u, P.g_begin + P.nx - 1u);
-            } else {
-                const uint64_t tl = min(tw + 63, nthreads - 1);
-                g_first = P.g_begin + (uint32_t)(tw / per);
-                g_last = P.g_begin + (uint32_t)(tl / per);
-            }
+            const uint64_t tl = min(tw + 63, nthreads - 1);
+            g_first = P.g_begin + (uint32_t)(tw / per);
+            const uint32_t g_last = P.g_begin + (uint32_t)(tl / per);
             const int n0 = P.x_slen[g_first];
             const int64_t bytes = (int64_t)(g_last - g_first + 1) * stride_of(n0);
             if (P.x_slen[g_last] == n0 && bytes <= kProbeStage) {
@@ -529,13 +529,7 @@ __global__ __launch_bounds__(kBlock) void k_probe(ProbeParams P, Div div)
                 if (maybe[u]) {
                     const bool hit = find_record(recs, rn[u], key[u], rv[u], &start, &count);
                     if (hit && P.self && l == n) {
-                        // keep members with g < gx (lists are ascending in g)
-                        uint32_t a = 0, b = count;
-                        while (a < b) {
-                            const uint32_t m = (a + b) >> 1;
-                            if (vals[start + m] < gx) a = m + 1; else b = m;
-                        }
-                        count = a;
+                        count = members_before(vals, start, count, gx);
                     }
                     if (!hit) count = 0;
                 }
@@ -546,6 +540,362 @@ __global__ __launch_bounds__(kBlock) void k_probe(ProbeParams P, Div div)
                 hh.meta = (uint32_t)(p - 1) | ((uint32_t)(i - 1) << 11) | ((uint32_t)l << 17);
                 app.push(found, hh, P.hits, P.hit_cap, &P.counters[0]);
                 if (found) my_cand += count;
+            }
+        }
+    }
+    block_flush(app, P.hits, P.hit_cap, &P.counters[0]);
+    unsigned long long* line = stat_line(P.counters, P.shards);
+    block_add(&line[1], my_cand);
+    block_add(&line[2], my_sel);
+}
+
+// Pair-major probe.  A wave takes a tile of up to 64 probe strings of one length and, one after
+// another, (length, slot) pairs: the partition, the window and the group's directory bounds are the
+// same for its 64 lanes (scalar work), every lane walks a window of the same size, and consecutive
+// waves look into the groups of a few lengths, whose directory and records stay in L2.  The strings
+// are staged in lane slots of an odd number of words, so reads at one offset hit distinct banks.
+// What bounds it is the random 8- and 16-byte reads of directory and records and, where most
+// lookups hit, the atomic per 256 hits that reserves their place.  Probe of 10^6 short strings at
+// tau = 1 / 2 / 4: 0.37 / 0.64 / 2.62 ms string-major, 0.09 / 0.30 / 2.17 here; 5x10^5 query lines at
+// tau = 6 1.48 -> 0.67 ms.
+constexpr int kTileStep = 4;       // window positions in flight
+constexpr uint32_t kStripes = 32;  // four an XCD: lengths differ in work
+
+template <int MAXQ>
+__global__ __launch_bounds__(kBlock) void k_probe_tiles(ProbeParams P, Div div, ProbeTiles T)
+{
+    constexpr int SW = 4 * MAXQ + 1;               // words of a lane's slot
+    __shared__ Hit s_hits[kWaves][kAppendCap];
+    __shared__ uint32_t s_x[kWaves][64 * SW];
+    __shared__ uint16_t s_sym[256];
+    s_sym[threadIdx.x] = P.sym.code[threadIdx.x];
+    __syncthreads();
+    const int sym_bits = P.sym.bits, exact_len = P.sym.exact_len;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    WaveAppender<Hit, kAppendCap> app{s_hits[w], 0};
+    uint32_t* slot = s_x[w] + lane * SW;
+    using LdsU8 = const __attribute__((address_space(3))) uint8_t*;
+    const LdsU8 xs = (LdsU8)slot;
+    const int tau = P.tau, T1 = tau + 1;
+    const uint32_t pairs = (uint32_t)P.nl * (uint32_t)T1;
+    const uint32_t f0 = T.first[lane], f1 = T.first[64 + lane];
+    uint64_t my_sel = 0, my_cand = 0;
+    // Workgroups go to the XCDs round robin, and each XCD has an L2 of its own: an XCD takes every
+    // eighth of kStripes stripes of consecutive tiles (strings of a few lengths, so of a few
+    // groups), and its waves run through the stripe pair group by pair group.
+    const uint32_t xcd = blockIdx.x & 7u, stripe = (T.tiles + kStripes - 1) / kStripes;
+    const uint32_t units = kStripes / 8 * stripe * T.groups;          // of an XCD
+    for (uint32_t u = (blockIdx.x >> 3) * kWaves + (uint32_t)w; u < units;
+         u += (gridDim.x >> 3) * kWaves) {
+        const uint32_t su = u / stripe, part = su % T.groups;
+        const uint32_t tile = (su / T.groups * 8u + xcd) * stripe + u % stripe;
+        if (tile >= T.tiles) continue;
+        const int n = __popcll(__ballot(f0 <= tile)) + __popcll(__ballot(f1 <= tile)) - 1;
+        const uint32_t n_first = (uint32_t)uniform_load(P.x_lenstart + n);
+        const uint32_t g0 = n_first + (tile - T.first[n]) * 64u;
+        const uint32_t cnt = min((uint32_t)uniform_load(P.x_lenstart + n + 1) - g0, 64u);
+        const bool mine = (uint32_t)lane < cnt;
+        const uint32_t gx = g0 + (uint32_t)lane;
+        {
+            const int nq = (n + 15) >> 4;
+            const uint4* src = reinterpret_cast<const uint4*>(
+                P.x_arena + uniform_load(P.x_gbase + n) + (int64_t)(g0 - n_first) * stride_of(n));
+            // the previous unit's reads were issued before these writes (in order)
+#pragma unroll
+            for (int q = 0; q < MAXQ; ++q) {
+                if (q < nq && mine) {
+                    const uint4 v = src[lane * nq + q];
+                    slot[4 * q] = v.x; slot[4 * q + 1] = v.y;
+                    slot[4 * q + 2] = v.z; slot[4 * q + 3] = v.w;
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+        // the unit's pairs, 64 at a time: a lane finds one pair's window and directory block, then
+        // the wave takes the pairs that have something to look up one by one
+        for (uint32_t rb = part; rb < pairs; rb += 64 * T.groups) {
+            const uint32_t rl = rb + (uint32_t)lane * T.groups;
+            int v_lo = 1, v_hi = 0, v_len = 0, v_l = 0, v_i = 0;
+            uint32_t v_first = 0, v_dk = 0;
+            if (rl < pairs) {
+                const int dl = (int)(rl / (uint32_t)T1);
+                v_i = (int)(rl % (uint32_t)T1) + 1;
+                v_l = P.self ? n - dl : n - tau + dl;
+                if (v_l >= T1) {
+                    // substrings selected whether or not strings of length l exist (Algorithm 1
+                    // selects for every l in the length window): for multi-match the Lemma 2
+                    // count, otherwise each slot's window size
+                    const Seg sg = partition_seg(v_l, v_i, tau, div);
+                    v_len = sg.len;
+                    select_window(P.selection, n, v_l, tau, v_i, sg, &v_lo, &v_hi);
+                    const int d = n - v_l;
+                    if (P.selection != 0) my_sel += (uint64_t)cnt * (uint64_t)max(v_hi - v_lo + 1, 0);
+                    else if (v_i == 1)
+                        my_sel += (uint64_t)cnt * (uint64_t)((tau * tau - d * d) / 2 + tau + 1);
+                    if (v_l >= P.ymin && v_l <= P.ymax &&
+                        P.y_lenstart[v_l + 1] > P.y_lenstart[v_l]) {
+                        const uint32_t grp = (uint32_t)((v_l - T1) * T1 + (v_i - 1));
+                        v_first = P.gdir[grp];
+                        v_dk = dir_bits(v_first, P.gdir[grp + 1]);
+                    } else {
+                        v_hi = 0;
+                    }
+                }
+            }
+            for (uint64_t todo = __ballot(v_lo <= v_hi); todo; todo &= todo - 1) {
+                const int q = __ffsll((unsigned long long)todo) - 1;
+                const int lo = __builtin_amdgcn_readlane(v_lo, q);
+                const int hi = __builtin_amdgcn_readlane(v_hi, q);
+                const int len = __builtin_amdgcn_readlane(v_len, q);
+                const int l = __builtin_amdgcn_readlane(v_l, q);
+                const int i = __builtin_amdgcn_readlane(v_i, q);
+                const uint32_t dk = (uint32_t)__builtin_amdgcn_readlane((int)v_dk, q);
+                const uint2* dir = P.dir + (uint32_t)__builtin_amdgcn_readlane((int)v_first, q);
+                const uint64_t gkey = (uint64_t)((l - T1) * T1 + (i - 1)) << kHashBits;
+                const bool exact = len <= exact_len;
+                const uint64_t cmask = exact ? (1ull << (len * sym_bits)) - 1ull : 0ull;
+                const uint64_t top = exact ? 0ull : pow_hash(len);
+                uint64_t h = 0;
+                if (exact)
+                    for (int k = 0; k < len; ++k)
+                        h = (h << sym_bits) | (uint64_t)s_sym[xs[lo - 1 + k]];
+                else
+                    for (int k = 0; k < len; ++k)
+                        h = h * kHashBase + (uint64_t)xs[lo - 1 + k] + 1ull;
+                for (int p0 = lo; p0 <= hi; p0 += kTileStep) {
+                    uint64_t key[kTileStep];
+                    uint2 de[kTileStep];
+#pragma unroll
+                    for (int v = 0; v < kTileStep; ++v) {
+                        const int p = p0 + v;
+                        de[v] = make_uint2(0u, 0u);
+                        key[v] = 0;
+                        if (p > hi) continue;
+                        if (p > lo) {
+                            if (exact)
+                                h = ((h << sym_bits) | (uint64_t)s_sym[xs[p - 2 + len]]) & cmask;
+                            else
+                                h = roll_hash(h, xs[p - 2], xs[p - 2 + len], top);
+                        }
+                        key[v] = gkey | spread_code(len, h, exact_len);
+                        if (mine) de[v] = dir[dir_entry(key[v], dk)];
+                    }
+                    uint4 rv[kTileStep];
+#pragma unroll
+                    for (int v = 0; v < kTileStep; ++v) {
+                        const uint32_t bit = dir_bit(key[v], dk);
+                        rv[v] = make_uint4(0u, 0u, 0u, 0u);
+                        if ((de[v].x >> bit) & 1u) {
+                            de[v].y += (uint32_t)__popc(de[v].x & ((1u << bit) - 1u));
+                            rv[v] = P.recs[de[v].y];
+                        } else {
+                            de[v].x = 0;
+                        }
+                    }
+#pragma unroll
+                    for (int v = 0; v < kTileStep; ++v) {
+                        if (__ballot(de[v].x != 0) == 0) continue;
+                        uint32_t start = 0, count = 0;
+                        if (de[v].x != 0) {
+                            const bool hit =
+                                find_record(P.recs, de[v].y, key[v], rv[v], &start, &count);
+                            if (!hit) count = 0;
+                            else if (P.self && l == n)
+                                count = members_before(P.vals, start, count, gx);
+                        }
+                        Hit hh;
+                        hh.gx = gx; hh.start = start; hh.count = count;
+                        hh.meta = (uint32_t)(p0 + v - 1) | ((uint32_t)(i - 1) << 11) |
+                                  ((uint32_t)l << 17);
+                        app.push(count > 0, hh, P.hits, P.hit_cap, &P.counters[0]);
+                        my_cand += count;
+                    }
+                }
+            }
+        }
+    }
+    block_flush(app, P.hits, P.hit_cap, &P.counters[0]);
+    unsigned long long* line = stat_line(P.counters, P.shards);
+    block_add(&line[1], my_cand);
+    block_add(&line[2], my_sel);
+}
+
+// Multi-match probe of long strings, a block per string.  Hashing every window's first segment byte
+// by byte and rolling on made a chain of thousands of multiplications per lane (the first segments
+// alone are nl * n bytes a string), and lanes with small windows waited for those with large ones.
+// Here the block computes the polynomial hashes of all prefixes once (a scan over the bytes:
+// H(ab) = H(a) B^|b| + H(b)), so any segment's hash is H[p + len] - H[p] B^len; notes every pair's
+// directory block in LDS; and takes the windows' positions from one list, 256 at a time.  The next
+// string's bytes are read meanwhile.  Vector issue bounds it (64-bit multiplications).  10^5 long
+// strings at tau = 16: 1.98 -> 1.20 ms.  NMAX: the longest string (LDS).
+template <int NMAX>
+__global__ __launch_bounds__(kBlock) void k_probe_long(ProbeParams P, Div div, ProbeItems I,
+                                                       uint32_t g_first, uint32_t g_end)
+{
+    constexpr int CAP = 64;                        // hits are rare
+    constexpr int U = 4;                           // positions a thread has in flight
+    __shared__ Hit s_hits[kWaves][CAP];
+    __shared__ uint64_t s_pre[NMAX];               // hashes of the prefixes of 0 .. NMAX - 1 bytes
+    __shared__ uint4 s_b4[NMAX / 16];              // the string's bytes
+    __shared__ uint32_t s_first[kItemPairs], s_grp[kItemPairs], s_pair[kItemPairs];
+    __shared__ uint64_t s_wave[kWaves], s_pow[4];
+    __shared__ uint16_t s_sym[256];
+    s_sym[threadIdx.x] = P.sym.code[threadIdx.x];
+    const uint8_t* s_b = reinterpret_cast<const uint8_t*>(s_b4);
+    const int sym_bits = P.sym.bits, exact_len = P.sym.exact_len;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    WaveAppender<Hit, CAP> app{s_hits[w], 0};
+    const int tau = P.tau, T1 = tau + 1;
+    const uint32_t pairs = (uint32_t)P.nl * (uint32_t)T1;
+    uint64_t my_sel = 0, my_cand = 0;
+    // a string's length and the thread's 16 bytes of it
+    auto fetch = [&](uint32_t gx, int& n, uint4& v) {
+        n = __builtin_amdgcn_readfirstlane((int)P.x_slen[gx]);
+        const uint4* src = reinterpret_cast<const uint4*>(
+            P.x_arena + uniform_load(P.x_gbase + n) +
+            (int64_t)(gx - (uint32_t)uniform_load(P.x_lenstart + n)) * stride_of(n));
+        if ((int)threadIdx.x < (n + 15) / 16) v = src[threadIdx.x];
+    };
+    uint32_t gx = g_first + blockIdx.x;
+    int n_next = 0;
+    uint4 v_next = make_uint4(0u, 0u, 0u, 0u);
+    if (gx < g_end) fetch(gx, n_next, v_next);
+    for (; gx < g_end; gx += gridDim.x) {
+        const int n = n_next;
+        __syncthreads();                           // the previous string's reads are done
+        if ((int)threadIdx.x < (n + 15) / 16) s_b4[threadIdx.x] = v_next;
+        if (gx + gridDim.x < g_end) fetch(gx + gridDim.x, n_next, v_next);
+        // segments of the probed lengths have at most four lengths, from qlo on
+        const int qlo = div(max(n - tau, T1));
+        if (threadIdx.x < 4) s_pow[threadIdx.x] = pow_hash(qlo + (int)threadIdx.x + 1);
+        __syncthreads();
+        // prefix hashes: thread t takes bytes [t * c, t * c + c) (bytes past the end count as
+        // nothing: they only enter prefixes that are never read)
+        const int c = (n + kBlock - 1) / kBlock;
+        const int b0 = (int)threadIdx.x * c;
+        uint64_t v = 0, bc = 1;
+        for (int k = 0; k < c; ++k) {
+            v = v * kHashBase + (b0 + k < n ? (uint64_t)s_b[b0 + k] + 1ull : 0ull);
+            bc *= kHashBase;
+        }
+        uint64_t mul = bc, bl = 1;                 // B^(bytes a lane's v covers), B^(lane * c)
+#pragma unroll
+        for (int b = 0; b < 6; ++b) {
+            const uint64_t before = __shfl_up(v, 1 << b, 64);
+            if (lane >= 1 << b) v += before * mul;
+            if ((lane >> b) & 1) bl *= mul;
+            mul *= mul;
+        }
+        if (lane == 63) s_wave[w] = v;
+        uint64_t run = __shfl_up(v, 1, 64);
+        if (lane == 0) run = 0;
+        __syncthreads();
+        uint64_t carry = 0;                        // the waves before: 64 * c bytes each
+        for (int k = 0; k < w; ++k) carry = carry * mul + s_wave[k];
+        run += carry * bl;
+        if (threadIdx.x == 0) s_pre[0] = 0;
+        for (int k = 0; k < c && b0 + k < n; ++k) {
+            run = run * kHashBase + (uint64_t)s_b[b0 + k] + 1ull;
+            s_pre[b0 + k + 1] = run;
+        }
+        for (int ch = 0; ch < I.chunks; ++ch) {
+            const uint32_t rbase = (uint32_t)ch * kItemPairs;
+            if (ch > 0) __syncthreads();           // the previous chunk's reads are done
+            for (uint32_t q = threadIdx.x; q < (uint32_t)kItemPairs && rbase + q < pairs; q += kBlock) {
+                const uint32_t r = rbase + q;
+                const int dl = (int)(r / (uint32_t)T1);
+                const int i = (int)(r % (uint32_t)T1) + 1;
+                const int l = P.self ? n - dl : n - tau + dl;
+                uint32_t info = 0;                 // no segment: nothing to look up
+                if (l >= T1) {
+                    // the Lemma 2 count, whether or not strings of length l exist (Algorithm 1
+                    // selects for every l in the length window)
+                    const int d = n - l;
+                    if (i == 1) my_sel += (uint64_t)((tau * tau - d * d) / 2 + tau + 1);
+                    if (l >= P.ymin && l <= P.ymax && P.y_lenstart[l + 1] > P.y_lenstart[l]) {
+                        const Seg sg = partition_seg(l, i, tau, div);
+                        const int rr = tau + 1 - i;
+                        const int p0 = max(sg.p - (i - 1), sg.p + d - rr);   // unclipped start
+                        const uint32_t grp = (uint32_t)((l - T1) * T1 + (i - 1));
+                        const uint32_t first = P.gdir[grp];
+                        s_first[q] = first;
+                        s_grp[q] = grp;
+                        info = (uint32_t)sg.len | dir_bits(first, P.gdir[grp + 1]) << 11 |
+                               (uint32_t)(p0 + 128) << 16;
+                    }
+                }
+                s_pair[q] = info;
+            }
+            __syncthreads();
+            const uint32_t i0 = uniform_load(I.chunk + ch), i1 = uniform_load(I.chunk + ch + 1);
+            for (uint32_t base = i0 + (uint32_t)w * 64u; base < i1; base += kBlock * U) {
+                uint32_t q[U];
+                int p[U];
+                uint64_t key[U];
+                uint2 de[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t it = base + (uint32_t)(u * kBlock + lane);
+                    q[u] = it < i1 ? I.items[it] : ~0u;
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    p[u] = 0;
+                    key[u] = 0;
+                    de[u] = make_uint2(0u, 0u);
+                    if (q[u] == ~0u) continue;
+                    const int s = (int)(q[u] & 255u);
+                    q[u] = (q[u] >> 8) - rbase;
+                    const uint32_t info = s_pair[q[u]];
+                    const int len = (int)(info & 2047u);
+                    p[u] = (int)(info >> 16) - 128 + s;
+                    if (len == 0 || p[u] < 1 || p[u] > n - len + 1) continue;
+                    uint64_t h = 0;
+                    if (len <= exact_len)
+                        for (int k = 0; k < len; ++k)
+                            h = (h << sym_bits) | (uint64_t)s_sym[s_b[p[u] - 1 + k]];
+                    else
+                        h = s_pre[p[u] - 1 + len] - s_pre[p[u] - 1] * s_pow[len - qlo];
+                    key[u] = (uint64_t)s_grp[q[u]] << kHashBits | spread_code(len, h, exact_len);
+                    const uint32_t k = (info >> 11) & 31u;
+                    de[u] = P.dir[s_first[q[u]] + dir_entry(key[u], k)];
+                    p[u] |= (int)(dir_bit(key[u], k) << 16);
+                }
+                uint4 rv[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t bit = (uint32_t)p[u] >> 16;
+                    rv[u] = make_uint4(0u, 0u, 0u, 0u);
+                    if ((de[u].x >> bit) & 1u) {
+                        de[u].y += (uint32_t)__popc(de[u].x & ((1u << bit) - 1u));
+                        rv[u] = P.recs[de[u].y];
+                    } else {
+                        de[u].x = 0;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (__ballot(de[u].x != 0) == 0) continue;
+                    uint32_t start = 0, count = 0;
+                    Hit hh{};
+                    if (de[u].x != 0) {
+                        const bool hit = find_record(P.recs, de[u].y, key[u], rv[u], &start, &count);
+                        const uint32_t r = rbase + q[u];
+                        const int dl = (int)(r / (uint32_t)T1), i0m = (int)(r % (uint32_t)T1);
+                        const int l = P.self ? n - dl : n - tau + dl;
+                        if (!hit) count = 0;
+                        else if (P.self && l == n) count = members_before(P.vals, start, count, gx);
+                        hh.gx = gx; hh.start = start; hh.count = count;
+                        hh.meta = ((uint32_t)p[u] & 0xffffu) - 1u | (uint32_t)i0m << 11 |
+                                  (uint32_t)l << 17;
+                    }
+                    app.push(count > 0, hh, P.hits, P.hit_cap, &P.counters[0]);
+                    my_cand += count;
+                }
             }
         }
     }
@@ -1050,13 +1400,6 @@ __device__ inline void vsp_lane_dispatch(bool yrows, LdsChars U, int lu, LdsLane
         PJ_LANE(GMAXW, -1);
     }
 #undef PJ_LANE
-}
-
-// a wave-uniform load through the scalar cache (read-only data)
-template <typename T>
-__device__ inline T uniform_load(const T* p)
-{
-    return *(const __attribute__((address_space(4))) T*)p;
 }
 
 // The 40-byte class of the 5-wide band fits 8 blocks per CU in LDS; it is compiled for 8 waves
@@ -2210,6 +2553,51 @@ __global__ __launch_bounds__(kBlock) void k_probe_order(int tau, int nl, int sel
         order[atomicAdd(&cnt[size_of(r)], 1u)] = (uint16_t)r;
 }
 
+// One block: the item list.  Thread t lays down the windows of its run of consecutive pairs.
+__global__ __launch_bounds__(kBlock) void k_probe_items(int tau, int nl, int self,
+                                                        uint32_t* __restrict__ items,
+                                                        uint32_t* __restrict__ chunk)
+{
+    __shared__ uint32_t s_wave[kWaves];
+    const int T1 = tau + 1, pairs = nl * T1;
+    const int per = (pairs + kBlock - 1) / kBlock;
+    const int r0 = min((int)threadIdx.x * per, pairs), r1 = min(r0 + per, pairs);
+    auto size_of = [&](int r) {
+        const int dl = r / T1, i = r % T1 + 1;
+        return (uint32_t)mm_window_size(tau, i, self ? dl : tau - dl);
+    };
+    uint32_t mine = 0;
+    for (int r = r0; r < r1; ++r) mine += size_of(r);
+    uint32_t total;
+    uint32_t at = block_excl_scan<uint32_t>(mine, s_wave, &total);
+    for (int r = r0; r < r1; ++r) {
+        if (r % kItemPairs == 0) chunk[r / kItemPairs] = at;
+        const uint32_t sz = size_of(r);
+        for (uint32_t s = 0; s < sz; ++s) items[at + s] = (uint32_t)r << 8 | s;
+        at += sz;
+    }
+    if (threadIdx.x == 0) chunk[(pairs + kItemPairs - 1) / kItemPairs] = total;
+}
+
+uint64_t probe_item_count(int tau, int nl, int self)
+{
+    // Lemma 2 for each length difference
+    uint64_t n = 0;
+    for (int dl = 0; dl < nl; ++dl) {
+        const int d = self ? dl : tau - dl;
+        n += (uint64_t)((tau * tau - d * d) / 2 + tau + 1);
+    }
+    return n;
+}
+
+hipError_t launch_probe_items(int tau, int nl, int self, uint32_t* items, uint32_t* chunk,
+                              hipStream_t s)
+{
+    if (tau < 0 || tau > kTauMax || nl < 1 || nl > 2 * kTauMax + 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_probe_items, dim3(1), dim3(kBlock), 0, s, tau, nl, self, items, chunk);
+    return hipGetLastError();
+}
+
 hipError_t launch_probe_order(int tau, int nl, int self, uint16_t* order, hipStream_t s)
 {
     if (tau < 0 || tau > kTauMax || nl < 1 || nl > 2 * kTauMax + 1 || !order)
@@ -2223,14 +2611,41 @@ hipError_t launch_probe(const ProbeParams& P, int max_blocks, hipStream_t s)
     if (P.threads == 0) return hipSuccess;
     if (!P.sym.code) return hipErrorInvalidValue;
     const uint64_t blocks = std::min<uint64_t>(blocks_for(P.threads), (uint64_t)max_blocks);
-    if (P.xmajor) {
-        if (P.q_tau || P.nx_dev || P.nx == 0) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_probe<true>, dim3((unsigned)blocks), dim3(kBlock), 0, s, P,
-                           make_div(P.tau + 1));
-    } else {
-        hipLaunchKernelGGL(k_probe<false>, dim3((unsigned)blocks), dim3(kBlock), 0, s, P,
-                           make_div(P.tau + 1));
-    }
+    hipLaunchKernelGGL(k_probe, dim3((unsigned)blocks), dim3(kBlock), 0, s, P, make_div(P.tau + 1));
+    return hipGetLastError();
+}
+
+hipError_t launch_probe_tiles(const ProbeParams& P, const ProbeTiles& T, int max_blocks,
+                              hipStream_t s)
+{
+    if (T.tiles == 0) return hipSuccess;
+    if (!P.sym.code || P.q_tau || P.nx_dev || T.groups < 1 || T.maxlen > kTileMaxLen ||
+        (uint64_t)T.tiles * T.groups > 0x7fffffffull)
+        return hipErrorInvalidValue;
+    const uint64_t units = (uint64_t)T.tiles * T.groups;
+    // a multiple of the XCDs
+    const dim3 grid((unsigned)std::min<uint64_t>(((units + kWaves - 1) / kWaves + 7) / 8 * 8,
+                                                 (uint64_t)std::max(max_blocks / 8 * 8, 8)));
+    const Div div = make_div(P.tau + 1);
+    if (T.maxlen <= 32) hipLaunchKernelGGL(k_probe_tiles<2>, grid, dim3(kBlock), 0, s, P, div, T);
+    else if (T.maxlen <= 64) hipLaunchKernelGGL(k_probe_tiles<4>, grid, dim3(kBlock), 0, s, P, div, T);
+    else hipLaunchKernelGGL(k_probe_tiles<8>, grid, dim3(kBlock), 0, s, P, div, T);
+    return hipGetLastError();
+}
+
+hipError_t launch_probe_long(const ProbeParams& P, const ProbeItems& I, uint32_t g_first,
+                             uint32_t g_end, int maxlen, int max_blocks, hipStream_t s)
+{
+    if (g_first >= g_end) return hipSuccess;
+    if (!P.sym.code || P.q_tau || P.nx_dev || P.selection != 0 || !I.items ||
+        I.chunks != (P.nl * (P.tau + 1) + kItemPairs - 1) / kItemPairs)
+        return hipErrorInvalidValue;
+    const dim3 grid(std::min<unsigned>(g_end - g_first, (unsigned)max_blocks));
+    const Div div = make_div(P.tau + 1);
+    if (maxlen < 1024)
+        hipLaunchKernelGGL(k_probe_long<1024>, grid, dim3(kBlock), 0, s, P, div, I, g_first, g_end);
+    else
+        hipLaunchKernelGGL(k_probe_long<2048>, grid, dim3(kBlock), 0, s, P, div, I, g_first, g_end);
     return hipGetLastError();
 }
 
@@ -2721,7 +3136,7 @@ hipError_t launch_graph_batch(const GraphBatch& G, hipStream_t s)
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, s, G.probe.counters, 8, 0ull);
     hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, s, G.bcounts, 4, 0ull);
-    hipLaunchKernelGGL(k_probe<false>, dim3(G.probe_grid), dim3(kBlock), 0, s, G.probe,
+    hipLaunchKernelGGL(k_probe, dim3(G.probe_grid), dim3(kBlock), 0, s, G.probe,
                        make_div(G.probe.tau + 1));
     hipLaunchKernelGGL(k_batch_prefix, dim3(1), dim3(kBlock), 0, s, G.probe.hits,
                        G.probe.counters, G.probe.hit_cap,

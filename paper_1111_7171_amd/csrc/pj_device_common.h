@@ -186,7 +186,8 @@ __device__ inline void select_window(int method, int n, int l, int tau, int i, S
 // Polynomial segment hash h = sum (c_k + 1) * B^(L-1-k) mod 2^64 (Horner form), rolled across
 // consecutive start positions.  Equal segments always hash equal; unequal ones that collide are
 // rejected by the byte comparison done before verification.
-constexpr uint64_t kHashBase = 0x9E3779B97F4A7C15ull;
+// The base is odd and below 2^32, so a Horner step is two 32-bit multiplications.
+constexpr uint64_t kHashBase = 2654435761ull;
 
 __device__ inline uint64_t seg_hash(const uint8_t* w, int len)
 {
@@ -258,13 +259,15 @@ __device__ inline uint64_t roll_code(uint64_t h, int len, uint8_t out, uint8_t i
 }
 
 // Index key: group(l, i) above a 40-bit code that is spread over its range whatever the segments
-// are: a hashed segment's finalised hash, or a packed code times an odd constant modulo 2^40 (one
-// to one, so exact keys stay exact).
-constexpr uint64_t kCodeMul = 0x9E3779B97F4A7C15ull << (64 - kHashBits);
+// are: a packed code times an odd constant modulo 2^40 (one to one, so exact keys stay exact), or
+// the leading bits of a hash folded and multiplied (hashes of segments that differ in their last
+// byte differ by less than 256, so the multiplication is what parts them).
+constexpr uint64_t kSpread = 0x9E3779B97F4A7C15ull;
 
 __device__ inline uint64_t spread_code(int len, uint64_t code, int exact_len)
 {
-    return (len <= exact_len ? code * kCodeMul : mix64(code)) >> (64 - kHashBits);
+    const uint64_t x = len <= exact_len ? code << (64 - kHashBits) : code ^ (code >> 32);
+    return x * kSpread >> (64 - kHashBits);
 }
 
 __device__ inline uint64_t make_key(int l, int i, int tau, int len, uint64_t code, int exact_len)

@@ -688,25 +688,6 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
         pp.g_begin = (uint32_t)probe_first;
         pp.nl = self ? T1 : 2 * tau + 1;
         pp.threads = (uint64_t)nprobe * (uint64_t)pp.nl * (uint64_t)T1;
-        // the thread mapping the tuner chose (pair-major keeps a wave's lanes on windows of
-        // one size when probe strings have few (length, slot) pairs); the plain path keeps the
-        // string-major one
-        if (!spec.q_tau && J.tp.probe_map == 1 && J.mode != PJ_MODE_PLAIN) {
-            pp.xmajor = 1;
-            pp.nx = (uint32_t)nprobe;
-            pp.threads = ((uint64_t)nprobe + 63) / 64 * 64 * (uint64_t)pp.nl * (uint64_t)T1;
-        }
-        // tests force either thread mapping (it changes no result)
-        if (const char* e = getenv("PJ_PROBE_XMAJOR")) {
-            if (atoi(e) == 0 || spec.q_tau) {
-                pp.xmajor = 0;
-                pp.threads = (uint64_t)nprobe * (uint64_t)pp.nl * (uint64_t)T1;
-            } else {
-                pp.xmajor = 1;
-                pp.nx = (uint32_t)nprobe;
-                pp.threads = ((uint64_t)nprobe + 63) / 64 * 64 * (uint64_t)pp.nl * (uint64_t)T1;
-            }
-        }
         pp.self = self ? 1 : 0;
         pp.q_tau = spec.q_tau;
         pp.refs = spec.refs;
@@ -721,7 +702,15 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
         pp.ymin = Y.lmin; pp.ymax = Y.lmax;
         pp.sym = spec.sym;
         pp.selection = spec.selection;
-        if (!spec.q_tau && spec.selection == PJ_SELECT_MULTIMATCH && J.mode != PJ_MODE_PLAIN) {
+        // a uniform threshold: strings of up to kTileMaxLen bytes pair-major, a wave per 64 of one
+        // length (unless a tuned setting or a test asks for the string-major kernel), longer ones a
+        // block each.  Query batches and the plain path take the string-major kernel.
+        const int max_blocks = device_cus() * J.tp.probe_blocks_per_cu;
+        bool split = !spec.q_tau && J.mode != PJ_MODE_PLAIN &&
+                     !(J.tp.tuned && J.tp.probe_map == 0);
+        // tests force either kernel (it changes no result)
+        if (const char* e = getenv("PJ_PROBE_XMAJOR")) split = atoi(e) != 0 && !spec.q_tau;
+        if (!split && !spec.q_tau && spec.selection == PJ_SELECT_MULTIMATCH && J.mode != PJ_MODE_PLAIN) {
             // the (length, slot) pairs grouped by window size, so a wave's lanes walk windows of
             // one size (the plain path keeps the natural order: it is the unscheduled baseline)
             uint16_t* order = (uint16_t*)W.get(
@@ -733,7 +722,52 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
         pp.counters = J.counters;
         pp.shards = kStatShards;
         int k0 = tm.mark();
-        hip_check(launch_probe(pp, device_cus() * J.tp.probe_blocks_per_cu, st), "probe");
+        if (split) {
+            // one launch per class of slot sizes
+            const uint64_t pairs = (uint64_t)pp.nl * (uint64_t)T1;
+            const int cls_hi[3] = {32, 64, kTileMaxLen};
+            for (int c = 0, l0 = 0; c < 3; l0 = cls_hi[c] + 1, ++c) {
+                ProbeTiles T{};
+                for (int l = 0; l <= kTileMaxLen; ++l) {
+                    T.first[l] = T.tiles;
+                    if (l < l0 || l > cls_hi[c] || P.h_lenstart[l] < probe_first) continue;
+                    const int64_t cnt = P.h_lenstart[l + 1] - P.h_lenstart[l];
+                    if (cnt == 0) continue;
+                    T.tiles += (uint32_t)((cnt + 63) / 64);
+                    T.maxlen = l;
+                }
+                // enough (tile, pairs) units for the resident waves and some to balance them
+                T.groups = (uint32_t)std::max<uint64_t>(
+                    1, std::min<uint64_t>(pairs, 64ull * (uint64_t)device_cus() /
+                                                     std::max<uint32_t>(T.tiles, 1)));
+                hip_check(launch_probe_tiles(pp, T, max_blocks, st), "probe_tiles");
+            }
+            const int cut = kTileMaxLen + 1;                 // first length of the long ones
+            const int64_t first_long = std::max<int64_t>(P.h_lenstart[cut], probe_first);
+            if (first_long < P.n && spec.selection == PJ_SELECT_MULTIMATCH) {
+                ProbeItems I{};
+                I.chunks = (int)((pairs + kItemPairs - 1) / kItemPairs);
+                uint32_t* items = (uint32_t*)W.get(
+                    "probe.items", sizeof(uint32_t) * (size_t)probe_item_count(tau, pp.nl, pp.self));
+                uint32_t* chunk = (uint32_t*)W.get("probe.chunk",
+                                                   sizeof(uint32_t) * (kItemChunks + 1));
+                hip_check(launch_probe_items(tau, pp.nl, pp.self, items, chunk, st), "probe_items");
+                I.items = items;
+                I.chunk = chunk;
+                const int64_t mid = std::max<int64_t>(P.h_lenstart[1024], first_long);
+                hip_check(launch_probe_long(pp, I, (uint32_t)first_long, (uint32_t)mid, 1023,
+                                            max_blocks, st), "probe_long");
+                hip_check(launch_probe_long(pp, I, (uint32_t)mid, (uint32_t)P.n, P.lmax, max_blocks,
+                                            st), "probe_long");
+            } else if (first_long < P.n) {
+                ProbeParams pl = pp;
+                pl.g_begin = (uint32_t)first_long;
+                pl.threads = (uint64_t)(P.n - first_long) * pairs;
+                hip_check(launch_probe(pl, max_blocks, st), "probe");
+            }
+        } else {
+            hip_check(launch_probe(pp, max_blocks, st), "probe");
+        }
         int k1 = tm.mark();
         J.kernel_marks.push_back({k0, k1, 0});
     }

@@ -144,10 +144,27 @@ struct ProbeParams {
     // permutation of 0 .. nl * (tau+1) - 1 grouped by window size, so that a wave's lanes walk
     // windows of one size (launch_probe_order); nullptr: natural order
     const uint16_t* order;
-    // 1: threads pair-major over blocks of 64 probe strings (threads = nx rounded up to 64,
-    // times nl * (tau+1)); not with q_tau or nx_dev
-    int xmajor;
-    uint32_t nx;                // probe strings (xmajor)
+};
+
+// Tiles of the pair-major probe: up to 64 consecutive probe strings of one length of at most
+// kTileMaxLen bytes; first[l] = the first tile of length l (of the lengths of one launch).
+constexpr int kTileMaxLen = 127;
+struct ProbeTiles {
+    uint32_t first[kTileMaxLen + 1];
+    uint32_t tiles;
+    uint32_t groups;            // a tile's (length, slot) pairs are split over this many waves
+    int maxlen;                 // longest probe string of a tile
+};
+
+// Multi-match window positions of a probe string as a list, for the probe of long strings: item
+// r << 8 | s is position s of the (unclipped) window of pair r = dl * (tau+1) + (i-1), in the order
+// of r.  Pairs are taken kItemPairs at a time; their items are items[chunk[c] .. chunk[c + 1]).
+constexpr int kItemPairs = 512;
+constexpr int kItemChunks = ((2 * kTauMax + 1) * (kTauMax + 1) + kItemPairs - 1) / kItemPairs;
+struct ProbeItems {
+    const uint32_t* items;
+    const uint32_t* chunk;      // [chunks + 1]
+    int chunks;
 };
 
 struct VerifyParams {
@@ -210,6 +227,17 @@ hipError_t launch_list_dir(const uint64_t* keys, const uint32_t* runstart, uint3
                            size_t scan_bytes, uint4* recs, uint32_t* gdir, uint2* dir,
                            hipStream_t s);
 hipError_t launch_probe(const ProbeParams& P, int max_blocks, hipStream_t s);
+// pair-major probe of the strings of T's tiles, and multi-match probe of the strings
+// g_first .. g_end - 1 (of at most maxlen bytes), a block each; uniform tau
+hipError_t launch_probe_tiles(const ProbeParams& P, const ProbeTiles& T, int max_blocks,
+                              hipStream_t s);
+hipError_t launch_probe_long(const ProbeParams& P, const ProbeItems& I, uint32_t g_first,
+                             uint32_t g_end, int maxlen, int max_blocks, hipStream_t s);
+// the item list of a (tau, nl): items has room for probe_item_count entries, chunk for
+// kItemChunks + 1
+uint64_t probe_item_count(int tau, int nl, int self);
+hipError_t launch_probe_items(int tau, int nl, int self, uint32_t* items, uint32_t* chunk,
+                              hipStream_t s);
 // order[0 .. nl * (tau+1)): the (length, slot) pairs r = dl * (tau+1) + (i-1) of a probe string
 // by decreasing multi-match window size (any order within a size)
 hipError_t launch_probe_order(int tau, int nl, int self, uint16_t* order, hipStream_t s);
