@@ -1012,8 +1012,7 @@ __global__ __launch_bounds__(kBlock) void k_verify(VerifyParams V, Div div)
 // from the hits' end offsets with one OR-reduced boundary mask per 64 candidates.
 // ------------------------------------------------------------------------------------------
 
-constexpr int kWaveRounds = kBatchedRoundsMax;   // captured batches use the full chunk
-constexpr uint64_t kWaveChunk = 64ull * kWaveRounds;
+constexpr int kWaveRounds = kBatchedRoundsMax;
 
 // Bucket of a hit: lists with at least `big` candidates after all smaller ones, each part in
 // slot order.
@@ -1175,7 +1174,7 @@ __attribute__((amdgpu_waves_per_eu(STG == 2 ? 5 : (STG || GMAXW <= 9) ? 4 : 1)))
     const uint64_t nhits = V.dev_counts ? V.dev_counts[0] : V.nhits;
     const uint64_t ncand = V.dev_counts ? V.dev_counts[1] : V.ncand;
     const uint64_t nch = V.dev_counts ? V.dev_counts[2] : nchunks;
-    const uint64_t chunk = 64ull * (uint64_t)V.wave_rounds;
+    const uint64_t chunk = 64ull * (V.dev_counts ? V.dev_counts[4] : (uint64_t)V.wave_rounds);
     for (uint64_t ch = wave; ch < nch; ch += nwaves) {
         const uint64_t c0 = ch * chunk;
         const uint64_t cend = (c0 + chunk < ncand) ? c0 + chunk : ncand;
@@ -1700,6 +1699,7 @@ void k_verify_segs(VerifyParams V, Div div,
             ++h;
             sidx = 0;
         }
+        if (!ticket) break;                        // a chunk for every wave
         unsigned long long t = 0;
         if (lane == 0) t = atomicAdd(ticket, 1ull);
         ch = nwaves + ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)t) |
@@ -3005,89 +3005,94 @@ hipError_t launch_short_path(const DevSet& P, const DevSet& Y, int tau, int self
 // of these launches serves every batch of a serving slot.
 // ------------------------------------------------------------------------------------------
 
-__global__ void k_fill_u64(unsigned long long* __restrict__ p, int n, unsigned long long v)
+// One block: exclusive prefix of the hits' candidate counts, the batch's sizes, and first[ch] (the
+// hit holding candidate ch * chunk: a hit writes the chunks that begin inside it).  A chunk is a
+// wave's 64 candidates until every wave of a full chip has one, then more rounds of 64.  An
+// overflow (more hits than the buffer holds, or more candidates than the batch may have) sets a
+// flag and leaves nothing to verify; the host then runs the batch another way.
+__global__ __launch_bounds__(1024) void k_batch_prefix(const Hit* __restrict__ hits,
+                                                       const unsigned long long* __restrict__ counters,
+                                                       uint64_t hit_cap,
+                                                       unsigned long long* __restrict__ prefix,
+                                                       unsigned long long* __restrict__ bc,
+                                                       uint32_t* __restrict__ first,
+                                                       uint64_t cand_cap)
 {
-    for (int k = threadIdx.x; k < n; k += blockDim.x) p[k] = v;
-}
-
-// One block: exclusive prefix of the hits' candidate counts, then the batch's sizes.  An
-// overflow (more hits than the buffer holds, or more wave chunks than the chunk table holds)
-// sets a flag and leaves nothing to verify; the host then runs the batch without the graph.
-__global__ __launch_bounds__(kBlock) void k_batch_prefix(const Hit* __restrict__ hits,
-                                                         const unsigned long long* __restrict__ counters,
-                                                         uint64_t hit_cap,
-                                                         unsigned long long* __restrict__ prefix,
-                                                         unsigned long long* __restrict__ bc,
-                                                         uint64_t chunk_cap)
-{
-    __shared__ unsigned long long s_w[kWaves];
-    uint64_t nh = counters[0];
+    constexpr int PER = 4;
+    __shared__ unsigned long long s_w[16];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    uint64_t nh = counters[0], ncand = counters[1];
     unsigned long long flags = 0;
-    if (nh > hit_cap) {
-        flags |= 1;
-        nh = 0;
-    }
+    if (nh > hit_cap) flags |= 1;
+    if (ncand > cand_cap) flags |= 2;
+    if (flags) nh = ncand = 0;
+    const uint64_t per_wave = (ncand + 64ull * kBatchWaves - 1) / (64ull * kBatchWaves);
+    const uint64_t rounds = per_wave < 1 ? 1 : per_wave > kWaveRounds ? kWaveRounds : per_wave;
+    const uint64_t chunk = 64ull * rounds;
     unsigned long long carry = 0;
-    for (uint64_t b = 0; b < nh; b += kBlock) {
-        const uint64_t k = b + threadIdx.x;
-        const unsigned long long v = k < nh ? (unsigned long long)hits[k].count : 0ull;
-        unsigned long long tot;
-        const unsigned long long ex = block_excl_scan(v, s_w, &tot);
-        if (k < nh) prefix[k] = carry + ex;
+    for (uint64_t b = 0; b < nh; b += 1024 * PER) {
+        const uint64_t k0 = b + (uint64_t)threadIdx.x * PER;
+        unsigned long long v[PER], sum = 0;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            v[q] = k0 + q < nh ? (unsigned long long)hits[k0 + q].count : 0ull;
+            sum += v[q];
+        }
+        const unsigned long long incl = wave_incl_scan(sum);
+        if (lane == 63) s_w[w] = incl;
+        __syncthreads();
+        unsigned long long at = carry + incl - sum, tot = 0;
+        for (int q = 0; q < 16; ++q) {
+            if (q < w) at += s_w[q];
+            tot += s_w[q];
+        }
         carry += tot;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            if (k0 + q < nh) {
+                prefix[k0 + q] = at;
+                for (uint64_t ch = (at + chunk - 1) / chunk; ch * chunk < at + v[q]; ++ch)
+                    first[ch] = (uint32_t)(k0 + q);
+                at += v[q];
+            }
+        }
     }
     if (threadIdx.x == 0) {
         prefix[nh] = carry;
-        uint64_t nch = (carry + kWaveChunk - 1) / kWaveChunk;
-        if (nch > chunk_cap) {
-            flags |= 2;
-            nch = 0;
-        }
         bc[0] = nh;
-        bc[1] = (flags & 2) ? 0ull : carry;
-        bc[2] = nch;
+        bc[1] = carry;
+        bc[2] = (carry + chunk - 1) / chunk;
         bc[3] = flags;
-    }
-}
-
-// first[ch] for a captured batch (grid-stride; sizes from bc)
-__global__ __launch_bounds__(kBlock) void k_chunk_starts_dev(const unsigned long long* __restrict__ prefix,
-                                                             const unsigned long long* __restrict__ bc,
-                                                             uint32_t* __restrict__ first)
-{
-    const uint64_t nh = bc[0], nch = bc[2];
-    for (uint64_t ch = (uint64_t)blockIdx.x * kBlock + threadIdx.x; ch < nch;
-         ch += (uint64_t)gridDim.x * kBlock) {
-        const unsigned long long c0 = ch * kWaveChunk;
-        uint64_t a = 0, b = nh - 1;
-        while (a < b) {
-            const uint64_t m = (a + b + 1) >> 1;
-            if (prefix[m] <= c0) a = m; else b = m - 1;
-        }
-        first[ch] = (uint32_t)a;
+        bc[4] = rounds;
     }
 }
 
 // One block: the batch's accepted (gx, gy) become (query id << 32 | indexed id) keys, sorted in
-// LDS (bitonic), deduplicated and compacted in order.  More than kGraphSortCap accepted pairs,
-// or more than the accepted buffer held, sets a flag and outputs nothing.
+// LDS (bitonic), deduplicated and compacted in order, after the batch's counters: the result block.
+// More than kGraphSortCap accepted pairs, or more than the accepted buffer held, sets a flag and
+// outputs nothing.
 __global__ __launch_bounds__(1024) void k_batch_dedupe(const uint64_t* __restrict__ acc,
                                                        const unsigned long long* __restrict__ counters,
                                                        uint64_t acc_cap,
                                                        const int32_t* __restrict__ xperm,
                                                        const int32_t* __restrict__ yperm,
-                                                       unsigned long long* __restrict__ bc,
-                                                       uint64_t* __restrict__ out,
-                                                       uint32_t* __restrict__ out_n)
+                                                       const unsigned long long* __restrict__ bc,
+                                                       unsigned long long* __restrict__ result)
 {
     __shared__ uint64_t s_k[kGraphSortCap];
     __shared__ uint32_t s_w[16];
+    uint64_t* out = (uint64_t*)(result + kBatchResultHead);
     const uint64_t m = counters[3];
-    if (m > acc_cap || m > (uint64_t)kGraphSortCap) {
-        if (threadIdx.x == 0) {
-            bc[3] |= (m > acc_cap ? 4ull : 0ull) | 8ull;
-            *out_n = 0;
-        }
+    const bool over = m > acc_cap || m > (uint64_t)kGraphSortCap;
+    if (threadIdx.x < 8) {
+        result[threadIdx.x] = counters[threadIdx.x];
+    } else if (threadIdx.x < 12) {
+        const int k = (int)threadIdx.x - 8;
+        result[threadIdx.x] = bc[k] | (k == 3 && over ? (m > acc_cap ? 4ull : 0ull) | 8ull : 0ull);
+    }
+    if (over) {
+        if (threadIdx.x == 0) result[12] = 0;
         return;
     }
     uint32_t N = 64;
@@ -3113,7 +3118,7 @@ __global__ __launch_bounds__(1024) void k_batch_dedupe(const uint64_t* __restric
         if (head) out[at] = s_k[k];
         carry += tot;
     }
-    if (threadIdx.x == 0) *out_n = carry;
+    if (threadIdx.x == 0) result[12] = carry;
 }
 
 template <int W>
@@ -3130,27 +3135,27 @@ static void graph_verify_short(const GraphBatch& G, hipStream_t s)
     }
 }
 
-hipError_t launch_graph_batch(const GraphBatch& G, hipStream_t s)
+hipError_t launch_graph_probe(const GraphBatch& G, hipStream_t s)
 {
     if (!G.probe.nx_dev || !G.verify.dev_counts || G.probe_grid < 1 || G.verify_grid < 1)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, s, G.probe.counters, 8, 0ull);
-    hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, s, G.bcounts, 4, 0ull);
     hipLaunchKernelGGL(k_probe, dim3(G.probe_grid), dim3(kBlock), 0, s, G.probe,
                        make_div(G.probe.tau + 1));
-    hipLaunchKernelGGL(k_batch_prefix, dim3(1), dim3(kBlock), 0, s, G.probe.hits,
-                       G.probe.counters, G.probe.hit_cap,
-                       const_cast<unsigned long long*>(G.verify.prefix), G.bcounts, G.chunk_cap);
-    hipLaunchKernelGGL(k_chunk_starts_dev, dim3(8), dim3(kBlock), 0, s, G.verify.prefix,
-                       G.bcounts, G.first);
+    return hipGetLastError();
+}
+
+hipError_t launch_graph_verify(const GraphBatch& G, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_batch_prefix, dim3(1), dim3(1024), 0, s, G.probe.hits, G.probe.counters,
+                       G.probe.hit_cap, const_cast<unsigned long long*>(G.verify.prefix), G.bcounts,
+                       G.first, G.cand_cap);
     const int w = G.verify.tau + 1;
     if (w <= 9) graph_verify_short<9>(G, s);
     else if (w <= 17) graph_verify_short<17>(G, s);
     else if (w <= 33) graph_verify_short<33>(G, s);
     else graph_verify_short<64>(G, s);
     hipLaunchKernelGGL(k_batch_dedupe, dim3(1), dim3(1024), 0, s, G.verify.out,
-                       G.verify.counters, G.verify.out_cap, G.xperm, G.yperm, G.bcounts, G.out,
-                       G.out_n);
+                       G.verify.counters, G.verify.out_cap, G.xperm, G.yperm, G.bcounts, G.result);
     return hipGetLastError();
 }
 

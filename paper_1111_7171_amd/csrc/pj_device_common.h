@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "pj_internal.h"
 
 namespace pj {
@@ -389,15 +391,65 @@ __device__ inline int vsp_global(const uint8_t* r, int lr, const uint8_t* s, int
 // Cells of rows 1..s of the band (closed form, defined below).
 __device__ inline int band_cells(int s, int nc, int a, int b);
 
+// A string read in order, a byte per row: from LDS (or a short range) directly, from global memory
+// eight bytes at a time, the next eight loaded while the current ones are used.  Every lane takes
+// the same rows, so the place in the eight bytes is uniform.  Bytes from index `end` on are not
+// needed: eight bytes are loaded only if the first of them is (a string's slot is followed by at
+// least seven readable bytes).
+template <typename P>
+struct ByteStream {
+    P p;
+    int end, ahead;                            // the next byte, read a row early
+    __device__ inline int at(int r) const { return r < end ? (int)p[r] : 256; }
+    __device__ inline ByteStream(P base, int first, int n)
+        : p(base + first), end(n - first), ahead(at(0))
+    {
+    }
+    __device__ inline int next(int r)
+    {
+        const int c = ahead;
+        ahead = at(r + 1);
+        return c;
+    }
+};
+
+template <>
+struct ByteStream<const uint8_t*> {
+    const uint8_t* p;
+    int end;
+    uint64_t cur, ahead;
+    __device__ inline uint64_t load(int r) const
+    {
+        uint64_t v = 0;
+        if (r < end) __builtin_memcpy(&v, p + r, 8);
+        return v;
+    }
+    __device__ inline ByteStream(const uint8_t* base, int first, int n)
+        : p(base + first), end(n - first)
+    {
+        cur = load(0);
+        ahead = load(8);
+    }
+    __device__ inline int next(int r)          // r = 0, 1, 2, ...
+    {
+        const int c = (int)(cur >> (8 * (r & 7))) & 255;
+        if ((r & 7) == 7) {
+            cur = ahead;
+            ahead = load(r + 9);
+        }
+        return c;
+    }
+};
+
 // VerifyStringPair for the batched path (one candidate per lane, each lane with its own
 // strings and band): the same orientation, band, early stop, result and cell count as
 // vsp_global, computed as vsp_lane does, on expected distances D = M + |kfin - k| with the
 // neighbour adjustments cu, cl (0 or 2) and no masks (the argument given for vsp_seg covers the
-// BIG borders, the unmasked band indices past a + b and the characters outside 1..nc, which
-// read as 256 here).  The band's column characters sit in a register window that shifts by one
-// per row; the character entering it and the next row character are loaded a row ahead.  The
-// cells of the rows evaluated follow in closed form.  P is a byte pointer into global memory
-// or LDS.
+// BIG borders, the unmasked band indices past a + b and the characters outside 1..nc, which may
+// be any here).  The band's column characters sit in a register window that shifts by one per
+// row.  The cells of the rows evaluated follow in closed form.  P is a byte pointer into global
+// memory or LDS.  A byte load from global memory per row and string had bounded the rows of long
+// parts (0.5 us a row): 64 queries of a lookup service 70 -> 31 us in this kernel.
 template <int MAXW, typename P>
 __device__ inline int vsp_fast(P r, int lr, P s, int ls, int t, int* cells)
 {
@@ -413,26 +465,40 @@ __device__ inline int vsp_fast(P r, int lr, P s, int ls, int t, int* cells)
     const int b = (t + delta) >> 1;              // kfin: band index of cell (nr, nc)
     constexpr int BIG = 1 << 20;
     int D[MAXW], w[MAXW], cu[MAXW], cl[MAXW];
+    ByteStream<P> rowc(A, 0, nr);
+    ByteStream<P> colc(B, MAXW - a, nc);         // characters entering the window after each row
+    if constexpr (std::is_same<P, const uint8_t*>::value && MAXW <= 9) {
+        // window of row 1: B index k - a for band index k, from the first bytes shifted by a
+        uint64_t lo = 0, hi = 0;
+        if (nc > 0) __builtin_memcpy(&lo, B, 8);
+        if (MAXW > 8 && nc > 8) hi = (uint64_t)B[8];
+        const int sh = 8 * a;                    // a <= 4 (t <= 8)
+        if (MAXW > 8 && sh) hi = lo >> (64 - sh);
+        lo <<= sh;
+#pragma unroll
+        for (int k = 0; k < MAXW; ++k)
+            w[k] = k < 8 ? (int)(lo >> (8 * k)) & 255 : (int)hi & 255;
+    } else {
+#pragma unroll
+        for (int k = 0; k < MAXW; ++k) {
+            const int j = k - a;
+            w[k] = ((unsigned)j < (unsigned)nc) ? (int)B[j] : 256;
+        }
+    }
 #pragma unroll
     for (int k = 0; k < MAXW; ++k) {
         const int j = k - a;                     // column of band index k in row 0
         const int ek = b > k ? b - k : k - b;
         D[k] = (j >= 0 && j <= min(nc, b)) ? j + ek : BIG;
-        w[k] = ((unsigned)j < (unsigned)nc) ? (int)B[j] : 256;   // B index of row 1's column
         cu[k] = k < b ? 2 : 0;
         cl[k] = k > b ? 2 : 0;
     }
-    int idx_in = MAXW - a;                       // B index entering the window after row 1
-    int cin = ((unsigned)idx_in < (unsigned)nc) ? (int)B[idx_in] : 256;
-    int ai = nr > 0 ? (int)A[0] : 256;
-    int ai_next = nr > 1 ? (int)A[1] : 256;
     int rows = nr;
     bool failed = false;
     for (int i = 1; i <= nr; ++i) {
-        // loads for the next row first, so their latency overlaps this row's arithmetic
-        const int idx2 = idx_in + 1;
-        const int cin_next = ((unsigned)idx2 < (unsigned)nc) ? (int)B[idx2] : 256;
-        const int ai_next2 = (i + 1 < nr) ? (int)A[i + 1] : 256;
+        const int row = __builtin_amdgcn_readfirstlane(i - 1);
+        const int ai = rowc.next(row);
+        const int cin = colc.next(row);
         int left = BIG;
 #pragma unroll
         for (int k = 0; k < MAXW; ++k) {
@@ -456,10 +522,6 @@ __device__ inline int vsp_fast(P r, int lr, P s, int ls, int t, int* cells)
 #pragma unroll
         for (int k = 0; k + 1 < MAXW; ++k) w[k] = w[k + 1];
         w[MAXW - 1] = cin;
-        cin = cin_next;
-        idx_in = idx2;
-        ai = ai_next;
-        ai_next = ai_next2;
     }
     *cells = band_cells(rows, nc, a, b);
     if (failed) return t + 1;

@@ -22,15 +22,20 @@ namespace pj {
 
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-BatchLayout batch_layout(int max_queries, uint64_t hcap, uint64_t chunk_cap, uint64_t acc_cap)
+// words of the tables before the queries' own: counters, batch counts, the number of queries
+constexpr size_t kHeadBytes = 128 + 8;
+
+BatchLayout batch_layout(int max_queries, uint64_t hcap, uint64_t cand_cap, uint64_t acc_cap)
 {
     BatchLayout L;
     L.qcap = std::max(1, max_queries);
     L.bcap = L.qcap * 512;
     L.hcap = hcap;
-    L.chunk_cap = chunk_cap;
+    L.cand_cap = cand_cap;
     L.acc_cap = acc_cap;
-    size_t o = 8;
+    // wave chunks: one candidate round each up to kBatchWaves, full ones beyond
+    L.first_words = (size_t)std::max<uint64_t>(kBatchWaves, cand_cap / (64 * kBatchedRoundsMax)) + 1;
+    size_t o = kHeadBytes;
     L.off_lenstart = o; o += sizeof(int32_t) * (kLenTab + 1);
     o = align256(o);
     L.off_gbase = o; o += sizeof(int64_t) * kLenTab;
@@ -39,7 +44,7 @@ BatchLayout batch_layout(int max_queries, uint64_t hcap, uint64_t chunk_cap, uin
     L.off_slen = o; o += sizeof(uint16_t) * (size_t)L.qcap;
     L.tables_bytes = align256(o);
     L.arena_bytes = align256((size_t)L.bcap + 64);
-    L.result_bytes = sizeof(unsigned long long) * 12 + 8 + sizeof(uint64_t) * kGraphSortCap;
+    L.result_bytes = sizeof(uint64_t) * (kBatchResultHead + kGraphSortCap);
     return L;
 }
 
@@ -47,7 +52,7 @@ size_t batch_device_bytes(const BatchLayout& L)
 {
     return L.tables_bytes + L.arena_bytes + align256(sizeof(Hit) * L.hcap) +
            align256(sizeof(unsigned long long) * (L.hcap + 1)) +
-           align256(sizeof(uint32_t) * L.chunk_cap) + align256(sizeof(uint64_t) * L.acc_cap) +
+           align256(sizeof(uint32_t) * L.first_words) + align256(sizeof(uint64_t) * L.acc_cap) +
            align256(L.result_bytes);
 }
 
@@ -59,18 +64,16 @@ BatchBuffers carve_batch_buffers(const BatchLayout& L, uint8_t* base)
     B.arena = base + o; o += L.arena_bytes;
     B.hits = (Hit*)(base + o); o += align256(sizeof(Hit) * L.hcap);
     B.prefix = (unsigned long long*)(base + o); o += align256(sizeof(unsigned long long) * (L.hcap + 1));
-    B.first = (uint32_t*)(base + o); o += align256(sizeof(uint32_t) * L.chunk_cap);
+    B.first = (uint32_t*)(base + o); o += align256(sizeof(uint32_t) * L.first_words);
     B.acc = (uint64_t*)(base + o); o += align256(sizeof(uint64_t) * L.acc_cap);
     B.result = base + o;
     return B;
 }
 
-void setup_graph_batch(const pj_index* idx, const BatchLayout& L, const BatchBuffers& B,
-                       const TuneParams& tp, GraphBatch& G)
+void setup_graph_batch(const pj_index* idx, const BatchLayout& L, const BatchBuffers& B, int tau_max,
+                       int queries, const TuneParams& tp, GraphBatch& G)
 {
-    int tau_min = 0, tau_max = 0;
-    index_taus(idx, &tau_min, &tau_max);
-    auto* counters = (unsigned long long*)B.result;
+    auto* counters = (unsigned long long*)B.tables;
     const DevSet& Y = index_set(idx);
     G = GraphBatch{};
     ProbeParams& pp = G.probe;
@@ -90,12 +93,12 @@ void setup_graph_batch(const pj_index* idx, const BatchLayout& L, const BatchBuf
     pp.hits = B.hits;
     pp.hit_cap = L.hcap;
     pp.counters = counters;
-    pp.nx_dev = (const uint32_t*)B.tables;
+    pp.nx_dev = (const uint32_t*)(B.tables + 128);
     pp.sym = index_sym(idx);
     pp.selection = PJ_SELECT_MULTIMATCH;
     // grids sized for the batch capacity (a serving batch is small; idle blocks of a chip-wide
     // grid would still cost every batch their launch)
-    const uint64_t probe_threads = (uint64_t)L.qcap * (uint64_t)pp.nl * (uint64_t)(tau_max + 1);
+    const uint64_t probe_threads = (uint64_t)queries * (uint64_t)pp.nl * (uint64_t)(tau_max + 1);
     G.probe_grid = (int)std::max<uint64_t>(1, std::min<uint64_t>(
         (uint64_t)device_cus() * tp.probe_blocks_per_cu, (probe_threads + 255) / 256));
     if (!index_has_entries(idx)) pp.ymax = -1;        // nothing indexed: the probe finds no list
@@ -103,7 +106,7 @@ void setup_graph_batch(const pj_index* idx, const BatchLayout& L, const BatchBuf
     vp.x_arena = pp.x_arena; vp.x_slen = pp.x_slen; vp.x_lenstart = pp.x_lenstart;
     vp.x_gbase = pp.x_gbase;
     vp.y_arena = Y.sarena; vp.y_lenstart = Y.lenstart; vp.y_gbase = Y.gbase;
-    vp.wave_rounds = kBatchedRoundsMax;               // fixed chunk: the sizes are on device
+    vp.wave_rounds = kBatchedRoundsMax;               // unused: the sizes are on device
     vp.y_inl = nullptr;                               // serving indices keep no inline copies
     vp.y_inl_base = nullptr;
     vp.hits = B.hits;
@@ -118,9 +121,10 @@ void setup_graph_batch(const pj_index* idx, const BatchLayout& L, const BatchBuf
     vp.counters = counters;
     G.bcounts = counters + 8;
     vp.dev_counts = G.bcounts;
-    G.verify_grid = std::max(1, std::min(device_cus() * tp.verify_waves_per_cu / 4, 256));
+    G.verify_grid = std::max(1, std::min(device_cus() * tp.verify_waves_per_cu / 4,
+                                         std::min(std::max(32, 16 * queries), 1024)));
     G.first = B.first;
-    G.chunk_cap = L.chunk_cap;
+    G.cand_cap = L.cand_cap;
     // indexed strings shorter than tau_max + 1 go through the side path
     if (Y.n > 0 && Y.lmin <= tau_max) {
         const int top = std::min(tau_max, Y.lmax);
@@ -130,15 +134,14 @@ void setup_graph_batch(const pj_index* idx, const BatchLayout& L, const BatchBuf
     G.y_arena = Y.sarena; G.y_slen = Y.slen; G.y_lenstart = Y.lenstart; G.y_gbase = Y.gbase;
     G.xperm = (const int32_t*)(B.tables + L.off_perm);
     G.yperm = Y.perm;
-    G.out_n = (uint32_t*)(counters + 12);
-    G.out = (uint64_t*)(counters + 13);
+    G.result = (unsigned long long*)B.result;
 }
 
 PackStatus pack_query_batch(const pj_index* idx, const BatchLayout& L, const pj_strings* Q,
-                            const int32_t* taus, uint8_t* h_tables, uint8_t* h_arena,
-                            int64_t* arena_used)
+                            const int32_t* taus, uint8_t* h_tables, int64_t* arena_used)
 {
     const int64_t n = Q->n;
+    uint8_t* h_arena = h_tables + L.tables_bytes;
     *arena_used = 0;
     if (n > L.qcap) return PackStatus::kTooManyQueries;
     int tau_min = 0, tau_max = 0;
@@ -182,7 +185,8 @@ PackStatus pack_query_batch(const pj_index* idx, const BatchLayout& L, const pj_
         const int pad = (int)stride_of(len) - len;
         if (pad) memset(dst + len, 0, (size_t)pad);
     }
-    *(uint32_t*)h_tables = (uint32_t)n;
+    memset(h_tables, 0, kHeadBytes);
+    *(uint32_t*)(h_tables + 128) = (uint32_t)n;
     *arena_used = bytes;
     return PackStatus::kOk;
 }
@@ -192,8 +196,8 @@ uint32_t batch_result(const uint8_t* h_result, pj_stats& stats, const uint64_t**
 {
     const auto* c = (const unsigned long long*)h_result;
     *flags = c[11];
-    const uint32_t m = *(const uint32_t*)(c + 12);
-    *pairs = (const uint64_t*)(c + 13);
+    const uint32_t m = (uint32_t)c[12];
+    *pairs = (const uint64_t*)(c + kBatchResultHead);
     stats.hits += (int64_t)c[0];
     stats.candidates += (int64_t)(c[1] - c[5]);      // less the hashed-key collisions
     stats.key_collisions += (int64_t)c[5];
@@ -204,14 +208,22 @@ uint32_t batch_result(const uint8_t* h_result, pj_stats& stats, const uint64_t**
     return m;
 }
 
+void read_batch_rest(uint8_t* h_result, const uint8_t* result, uint32_t m, hipStream_t st)
+{
+    if (m <= kBatchFirstPairs) return;
+    hip_check(hipMemcpyAsync(h_result + kBatchFirstBytes, result + kBatchFirstBytes,
+                             sizeof(uint64_t) * (m - kBatchFirstPairs), hipMemcpyDeviceToHost, st),
+              "download result");
+    hip_check(hipStreamSynchronize(st), "sync");
+}
+
 struct GraphPlan {
     const pj_index* idx = nullptr;
     hipStream_t st = nullptr;
     BatchLayout L;
     Owned mem;
     BatchBuffers B;                 // device buffers of fixed capacity (owned by mem)
-    uint8_t* h_tables = nullptr;    // pinned mirrors of the batch tables, arena and result
-    uint8_t* h_arena = nullptr;
+    uint8_t* h_tables = nullptr;    // pinned mirrors of the batch tables and arena, and the result
     uint8_t* h_result = nullptr;
     hipGraphExec_t exec = nullptr;
 
@@ -219,21 +231,20 @@ struct GraphPlan {
     {
         if (exec) (void)hipGraphExecDestroy(exec);
         if (h_tables) (void)hipHostFree(h_tables);
-        if (h_arena) (void)hipHostFree(h_arena);
         if (h_result) (void)hipHostFree(h_result);
     }
 };
 
-// Plan capacities: hit records, wave chunks of 1024 candidates, accepted candidates.
+// Plan capacities: hit records, candidates, accepted candidates.
 constexpr uint64_t kPlanHits = 1ull << 20;
-constexpr uint64_t kPlanChunks = (1ull << 26) / 1024;
+constexpr uint64_t kPlanCands = 1ull << 26;
 constexpr uint64_t kPlanAccepted = 1ull << 20;
 
 // Device bytes a plan for max_queries queries allocates (its fixed-capacity buffers).
 int64_t graph_plan_device_bytes(int max_queries)
 {
     return (int64_t)batch_device_bytes(
-        batch_layout(max_queries, kPlanHits, kPlanChunks, kPlanAccepted));
+        batch_layout(max_queries, kPlanHits, kPlanCands, kPlanAccepted));
 }
 
 GraphPlan* graph_plan_create(const pj_index* idx, int max_queries, hipStream_t st,
@@ -242,14 +253,12 @@ GraphPlan* graph_plan_create(const pj_index* idx, int max_queries, hipStream_t s
     std::unique_ptr<GraphPlan> g(new GraphPlan());
     g->idx = idx;
     g->st = st;
-    g->L = batch_layout(max_queries, kPlanHits, kPlanChunks, kPlanAccepted);
+    g->L = batch_layout(max_queries, kPlanHits, kPlanCands, kPlanAccepted);
     const BatchLayout& L = g->L;
     uint8_t* base = (uint8_t*)g->mem.get("graph.buffers", batch_device_bytes(L));
     g->B = carve_batch_buffers(L, base);
-    hip_check(hipHostMalloc((void**)&g->h_tables, L.tables_bytes, hipHostMallocDefault),
-              "hipHostMalloc");
-    hip_check(hipHostMalloc((void**)&g->h_arena, L.arena_bytes, hipHostMallocDefault),
-              "hipHostMalloc");
+    hip_check(hipHostMalloc((void**)&g->h_tables, L.tables_bytes + L.arena_bytes,
+                            hipHostMallocDefault), "hipHostMalloc");
     hip_check(hipHostMalloc((void**)&g->h_result, L.result_bytes, hipHostMallocDefault),
               "hipHostMalloc");
     memset(g->h_tables, 0, L.tables_bytes);
@@ -263,12 +272,13 @@ GraphPlan* graph_plan_create(const pj_index* idx, int max_queries, hipStream_t s
     index_taus(idx, &tau_min, &tau_max);
     const TuneParams tp = tune_lookup(tune_cache, tau_max, ymean);
     GraphBatch G;
-    setup_graph_batch(idx, L, g->B, tp, G);
+    setup_graph_batch(idx, L, g->B, tau_max, (int)L.qcap, tp, G);
 
     hipGraph_t graph = nullptr;
     hip_check(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal), "begin capture");
-    hipError_t e1 = launch_graph_batch(G, st);
-    hipError_t e2 = hipMemcpyAsync(g->h_result, g->B.result, L.result_bytes,
+    hipError_t e1 = launch_graph_probe(G, st);
+    if (e1 == hipSuccess) e1 = launch_graph_verify(G, st);
+    hipError_t e2 = hipMemcpyAsync(g->h_result, g->B.result, kBatchFirstBytes,
                                    hipMemcpyDeviceToHost, st);
     hipError_t e3 = hipStreamEndCapture(st, &graph);
     if (e1 != hipSuccess || e2 != hipSuccess || e3 != hipSuccess) {
@@ -290,14 +300,10 @@ bool graph_plan_run(GraphPlan* g, const pj_strings* Q, const int32_t* taus,
 {
     if (Q->n == 0) return true;
     int64_t bytes = 0;
-    if (pack_query_batch(g->idx, g->L, Q, taus, g->h_tables, g->h_arena, &bytes) !=
-        PackStatus::kOk)
+    if (pack_query_batch(g->idx, g->L, Q, taus, g->h_tables, &bytes) != PackStatus::kOk)
         return false;
-    hip_check(hipMemcpyAsync(g->B.tables, g->h_tables, g->L.tables_bytes, hipMemcpyHostToDevice,
-                             g->st), "upload batch tables");
-    if (bytes > 0)
-        hip_check(hipMemcpyAsync(g->B.arena, g->h_arena, (size_t)bytes, hipMemcpyHostToDevice,
-                                 g->st), "upload batch arena");
+    hip_check(hipMemcpyAsync(g->B.tables, g->h_tables, g->L.tables_bytes + (size_t)bytes,
+                             hipMemcpyHostToDevice, g->st), "upload batch");
     hip_check(hipGraphLaunch(g->exec, g->st), "graph launch");
     hip_check(hipStreamSynchronize(g->st), "sync");
     pj_stats part{};
@@ -305,6 +311,7 @@ bool graph_plan_run(GraphPlan* g, const pj_strings* Q, const int32_t* taus,
     unsigned long long flags = 0;
     const uint32_t m = batch_result(g->h_result, part, &out, &flags);
     if (flags != 0) return false;
+    read_batch_rest(g->h_result, g->B.result, m, g->st);
     pairs.insert(pairs.end(), out, out + m);
     stats.hits += part.hits;
     stats.candidates += part.candidates;

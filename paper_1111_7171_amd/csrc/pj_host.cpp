@@ -33,13 +33,22 @@ constexpr size_t kPinnedOutputMin = 1u << 20;
 constexpr uint64_t kBucketMinCandidates = 1ull << 20;
 
 // List segments per wave chunk without a tuned setting.  A chunk sets a hit up anew where it begins
-// inside one, and its ticket is an atomic on one address (6 ns each, one after another), so chunks
-// are as long as the balance between some 8,192 waves allows: at least four a wave, at most 256
-// segments.  Measured on short strings, list kernel: 10^6 at tau = 4 (1.6x10^8 segments) 80 ms with
-// 4, 50 with 32, 48 with 128-256; 10^5 at tau = 3 (3x10^5) 0.24, 0.19 and 0.37 ms.
+// inside one, and its ticket is an atomic on one address (some 10 ns each, one after another):
+// up to 32 segments a chunk, all of them are handed out at the start, a chunk per wave of a full
+// chip; beyond, waves take more by ticket, and long runs take longer chunks.  Measured on short
+// strings, list kernel, with 4 / 8 / 32 / 128 segments: 10^6 at tau = 1 0.06, 0.04, 0.09, 0.30 ms;
+// 10^5 at tau = 3 0.52, 0.28, 0.16, 0.39; 2x10^5 at tau = 4 18.5, 9.3, 2.6, 2.7; 10^6 at tau = 4 with
+// 32 / 128 / 256: 50, 48.7, 47.5.
 static int auto_seg_chunk(uint64_t nseg)
 {
-    return (int)std::max<uint64_t>(1, std::min<uint64_t>(nseg / 32768, 256));
+    const uint64_t even = std::max<uint64_t>(4, std::min<uint64_t>((nseg + 8191) / 8192, 32));
+    return (int)std::max<uint64_t>(even, std::min<uint64_t>(nseg / 131072, 256));
+}
+
+uint64_t bucket_min_candidates()
+{
+    if (const char* e = getenv("PJ_BUCKET_MIN_CANDIDATES")) return strtoull(e, nullptr, 10);
+    return kBucketMinCandidates;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -800,8 +809,7 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
     uint64_t cls_nseg[kLenClasses] = {};
     uint32_t* segp = nullptr;                  // class c's scan at segp + cls_off[c] + c
     // few candidates (a serving batch): the bucketing round trips would cost more than they save
-    uint64_t bucket_min = kBucketMinCandidates;
-    if (const char* e = getenv("PJ_BUCKET_MIN_CANDIDATES")) bucket_min = strtoull(e, nullptr, 10);
+    const uint64_t bucket_min = bucket_min_candidates();
     if (batched && J.nhits > 0 && J.ncand >= bucket_min) {
         const unsigned g = slot_bucket_grid(J.nhits);
         const size_t nbb = (size_t)g * kHitBuckets;
@@ -1034,7 +1042,8 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
                     hip_check(launch_verify_segs(vc, bigp + o, segp + o + c, nb, nseg, first2,
                                                  chunk_c[c], J.tp.lane_cands,
                                                  (int)((waves + 3) / 4),
-                                                 J.counters + kTicketWord + c, st),
+                                                 waves < nchunks ? J.counters + kTicketWord + c
+                                                                 : nullptr, st),
                               "verify_segs");
                     const int s1 = tm.mark();
                     J.kernel_marks.push_back({s0, s1, 2});

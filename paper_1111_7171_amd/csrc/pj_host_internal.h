@@ -52,6 +52,8 @@ struct Owned : Alloc {
 
 Workspace& thread_workspace();
 int device_cus();
+// candidates from which the batched path buckets its hits (tests set it by the environment)
+uint64_t bucket_min_candidates();
 
 // Values the host reads back from the device to size the next phase.  A self-join plan
 // (pj_plan.cpp) runs the join once recording them in order, then captures the same sequence of
@@ -165,16 +167,22 @@ int index_device(const pj_index* idx);
 int64_t query_selections(const pj_index* idx, int n, int tau);
 
 // Fixed-capacity buffers of one mixed-tau query batch run by launch_graph_batch: the layout of
-// the batch tables (nx | lenstart | gbase | perm | q_tau | slen, packed on the host), the arena
-// and the device work buffers.  Used by the serving slots' captured pipelines (allocated) and
-// by pj_query_noalloc (carved out of a static device array).
+// the batch tables (counters, zero | nx | lenstart | gbase | perm | q_tau | slen, packed on the
+// host) and the arena, uploaded in one copy, and the device work buffers.  Used by the serving
+// slots' captured pipelines (allocated), by small pj_query calls (in the thread's workspace) and by
+// pj_query_noalloc (carved out of a static device array).
 struct BatchLayout {
     int64_t qcap = 0, bcap = 0;             // queries, arena bytes
-    uint64_t hcap = 0, chunk_cap = 0, acc_cap = 0;
+    uint64_t hcap = 0, cand_cap = 0, acc_cap = 0;
     size_t off_lenstart = 0, off_gbase = 0, off_perm = 0, off_qtau = 0, off_slen = 0;
     size_t tables_bytes = 0, arena_bytes = 0;
+    size_t first_words = 0;
     size_t result_bytes = 0;                // [counters 8 | bcounts 4 | out_n | out kGraphSortCap]
 };
+// Part of a result block read back at once: most batches have no more pairs (a larger one's rest
+// is a second copy).
+constexpr uint32_t kBatchFirstPairs = 1024;
+constexpr size_t kBatchFirstBytes = sizeof(uint64_t) * (kBatchResultHead + kBatchFirstPairs);
 struct BatchBuffers {
     uint8_t* tables = nullptr;
     uint8_t* arena = nullptr;
@@ -185,15 +193,17 @@ struct BatchBuffers {
     uint8_t* result = nullptr;
 };
 enum class PackStatus { kOk, kTooManyQueries, kTauOutOfRange, kTooManySelections, kTooManyBytes };
-BatchLayout batch_layout(int max_queries, uint64_t hcap, uint64_t chunk_cap, uint64_t acc_cap);
+BatchLayout batch_layout(int max_queries, uint64_t hcap, uint64_t cand_cap, uint64_t acc_cap);
 size_t batch_device_bytes(const BatchLayout& L);
 BatchBuffers carve_batch_buffers(const BatchLayout& L, uint8_t* base);
-void setup_graph_batch(const pj_index* idx, const BatchLayout& L, const BatchBuffers& B,
-                       const TuneParams& tp, GraphBatch& G);
-// Packs Q into the host mirrors of the tables and the arena; *arena_used = arena bytes to upload.
+// tau_max: the largest threshold a batch may hold; queries: the most queries (grid sizes)
+void setup_graph_batch(const pj_index* idx, const BatchLayout& L, const BatchBuffers& B, int tau_max,
+                       int queries, const TuneParams& tp, GraphBatch& G);
+// Packs Q into the host mirror of the tables and, after them, the arena; *arena_used = its bytes.
 PackStatus pack_query_batch(const pj_index* idx, const BatchLayout& L, const pj_strings* Q,
-                            const int32_t* taus, uint8_t* h_tables, uint8_t* h_arena,
-                            int64_t* arena_used);
+                            const int32_t* taus, uint8_t* h_tables, int64_t* arena_used);
+// Reads the rest of a result block of m pairs after its first part has been read back to h_result.
+void read_batch_rest(uint8_t* h_result, const uint8_t* result, uint32_t m, hipStream_t st);
 // Reads a batch result block: adds its counters to stats, returns the number of sorted
 // (query << 32 | indexed id) pairs at *pairs; *flags != 0 means a capacity overflowed.
 uint32_t batch_result(const uint8_t* h_result, pj_stats& stats, const uint64_t** pairs,

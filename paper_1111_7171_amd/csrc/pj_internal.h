@@ -183,8 +183,8 @@ struct VerifyParams {
     uint64_t* out; uint64_t out_cap;                      // accepted (gx << 32 | gy)
     unsigned long long* counters;    // [3] accepted, [4] cells, [5] guard misses, [7] list-segment cells
     int shards;                      // statistics lines after them (0: none)
-    // device-resident sizes (captured batches): [0] hits, [1] candidates, [2] wave chunks;
-    // when set they replace nhits, ncand and the launch's chunk count
+    // device-resident sizes (captured batches): [0] hits, [1] candidates, [2] wave chunks, [4]
+    // rounds per chunk; when set they replace nhits, ncand, the launch's chunk count, wave_rounds
     const unsigned long long* dev_counts;
     int exact_len;              // segments up to this length have exact keys (no byte guard)
     int wave_rounds;            // batched verification: rounds of 64 candidates per wave chunk
@@ -255,7 +255,8 @@ hipError_t launch_slot_bucket(const Hit* hits, const unsigned long long* nh_dev,
                               size_t scan_bytes, Hit* out, hipStream_t s);
 // list-segment verification of the lists with >= big candidates (hits big[0 .. nbig), segp =
 // exclusive scan of ceil(count / seg_members), nseg segments, `chunk` segments per wave chunk; first:
-// seg_chunks(nseg, chunk) u32 of scratch; ticket: a zeroed word)
+// seg_chunks(nseg, chunk) u32 of scratch; ticket: a zeroed word, or nullptr when the grid has a wave
+// for every chunk)
 // list segments of `members` candidates each (seg_members: what k_verify_segs expects)
 int seg_members(int y_maxlen, int tau, int lane_cands);
 hipError_t launch_seg_counts(const Hit* big, uint64_t nbig, int members, uint32_t* segs,
@@ -299,28 +300,35 @@ hipError_t launch_verify_long(const VerifyParams& V, uint64_t ncand, int max_row
                               int grid, hipStream_t s);
 // wave chunks of 64 * rounds candidates (rounds in [1, kBatchedRoundsMax])
 uint64_t batched_chunks(uint64_t ncand, int rounds);
-// A captured query batch: every size is read from device memory, so one instantiated graph
-// serves every batch.  counters: [0] hits [1] candidates [2] selected [3] accepted [4] cells
-// [5] guard misses [6] side pairs [7] unused; bcounts: [0] hits [1] candidates [2] wave chunks
-// [3] overflow flags (1 hits, 2 chunks, 4 accepted, 8 sort); out: the batch's sorted distinct
-// (query id << 32 | indexed id) pairs, out_n their number.
+// A query batch with every size in device memory (a serving slot's captured pipeline, a small
+// pj_query, pj_query_noalloc).  counters (zeroed by the upload of the batch tables): [0] hits
+// [1] candidates [2] selected [3] accepted [4] cells [5] guard misses [6] side pairs [7] unused;
+// bcounts after them: [0] hits [1] candidates [2] wave chunks [3] overflow flags (1 hits, 2
+// candidates, 4 accepted, 8 sort) [4] rounds of 64 candidates per chunk.  result: the 8 counters, 4
+// bcounts, the number of pairs, then the batch's sorted distinct (query id << 32 | indexed id)
+// pairs.
 struct GraphBatch {
     ProbeParams probe;          // nx_dev set; hits/hit_cap/counters set
     int probe_grid;
     VerifyParams verify;        // dev_counts = bcounts; prefix/out/out_cap/counters set
     int verify_grid;
     unsigned long long* bcounts;
-    uint32_t* first; uint64_t chunk_cap;
+    uint32_t* first;            // [max(kBatchWaves, cand_cap / 1024) + 1]
+    uint64_t cand_cap;          // candidates beyond it overflow
     // short side path (indexed strings shorter than tau_max + 1), y_count == 0: none
     uint32_t y_first, y_count;
     const uint8_t* y_arena; const uint16_t* y_slen; const int32_t* y_lenstart;
     const int64_t* y_gbase;
     // output
     const int32_t* xperm; const int32_t* yperm;
-    uint64_t* out; uint32_t* out_n;
+    unsigned long long* result;
 };
 constexpr int kGraphSortCap = 8192;     // accepted pairs a captured batch can sort
-hipError_t launch_graph_batch(const GraphBatch& G, hipStream_t s);
+constexpr int kBatchWaves = 8192;       // wave chunks a batch is spread over before they grow
+constexpr int kBatchResultHead = 13;    // words of a result before its pairs
+// the probe, then the rest of the batch
+hipError_t launch_graph_probe(const GraphBatch& G, hipStream_t s);
+hipError_t launch_graph_verify(const GraphBatch& G, hipStream_t s);
 hipError_t launch_short_path(const DevSet& P, const DevSet& Y, int tau, int self,
                              const int32_t* q_tau, uint64_t* out, uint64_t out_cap,
                              unsigned long long* counters, hipStream_t s);

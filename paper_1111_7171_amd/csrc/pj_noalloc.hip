@@ -1,8 +1,8 @@
 // pj_noalloc.hip -- pj_query_noalloc: pj_query for callers that cannot allocate memory.
 //
 // The query batch runs the same device phases as a serving slot's captured pipeline
-// (launch_graph_batch: counter reset by a fill kernel, multi-match probe, candidate prefix,
-// extension verification, short-string side path, in-LDS sort and deduplication), but every
+// (launch_graph_probe, launch_graph_verify: multi-match probe, candidate prefix, extension
+// verification, short-string side path, in-LDS sort and deduplication), but every
 // device work buffer is carved out of one static device array, `scratch`, and the host staging
 // lives in static host arrays: the call makes no device or host allocation.  Capacities are
 // fixed (kNaQueries queries, kNaHits hit records, ...); a batch beyond them is refused with
@@ -20,7 +20,7 @@ namespace pj {
 
 constexpr int kNaQueries = 512;                        // queries per call
 constexpr uint64_t kNaHits = 1ull << 18;               // hit records (Lemma 2 bound of the batch)
-constexpr uint64_t kNaChunks = (1ull << 24) / 1024;    // wave chunks: 2^24 candidates
+constexpr uint64_t kNaCands = 1ull << 24;              // candidates
 constexpr uint64_t kNaAccepted = kGraphSortCap;        // accepted candidates (the sort's limit)
 constexpr size_t kNaScratchBytes = 8ull << 20;         // device work buffers, one array per GPU
 constexpr size_t kNaTablesMax = 32u << 10;             // host staging of the batch tables
@@ -39,8 +39,7 @@ namespace pj {
 
 static std::mutex s_na_mu;                             // one call at a time per process
 static void* s_na_scratch[kNaMaxDevices];              // hipGetSymbolAddress(scratch) per device
-alignas(256) static uint8_t s_na_tables[kNaTablesMax];
-alignas(256) static uint8_t s_na_arena[kNaArenaMax];
+alignas(256) static uint8_t s_na_tables[kNaTablesMax + kNaArenaMax];   // tables, then the arena
 alignas(256) static uint8_t s_na_result[kNaResultMax];
 
 // The current device's copy of `scratch`, resolved once per device with that device current.
@@ -85,7 +84,7 @@ static void query_noalloc(const pj_index* idx, const pj_strings* Q, const int32_
     t_stats.strings = Q->n;
     if (Q->n == 0) return;
 
-    const BatchLayout L = batch_layout(kNaQueries, kNaHits, kNaChunks, kNaAccepted);
+    const BatchLayout L = batch_layout(kNaQueries, kNaHits, kNaCands, kNaAccepted);
     if (batch_device_bytes(L) > kNaScratchBytes || L.tables_bytes > kNaTablesMax ||
         (size_t)L.bcap + 64 > kNaArenaMax || L.result_bytes > kNaResultMax)
         throw Error(PJ_EDEVICE, "static scratch layout does not fit its arrays");
@@ -93,7 +92,7 @@ static void query_noalloc(const pj_index* idx, const pj_strings* Q, const int32_
 
     std::lock_guard<std::mutex> lk(s_na_mu);
     int64_t bytes = 0;
-    switch (pack_query_batch(idx, L, Q, taus, s_na_tables, s_na_arena, &bytes)) {
+    switch (pack_query_batch(idx, L, Q, taus, s_na_tables, &bytes)) {
     case PackStatus::kOk: break;
     case PackStatus::kTooManySelections:
         throw Error(PJ_ERANGE, "the batch selects more than %llu substrings (Lemma 2 bound), "
@@ -107,14 +106,14 @@ static void query_noalloc(const pj_index* idx, const pj_strings* Q, const int32_
     uint8_t* base = noalloc_scratch(dev);
     const BatchBuffers B = carve_batch_buffers(L, base);
     GraphBatch G;
-    setup_graph_batch(idx, L, B, TuneParams{}, G);
-    hip_check(hipMemcpyAsync(B.tables, s_na_tables, L.tables_bytes, hipMemcpyHostToDevice, st),
-              "upload batch tables");
-    if (bytes > 0)
-        hip_check(hipMemcpyAsync(B.arena, s_na_arena, (size_t)bytes, hipMemcpyHostToDevice, st),
-                  "upload batch arena");
-    hip_check(launch_graph_batch(G, st), "query batch");
-    hip_check(hipMemcpyAsync(s_na_result, B.result, L.result_bytes, hipMemcpyDeviceToHost, st),
+    int tmax = 0;
+    for (int64_t q = 0; q < Q->n; ++q) tmax = std::max(tmax, taus[q]);
+    setup_graph_batch(idx, L, B, tmax, (int)Q->n, TuneParams{}, G);
+    hip_check(hipMemcpyAsync(B.tables, s_na_tables, L.tables_bytes + (size_t)bytes,
+                             hipMemcpyHostToDevice, st), "upload batch");
+    hip_check(launch_graph_probe(G, st), "query batch");
+    hip_check(launch_graph_verify(G, st), "query batch");
+    hip_check(hipMemcpyAsync(s_na_result, B.result, kBatchFirstBytes, hipMemcpyDeviceToHost, st),
               "download result");
     hip_check(hipStreamSynchronize(st), "sync");
     const uint64_t* pairs = nullptr;
@@ -122,9 +121,10 @@ static void query_noalloc(const pj_index* idx, const pj_strings* Q, const int32_
     const uint32_t m = batch_result(s_na_result, t_stats, &pairs, &flags);
     if (flags & 1) throw Error(PJ_ERANGE, "more hit records than the static buffer holds");
     if (flags & 2)
-        throw Error(PJ_ERANGE, "more than %llu candidates", (unsigned long long)(kNaChunks * 1024));
+        throw Error(PJ_ERANGE, "more than %llu candidates", (unsigned long long)kNaCands);
     if (flags & 12)
         throw Error(PJ_ERANGE, "more than %d accepted candidates", (int)kNaAccepted);
+    read_batch_rest(s_na_result, B.result, m, st);
     *out_count = (int64_t)m;
     t_stats.pairs = (int64_t)m;
     if ((int64_t)m > out_cap)
