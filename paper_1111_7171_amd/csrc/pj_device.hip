@@ -112,6 +112,8 @@ __device__ inline void block_add(unsigned long long* counter, uint64_t v)
 // String arena: length histogram + validation, (length, id) keys, packing
 // ------------------------------------------------------------------------------------------
 
+// Few blocks: each adds its counts to the shared ones, an atomic per length present (10^6 short
+// strings: 46 us with a block per 256 strings, 9 us so)
 __global__ __launch_bounds__(kBlock) void k_length_hist(const int32_t* __restrict__ offs,
                                                         int64_t n, int32_t* __restrict__ lcount,
                                                         int32_t* __restrict__ err)
@@ -119,12 +121,13 @@ __global__ __launch_bounds__(kBlock) void k_length_hist(const int32_t* __restric
     __shared__ int32_t h[kLenTab];
     for (int k = threadIdx.x; k < kLenTab; k += kBlock) h[k] = 0;
     __syncthreads();
-    int64_t id = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     int32_t e = 0;
-    if (id < n) {
-        int32_t a = offs[id], b = offs[id + 1];
-        int32_t l = b - a;
+    for (int64_t id = (int64_t)blockIdx.x * kBlock + threadIdx.x; id < n;
+         id += (int64_t)gridDim.x * kBlock) {
+        const int32_t a = offs[id], b = offs[id + 1];
         if (id == 0 && a != 0) e |= 1;
+        // the length as a 64-bit difference: offsets of any value are judged, not wrapped
+        const int64_t l = (int64_t)b - (int64_t)a;
         if (l < 0) e |= 2;
         else if (l > kLenMax) e |= 4;
         else atomicAdd(&h[l], 1);
@@ -146,30 +149,70 @@ __global__ __launch_bounds__(kBlock) void k_len_keys(const int32_t* __restrict__
     }
 }
 
-// One wave per sorted position: copies the string into its padded slot of the sorted arena.
-// 2^lps_shift lanes per string, at least a quarter of the widest slot (16 when every slot is at
-// most 64 bytes: a wave packs 4 strings at once, so their dependent loads of position, offsets
-// and group base overlap; 32 up to 128 bytes; else 64)
+// The strings in their padded slots of the sorted arena, 2^lps_shift lanes per string and 16 bytes
+// a lane at a time (unaligned reads, aligned writes), and the byte values present: flags in LDS by
+// block, added to the set's bitmap at the end.  A chunk that would read past the set's last byte is
+// read byte by byte.  10^6 short strings: 59 us byte by byte and 37 for the byte values in a pass
+// of their own, 32 us so (48 with a tested bit for each byte in place of the flags).
+struct __attribute__((packed)) Unaligned16 {
+    uint32_t w[4];
+};
+
 __global__ __launch_bounds__(kBlock) void k_pack_arena(const uint8_t* __restrict__ bytes,
                                                        const int32_t* __restrict__ offs,
                                                        const int32_t* __restrict__ perm, int64_t n,
                                                        const int32_t* __restrict__ lenstart,
                                                        const int64_t* __restrict__ gbase,
                                                        uint8_t* __restrict__ sarena,
-                                                       uint16_t* __restrict__ slen, int lps_shift)
+                                                       uint16_t* __restrict__ slen, int lps_shift,
+                                                       uint32_t* __restrict__ bitmap)
 {
+    __shared__ uint32_t seen[256];           // by byte value: not zero if present
+    for (int k = threadIdx.x; k < 256; k += kBlock) seen[k] = 0;
+    __syncthreads();
     const int lps = 1 << lps_shift;
     const int sub = threadIdx.x & (lps - 1);
+    const int64_t total = offs[n];
     int64_t g = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> lps_shift;
     const int64_t gstep = ((int64_t)gridDim.x * kBlock) >> lps_shift;
     for (; g < n; g += gstep) {
-        int32_t id = perm[g];
-        int32_t a = offs[id];
-        int32_t l = offs[id + 1] - a;
-        uint8_t* dst = sarena + gbase[l] + (g - lenstart[l]) * stride_of(l);
-        int32_t st = (int32_t)stride_of(l);
-        for (int32_t k = sub; k < st; k += lps) dst[k] = (k < l) ? bytes[a + k] : (uint8_t)0;
+        const int32_t id = perm[g];
+        const int64_t a = offs[id];
+        const int l = (int)(offs[id + 1] - a);
+        uint4* dst = reinterpret_cast<uint4*>(sarena + gbase[l] + (g - lenstart[l]) * stride_of(l));
         if (sub == 0) slen[g] = (uint16_t)l;
+        for (int q = sub; 16 * q < l; q += lps) {
+            const int left = l - 16 * q;                   // bytes of the string from here on
+            uint32_t w[4] = {0u, 0u, 0u, 0u};
+            const uint8_t* src = bytes + a + 16 * q;
+            if (a + 16 * q + 16 <= total) {
+                const Unaligned16 v = *reinterpret_cast<const Unaligned16*>(src);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int in = left - 4 * k;           // bytes of the word inside the string
+                    w[k] = in >= 4 ? v.w[k] : in > 0 ? v.w[k] & ((1u << (8 * in)) - 1u) : 0u;
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < 16; ++k)
+                    if (k < left) w[k >> 2] |= (uint32_t)src[k] << (8 * (k & 3));
+            }
+            dst[q] = make_uint4(w[0], w[1], w[2], w[3]);
+            if (bitmap) {
+#pragma unroll
+                for (int k = 0; k < 16; ++k) {
+                    const uint32_t byte = (w[k >> 2] >> ((k & 3) * 8)) & 255u;
+                    if (k < left) seen[byte] = 1u;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    if (bitmap && threadIdx.x < 8) {
+        uint32_t m = 0;
+        for (int k = 0; k < 32; ++k) m |= seen[32 * threadIdx.x + k] << k;
+        if (m & ~__hip_atomic_load(&bitmap[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicOr(&bitmap[threadIdx.x], m);
     }
 }
 
@@ -179,47 +222,6 @@ __global__ __launch_bounds__(kBlock) void k_pack_arena(const uint8_t* __restrict
 
 // One thread per (indexed string, slot): emits (key, g) at a position grouped by (l, i) and
 // ordered by g inside the group, so a stable sort by key keeps lists in ascending g.
-// bitmap of the bytes present in the strings of a set (one thread per string)
-// Byte values present in the arena: one thread per 16-byte chunk of the length-sorted arena
-// (coalesced wide loads); the chunk's length group l is found by binary search over the
-// groups' byte ranges [gbase[l], gbase[l + 1]) (an empty group's range is empty), and only the
-// bytes inside a string count, not the padding of its slot.
-__global__ __launch_bounds__(kBlock) void k_byte_presence(const uint8_t* __restrict__ sarena,
-                                                          const int64_t* __restrict__ gbase,
-                                                          int64_t total,
-                                                          uint32_t* __restrict__ bitmap)
-{
-    __shared__ uint32_t bm[8];
-    if (threadIdx.x < 8) bm[threadIdx.x] = 0;
-    __syncthreads();
-    const int64_t nchunks = total >> 4;
-    for (int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x; c < nchunks;
-         c += (int64_t)gridDim.x * kBlock) {
-        const int64_t o = c << 4;
-        int lo = 0, hi = kLenTab - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            const int64_t end = mid + 1 < kLenTab ? gbase[mid + 1] : total;
-            if (end > o) hi = mid; else lo = mid + 1;
-        }
-        const int l = lo;
-        const int within = (int)((o - gbase[l]) % stride_of(l));
-        const int valid = l - within < 16 ? l - within : 16;
-        const uint4 v = *reinterpret_cast<const uint4*>(sarena + o);
-        const uint32_t wd[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            if (k < valid) {
-                const uint32_t byte = (wd[k >> 2] >> ((k & 3) * 8)) & 255u;
-                const uint32_t bit = 1u << (byte & 31u);
-                if (!(bm[byte >> 5] & bit)) atomicOr(&bm[byte >> 5], bit);
-            }
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x < 8 && bm[threadIdx.x]) atomicOr(&bitmap[threadIdx.x], bm[threadIdx.x]);
-}
-
 __global__ __launch_bounds__(kBlock) void k_emit_segments(const uint8_t* __restrict__ sarena,
                                                           const uint16_t* __restrict__ slen,
                                                           const int32_t* __restrict__ lenstart,
@@ -2417,7 +2419,8 @@ hipError_t launch_length_hist(const int32_t* offs, int64_t n, int32_t* lcount, i
                               hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_length_hist, dim3(blocks_for(n)), dim3(kBlock), 0, s, offs, n, lcount, err);
+    const unsigned grid = (unsigned)std::min<uint64_t>(blocks_for((uint64_t)n), 256);
+    hipLaunchKernelGGL(k_length_hist, dim3(grid), dim3(kBlock), 0, s, offs, n, lcount, err);
     return hipGetLastError();
 }
 
@@ -2431,27 +2434,17 @@ hipError_t launch_iota_len_keys(const int32_t* offs, int64_t n, uint32_t* keys, 
 
 hipError_t launch_pack_arena(const uint8_t* bytes, const int32_t* offs, const int32_t* perm,
                              int64_t n, const int32_t* lenstart, const int64_t* gbase,
-                             uint8_t* sarena, uint16_t* slen, int lmax, hipStream_t s)
+                             uint8_t* sarena, uint16_t* slen, int lmax, uint32_t* bitmap,
+                             hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    const int64_t widest = stride_of(std::max(lmax, 0));
-    const int lps_shift = widest <= 64 ? 4 : widest <= 128 ? 5 : 6;
+    // lanes for the widest slot, up to a wave
+    int lps_shift = 0;
+    while (lps_shift < 6 && (16 << lps_shift) < lmax) ++lps_shift;
     const uint64_t threads = (uint64_t)n << lps_shift;
-    uint64_t blocks = (threads + kBlock - 1) / kBlock;
-    if (blocks > 65536) blocks = 65536;
+    const uint64_t blocks = std::min<uint64_t>((threads + kBlock - 1) / kBlock, bitmap ? 2048 : 65536);
     hipLaunchKernelGGL(k_pack_arena, dim3((unsigned)blocks), dim3(kBlock), 0, s, bytes, offs, perm,
-                       n, lenstart, gbase, sarena, slen, lps_shift);
-    return hipGetLastError();
-}
-
-hipError_t launch_byte_presence(const DevSet& S, uint32_t* bitmap, hipStream_t s)
-{
-    if (S.n == 0) return hipSuccess;
-    const uint64_t nchunks = (uint64_t)S.arena_bytes >> 4;
-    if (nchunks == 0) return hipSuccess;
-    const unsigned grid = (unsigned)std::min<uint64_t>(blocks_for(nchunks), 2048);
-    hipLaunchKernelGGL(k_byte_presence, dim3(grid), dim3(kBlock), 0, s, S.sarena, S.gbase,
-                       (int64_t)S.arena_bytes, bitmap);
+                       n, lenstart, gbase, sarena, slen, lps_shift, bitmap);
     return hipGetLastError();
 }
 

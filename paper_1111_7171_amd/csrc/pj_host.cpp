@@ -381,7 +381,7 @@ static size_t device_extent(const void* p, const std::string& what)
 }
 
 void build_set(const pj_strings* S, bool on_device, Alloc& A, const std::string& tag, DevSet& D,
-               hipStream_t st)
+               hipStream_t st, bool with_sym)
 {
     ReadbackScope rb_scope;
     if (!S) throw Error(PJ_EINVAL, "%s: null pj_strings", tag.c_str());
@@ -467,25 +467,46 @@ void build_set(const pj_strings* S, bool on_device, Alloc& A, const std::string&
     D.perm = (int32_t*)A.get(nm("perm").c_str(), sizeof(int32_t) * (size_t)std::max<int64_t>(n, 1));
     D.slen = (uint16_t*)A.get(nm("slen").c_str(), sizeof(uint16_t) * (size_t)std::max<int64_t>(n, 1));
     D.sarena = (uint8_t*)A.get(nm("sarena").c_str(), (size_t)bytes + 64);
-    if (n == 0) return;
-
-    // stable sort of ids by length -> perm
     Workspace& W = thread_workspace();
-    uint32_t* k0 = (uint32_t*)W.get("lensort.k0", sizeof(uint32_t) * (size_t)n);
-    uint32_t* k1 = (uint32_t*)W.get("lensort.k1", sizeof(uint32_t) * (size_t)n);
-    uint32_t* v1 = (uint32_t*)W.get("lensort.v1", sizeof(uint32_t) * (size_t)n);
-    size_t tb = radix_tmp_bytes((uint64_t)n);
-    void* tmp = W.get("radix.tmp", tb);
-    // the ids start in the buffer from which the passes end in perm
-    const int len_bits = bitlen((uint64_t)std::max(D.lmax, 1));
-    uint32_t* v0 = (uint32_t*)D.perm;
-    if (radix_passes(len_bits) & 1) std::swap(v0, v1);
-    hip_check(launch_iota_len_keys(d_offs, n, k0, v0, st), "len_keys");
-    bool alt = false;
-    hip_check(radix_sort_u32(k0, v0, k1, v1, (uint64_t)n, len_bits, tmp, tb, &alt, st),
-              "radix(len)");
-    hip_check(launch_pack_arena(d_bytes, d_offs, D.perm, n, D.lenstart, D.gbase, D.sarena, D.slen,
-                                D.lmax, st), "pack_arena");
+    uint32_t* bitmap = nullptr;
+    if (with_sym) {
+        bitmap = (uint32_t*)W.get("set.bytemap", 8 * sizeof(uint32_t));
+        zero_words(bitmap, 8 * sizeof(uint32_t), st);
+    }
+    if (n > 0) {
+        // stable sort of ids by length -> perm
+        size_t tb = radix_tmp_bytes((uint64_t)n);
+        void* tmp = W.get("radix.tmp", tb);
+        if (D.lmax < 256) {
+            hip_check(launch_length_sort(d_offs, n, lcount, D.perm, tmp, tb, st), "length_sort");
+        } else {
+            uint32_t* k0 = (uint32_t*)W.get("lensort.k0", sizeof(uint32_t) * (size_t)n);
+            uint32_t* k1 = (uint32_t*)W.get("lensort.k1", sizeof(uint32_t) * (size_t)n);
+            uint32_t* v1 = (uint32_t*)W.get("lensort.v1", sizeof(uint32_t) * (size_t)n);
+            // two passes: the ids end where they start
+            hip_check(launch_iota_len_keys(d_offs, n, k0, (uint32_t*)D.perm, st), "len_keys");
+            bool alt = false;
+            hip_check(radix_sort_u32(k0, (uint32_t*)D.perm, k1, v1, (uint64_t)n, 16, tmp, tb, &alt,
+                                     st), "radix(len)");
+        }
+        hip_check(launch_pack_arena(d_bytes, d_offs, D.perm, n, D.lenstart, D.gbase, D.sarena,
+                                    D.slen, D.lmax, bitmap, st), "pack_arena");
+    }
+    if (with_sym) {
+        // symbol map of the bytes the set contains: codes 1..sigma, 0 for absent bytes
+        uint32_t hb[8];
+        readback(hb, bitmap, sizeof hb, st);
+        sync_readback(st);
+        uint16_t code[256];
+        int sigma = 0;
+        for (int b = 0; b < 256; ++b)
+            code[b] = (hb[b >> 5] >> (b & 31)) & 1u ? (uint16_t)(++sigma) : (uint16_t)0;
+        const int sbits = std::max(1, bitlen((uint64_t)sigma));
+        uint16_t* dcode = (uint16_t*)A.get(nm("sym").c_str(), sizeof code);
+        upload(dcode, code, sizeof code, st);
+        sync_readback(st);                  // code[] is on this stack frame
+        D.sym = SymMap{dcode, sbits, kHashBits / sbits};
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -504,25 +525,7 @@ void build_index(const DevSet& D, int tau, Alloc& A, const std::string& tag, Dev
     int64_t E = g_count * T1;
     if (E >= (int64_t)UINT32_MAX) throw Error(PJ_ERANGE, "index too large (%lld entries)", (long long)E);
     X.entries = E;
-    {
-        // symbol map of the bytes the set contains: codes 1..sigma, 0 for absent bytes
-        Workspace& WS = thread_workspace();
-        uint32_t* bm = (uint32_t*)WS.get("index.bytemap", 8 * sizeof(uint32_t));
-        zero_words(bm, 8 * sizeof(uint32_t), st);
-        hip_check(launch_byte_presence(D, bm, st), "byte_presence");
-        uint32_t hb[8];
-        readback(hb, bm, sizeof hb, st);
-        sync_readback(st);
-        uint16_t code[256];
-        int sigma = 0;
-        for (int b = 0; b < 256; ++b)
-            code[b] = (hb[b >> 5] >> (b & 31)) & 1u ? (uint16_t)(++sigma) : (uint16_t)0;
-        const int sbits = std::max(1, bitlen((uint64_t)sigma));
-        uint16_t* dcode = (uint16_t*)A.get(nm("sym").c_str(), sizeof code);
-        upload(dcode, code, sizeof code, st);
-        sync_readback(st);                  // code[] is on this stack frame
-        X.sym = SymMap{dcode, sbits, kHashBits / sbits};
-    }
+    X.sym = D.sym;
     if (E == 0) {
         X.keys = (uint64_t*)A.get(nm("keys").c_str(), 16);
         X.vals = (uint32_t*)A.get(nm("vals").c_str(), 16);
@@ -1276,8 +1279,8 @@ static void join_impl(const pj_strings* R, const pj_strings* S, int32_t tau, con
     Timer tm(st);
     int e0 = tm.mark();
     DevSet P, Y;
-    build_set(self ? S : R, on_dev, W, "P", P, st);
-    if (!self) build_set(S, on_dev, W, "Y", Y, st);
+    build_set(self ? S : R, on_dev, W, "P", P, st, self);
+    if (!self) build_set(S, on_dev, W, "Y", Y, st, true);
     const DevSet& YY = self ? P : Y;
     int e1 = tm.mark();
     DevIndex X;

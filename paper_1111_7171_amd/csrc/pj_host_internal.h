@@ -127,8 +127,9 @@ struct JoinScratch {
     std::vector<Mark> kernel_marks;
 };
 
+// with_sym: also the symbol map of the set's bytes (sets to be indexed)
 void build_set(const pj_strings* S, bool on_device, Alloc& A, const std::string& tag, DevSet& D,
-               hipStream_t st);
+               hipStream_t st, bool with_sym = false);
 void build_index(const DevSet& D, int tau, Alloc& A, const std::string& tag, DevIndex& X,
                  hipStream_t st, bool with_inline = false, bool with_share = false);
 // What to probe: a uniform tau against one index, or per-probe thresholds (q_tau, by sorted

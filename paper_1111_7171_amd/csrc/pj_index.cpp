@@ -238,7 +238,7 @@ int pj_build_index(const pj_strings* S, int32_t tau_min, int32_t tau_max, const 
         idx->mem.budget = opt ? opt->mem_budget_bytes : 0;
         hip_check(hipGetDevice(&idx->device), "hipGetDevice");
         thread_workspace().begin_call(0);
-        build_set(S, on_dev, idx->mem, "I", idx->S, st);
+        build_set(S, on_dev, idx->mem, "I", idx->S, st, true);
         idx->X.resize((size_t)(tau_max - tau_min + 1));
         int64_t entries = 0;
         std::vector<IndexRef> refs(kTauMax + 1);

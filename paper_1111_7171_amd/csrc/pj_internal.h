@@ -66,6 +66,7 @@ struct DevSet {
     uint8_t* sarena = nullptr;          // padded, length-sorted bytes
     int32_t* perm = nullptr;            // [n] sorted position -> id
     uint16_t* slen = nullptr;           // [n] sorted position -> length
+    SymMap sym;                         // the set's symbol map (sets to be indexed)
     int32_t* lenstart = nullptr;        // [kLenTab + 1] first sorted position of each length
     int64_t* gbase = nullptr;           // [kLenTab] byte base of each length group
     // host copies of the per-length tables
@@ -210,9 +211,11 @@ hipError_t launch_iota_len_keys(const int32_t* offs, int64_t n, uint32_t* keys, 
                                 hipStream_t s);
 hipError_t launch_pack_arena(const uint8_t* bytes, const int32_t* offs, const int32_t* perm,
                              int64_t n, const int32_t* lenstart, const int64_t* gbase,
-                             uint8_t* sarena, uint16_t* slen, int lmax, hipStream_t s);
-// bytes present in a set's strings: bitmap (8 u32, zeroed by the caller)
-hipError_t launch_byte_presence(const DevSet& S, uint32_t* bitmap, hipStream_t s);
+                             uint8_t* sarena, uint16_t* slen, int lmax, uint32_t* bitmap,
+                             hipStream_t s);   // bitmap: 8 zeroed words for the bytes present, or null
+// stable sort of the ids by length (strings of at most 255 bytes; hist: strings per length)
+hipError_t launch_length_sort(const int32_t* offs, int64_t n, const int32_t* hist, int32_t* perm,
+                              void* tmp, size_t tmp_bytes, hipStream_t s);
 hipError_t launch_emit_segments(const DevSet& S, int tau, const int64_t* ebase_dev,
                                 int64_t g_first, int64_t g_count, const SymMap& sym,
                                 uint64_t* keys, uint32_t* vals, hipStream_t s);
