@@ -43,11 +43,26 @@ struct Workspace : Alloc {
     void release_all();
 };
 
-// Allocations owned by a long-lived object (an index); freed with it.
+// hipMalloc which, when memory runs out, first gives back the blocks kept for reuse
+hipError_t device_malloc(void** p, size_t bytes);
+
+// Allocations owned by a long-lived object (an index); freed with it.  Small ones share chunks, and
+// the blocks of one object serve the next: unmapping a block of some 20 MB takes 300-700 us.
 struct Owned : Alloc {
-    std::vector<void*> ptrs;
+    struct Block {
+        void* p = nullptr;
+        size_t cap = 0;
+        int device = 0;
+        uint64_t freed = 0;     // when it was given up (count of objects freed)
+    };
+    std::vector<Block> blocks;
+    void* chunk = nullptr;      // of the last chunk for small ones: the free part
+    size_t chunk_left = 0;
     ~Owned() override;
     void* get(const char* name, size_t bytes) override;
+
+private:
+    void* take(size_t bytes);
 };
 
 Workspace& thread_workspace();

@@ -330,7 +330,7 @@ int pj_query(const pj_index* idx, const pj_strings* Q, const int32_t* taus, cons
         out->on_device = to_dev ? 1 : 0;
         if (to_dev) {
             void *pa = nullptr, *pb = nullptr;
-            if (hipMalloc(&pa, bytes) != hipSuccess || hipMalloc(&pb, bytes) != hipSuccess) {
+            if (device_malloc(&pa, bytes) != hipSuccess || device_malloc(&pb, bytes) != hipSuccess) {
                 (void)hipGetLastError();
                 if (pa) (void)hipFree(pa);
                 throw Error(PJ_ENOMEM, "output allocation failed");

@@ -80,7 +80,6 @@ struct DevIndex {
     SymMap sym;
     int64_t entries = 0;                // (string, slot) entries
     int64_t lists = 0;                  // distinct keys (inverted lists)
-    uint64_t* keys = nullptr;           // [entries] sorted
     uint32_t* vals = nullptr;           // [entries] sorted position g of the string
     // the lists' records {key lo, key hi, start, count} in key order, closed by one of the
     // largest key; the directory into them: group g = key >> 40 owns the entries
