@@ -16,98 +16,6 @@
 
 namespace pj {
 
-// Wave-private append buffer in LDS: lanes push items without touching global atomics; the
-// wave reserves space in the global output with one atomic per flush (a single-address device
-// atomic is serialised across all XCDs, so one per item would throttle the kernel).  `buf`
-// is this wave's region of CAP items; `fill` is wave-uniform.
-template <typename T, int CAP>
-struct WaveAppender {
-    static_assert(CAP >= 64, "a push adds up to 64 items after at most one flush");
-    T* buf;
-    int fill;
-
-    __device__ inline void flush(T* out, uint64_t cap, unsigned long long* counter)
-    {
-        if (fill == 0) return;
-        const int lane = threadIdx.x & 63;
-        unsigned long long base = 0;
-        if (lane == 0) base = atomicAdd(counter, (unsigned long long)fill);
-        base = __shfl(base, 0, 64);
-        for (int k = lane; k < fill; k += 64)
-            if (base + (uint64_t)k < cap) out[base + k] = buf[k];
-        fill = 0;
-    }
-
-    __device__ inline void push(bool flag, const T& item, T* out, uint64_t cap,
-                                unsigned long long* counter)
-    {
-        const uint64_t m = __ballot(flag);
-        if (m == 0) return;
-        const int k = __popcll(m);
-        if (fill + k > CAP) flush(out, cap, counter);
-        if (flag) buf[fill + __popcll(m & lanemask_lt())] = item;
-        fill += k;
-    }
-};
-
-// a wave-uniform load through the scalar cache (read-only data)
-template <typename T>
-__device__ inline T uniform_load(const T* p)
-{
-    return *(const __attribute__((address_space(4))) T*)p;
-}
-
-constexpr int kAppendCap = 256;
-
-// End of a kernel: what the block's waves still hold, with one atomic for the block.  An atomic on
-// one address from every XCD takes about 6 ns whatever else runs, so a kernel of 8,192 waves that
-// ended with three of them each spent 150 us there; every thread of the block calls this.
-template <typename T, int CAP>
-__device__ inline void block_flush(WaveAppender<T, CAP>& app, T* out, uint64_t cap,
-                                   unsigned long long* counter)
-{
-    __shared__ uint32_t s_fill[kWaves];
-    __shared__ unsigned long long s_base;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0) s_fill[w] = (uint32_t)app.fill;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t total = 0;
-        for (int k = 0; k < kWaves; ++k) total += s_fill[k];
-        s_base = total ? atomicAdd(counter, (unsigned long long)total) : 0ull;
-    }
-    __syncthreads();
-    unsigned long long base = s_base;
-    for (int k = 0; k < w; ++k) base += s_fill[k];
-    for (int k = lane; k < app.fill; k += 64)
-        if (base + (uint64_t)k < cap) out[base + k] = app.buf[k];
-    app.fill = 0;
-    __syncthreads();
-}
-
-// The line of statistics the calling block adds to: one of kStatShards, so that blocks do not wait
-// for each other on one address (the host adds the lines up), or with shards == 0 (a captured
-// batch: few blocks) the counters themselves.
-__device__ inline unsigned long long* stat_line(unsigned long long* counters, int shards)
-{
-    return shards ? counters + kCounterLine * (1 + (int)(blockIdx.x % (unsigned)shards)) : counters;
-}
-
-// adds the block's sum of v to *counter; every thread of the block calls this
-__device__ inline void block_add(unsigned long long* counter, uint64_t v)
-{
-    __shared__ uint64_t s_sum[kWaves];
-    v = wave_sum(v);
-    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint64_t t = 0;
-        for (int k = 0; k < kWaves; ++k) t += s_sum[k];
-        if (t) atomicAdd(counter, (unsigned long long)t);
-    }
-    __syncthreads();
-}
-
 // ------------------------------------------------------------------------------------------
 // String arena: length histogram + validation, (length, id) keys, packing
 // ------------------------------------------------------------------------------------------
@@ -1403,12 +1311,8 @@ __device__ inline void vsp_lane_dispatch(bool yrows, LdsChars U, int lu, LdsLane
 #undef PJ_LANE
 }
 
-// The 40-byte class of the 5-wide band fits 8 blocks per CU in LDS; it is compiled for 8 waves
-// per SIMD (at most 64 VGPRs) to match.
 template <int GMAXW, int REGY, int NCT>
-__global__ __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu((REGY == 40 && GMAXW <= 5) ? 8 : 1)))
-void k_verify_segs(VerifyParams V, Div div,
+__global__ __launch_bounds__(kBlock) void k_verify_segs(VerifyParams V, Div div,
                                                         const Hit* __restrict__ big,
                                                         const uint32_t* __restrict__ segp,
                                                         uint64_t /* hits (unused) */,
@@ -2694,10 +2598,9 @@ static void verify_segs_wn(const VerifyParams& V, const Hit* big, const uint32_t
                            uint64_t nbig, uint64_t nseg, const uint32_t* first, uint64_t nchunks,
                            uint32_t chunk, int grid, unsigned long long* ticket, hipStream_t s)
 {
-    // one candidate per lane with strings of at most 40 bytes: 44-byte lane slots, so that 8
-    // blocks fit a CU's LDS
-    if (NC == 1 && W <= 9 && V.y_maxlen <= 40)
-        hipLaunchKernelGGL((k_verify_segs<W, (NC == 1 && W <= 9) ? 40 : 48, NC>), dim3(grid),
+    // one candidate per lane with strings of at most 40 bytes: 44-byte lane slots
+    if (NC == 1 && W == 9 && V.y_maxlen <= 40)
+        hipLaunchKernelGGL((k_verify_segs<W, (NC == 1 && W == 9) ? 40 : 48, NC>), dim3(grid),
                            dim3(kBlock), 0, s, V, make_div(V.tau + 1), big, segp, nbig, nseg,
                            first, nchunks, chunk, ticket);
     else if (V.y_maxlen <= 48)
@@ -2756,6 +2659,9 @@ hipError_t launch_verify_segs(const VerifyParams& V, const Hit* big, const uint3
                        nbig, nchunks, c, first);
     const int w = V.tau + 1;
     const int lc = lane_cands;
+    if (w <= 5 && lc == 1 && V.y_maxlen <= kAutoMaxLen)
+        return launch_verify_auto(V, big, segp, nseg, first, nchunks, c, (uint64_t)grid * kWaves,
+                                  ticket, s);
     if (w <= 5) verify_segs_w<5>(V, big, segp, nbig, nseg, first, nchunks, c, lc, grid, ticket, s);
     else if (w <= 9) verify_segs_w<9>(V, big, segp, nbig, nseg, first, nchunks, c, lc, grid, ticket, s);
     else if (w <= 17) verify_segs_w<17>(V, big, segp, nbig, nseg, first, nchunks, c, lc, grid, ticket, s);

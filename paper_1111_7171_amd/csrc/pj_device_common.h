@@ -60,6 +60,99 @@ __device__ inline T block_excl_scan(T v, T* s_wave, T* total)
 
 __device__ inline uint64_t lanemask_lt() { return (1ull << (threadIdx.x & 63)) - 1ull; }
 
+// Wave-private append buffer in LDS: lanes push items without touching global atomics; the
+// wave reserves space in the global output with one atomic per flush (a single-address device
+// atomic is serialised across all XCDs, so one per item would throttle the kernel).  `buf`
+// is this wave's region of CAP items; `fill` is wave-uniform.
+template <typename T, int CAP>
+struct WaveAppender {
+    static_assert(CAP >= 64, "a push adds up to 64 items after at most one flush");
+    T* buf;
+    int fill;
+
+    __device__ inline void flush(T* out, uint64_t cap, unsigned long long* counter)
+    {
+        if (fill == 0) return;
+        const int lane = threadIdx.x & 63;
+        unsigned long long base = 0;
+        if (lane == 0) base = atomicAdd(counter, (unsigned long long)fill);
+        base = __shfl(base, 0, 64);
+        for (int k = lane; k < fill; k += 64)
+            if (base + (uint64_t)k < cap) out[base + k] = buf[k];
+        fill = 0;
+    }
+
+    __device__ inline void push(bool flag, const T& item, T* out, uint64_t cap,
+                                unsigned long long* counter)
+    {
+        const uint64_t m = __ballot(flag);
+        if (m == 0) return;
+        const int k = __popcll(m);
+        if (fill + k > CAP) flush(out, cap, counter);
+        if (flag) buf[fill + __popcll(m & lanemask_lt())] = item;
+        fill += k;
+    }
+};
+
+// a wave-uniform load through the scalar cache (read-only data)
+template <typename T>
+__device__ inline T uniform_load(const T* p)
+{
+    return *(const __attribute__((address_space(4))) T*)p;
+}
+
+constexpr int kAppendCap = 256;
+
+// End of a kernel: what the block's waves still hold, with one atomic for the block.  An atomic on
+// one address from every XCD takes about 6 ns whatever else runs, so a kernel of 8,192 waves that
+// ended with three of them each spent 150 us there; every thread of the block calls this.
+template <int NW = kWaves, typename T, int CAP>
+__device__ inline void block_flush(WaveAppender<T, CAP>& app, T* out, uint64_t cap,
+                                   unsigned long long* counter)
+{
+    __shared__ uint32_t s_fill[NW];
+    __shared__ unsigned long long s_base;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (lane == 0) s_fill[w] = (uint32_t)app.fill;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t total = 0;
+        for (int k = 0; k < NW; ++k) total += s_fill[k];
+        s_base = total ? atomicAdd(counter, (unsigned long long)total) : 0ull;
+    }
+    __syncthreads();
+    unsigned long long base = s_base;
+    for (int k = 0; k < w; ++k) base += s_fill[k];
+    for (int k = lane; k < app.fill; k += 64)
+        if (base + (uint64_t)k < cap) out[base + k] = app.buf[k];
+    app.fill = 0;
+    __syncthreads();
+}
+
+// The line of statistics the calling block adds to: one of kStatShards, so that blocks do not wait
+// for each other on one address (the host adds the lines up), or with shards == 0 (a captured
+// batch: few blocks) the counters themselves.
+__device__ inline unsigned long long* stat_line(unsigned long long* counters, int shards)
+{
+    return shards ? counters + kCounterLine * (1 + (int)(blockIdx.x % (unsigned)shards)) : counters;
+}
+
+// adds the block's sum of v to *counter; every thread of the block calls this
+template <int NW = kWaves>
+__device__ inline void block_add(unsigned long long* counter, uint64_t v)
+{
+    __shared__ uint64_t s_sum[NW];
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint64_t t = 0;
+        for (int k = 0; k < NW; ++k) t += s_sum[k];
+        if (t) atomicAdd(counter, (unsigned long long)t);
+    }
+    __syncthreads();
+}
+
 // Bitonic sort of N keys (a power of two, at least 64) in LDS by a block of T threads.  A thread
 // takes pair p of a step, so the pairs of a step of stride at most 64 stay inside the 128 keys
 // that the wave's pairs cover: between such steps the wave needs no block barrier.

@@ -699,9 +699,11 @@ void build_index(const DevSet& D, int tau, Alloc& A, const std::string& tag, Dev
             inl_base[l] = bytes - ebase[l] * stride_of(l);
             bytes += (int64_t)(D.h_lenstart[l + 1] - D.h_lenstart[l]) * T1 * stride_of(l);
         }
-        const size_t need = (size_t)bytes + sizeof(int64_t) * kLenTab;
+        auto held = [](size_t b) { return (b + 255) & ~(size_t)255; };
+        const size_t need = held((size_t)bytes + 64) + held(sizeof(int64_t) * kLenTab);
         if (A.budget == 0 || (long long)(A.used + need) <= A.budget) {
-            X.inl = (uint8_t*)A.get(nm("inl").c_str(), (size_t)std::max<int64_t>(bytes, 16));
+            // (64 bytes more: a part's characters are read 16 at a time from any position)
+            X.inl = (uint8_t*)A.get(nm("inl").c_str(), (size_t)bytes + 64);
             X.inl_base = (int64_t*)A.get(nm("inl_base").c_str(), sizeof(int64_t) * kLenTab);
             upload(X.inl_base, inl_base.data(), sizeof(int64_t) * kLenTab, st);
             hip_check(launch_gather_inline(D, keys, vals, E, tau, X.inl_base, X.inl, st),

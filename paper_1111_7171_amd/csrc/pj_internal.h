@@ -263,6 +263,12 @@ hipError_t launch_slot_bucket(const Hit* hits, const unsigned long long* nh_dev,
 int seg_members(int y_maxlen, int tau, int lane_cands);
 hipError_t launch_seg_counts(const Hit* big, uint64_t nbig, int members, uint32_t* segs,
                              hipStream_t s);
+// the same through the parts' automata: tau <= 4, one candidate per lane, strings of up to kAutoMaxLen
+constexpr int kAutoMaxLen = 47;
+hipError_t launch_verify_auto(const VerifyParams& V, const Hit* big, const uint32_t* segp,
+                              uint64_t nseg, const uint32_t* first, uint64_t nchunks,
+                              uint32_t chunk, uint64_t waves, unsigned long long* ticket,
+                              hipStream_t s);
 hipError_t launch_verify_segs(const VerifyParams& V, const Hit* big, const uint32_t* segp,
                               uint64_t nbig, uint64_t nseg, uint32_t* first, int chunk,
                               int lane_cands, int grid, unsigned long long* ticket,
