@@ -112,6 +112,25 @@ struct AutoFor {
     static constexpr int bytes = states.n << (shape.mb() + 1);
 };
 
+// Cells of the band of Lemma 4 in the first s rows of a part of nr rows and nr + delta columns.
+template <int T, int DELTA>
+struct AutoCells {
+    static constexpr int kMost = 48;             // rows 0 .. 47
+    uint16_t cells[kMost][kMost] = {};           // [nr][s]
+    constexpr AutoCells()
+    {
+        const int a = (T - DELTA) >> 1, b = (T + DELTA) >> 1;
+        for (int nr = 0; nr < kMost; ++nr) {
+            int sum = 0;
+            for (int s = 1; s <= nr; ++s) {
+                const int lo = s - a < 1 ? 1 : s - a, hi = s + b > nr + DELTA ? nr + DELTA : s + b;
+                sum += hi - lo + 1;
+                cells[nr][s] = (uint16_t)sum;
+            }
+        }
+    }
+};
+
 // What a kernel needs to run a shape: 16 bytes, read as one.
 struct alignas(16) AutoGeom {
     uint16_t init[kAutoWidth + 1];   // entry of row 0 with 0, 1, .. positions
@@ -143,8 +162,11 @@ struct AutoTable {
     }
     static constexpr int kBytes = (bytes_through<TMAX, TMAX, 1>() + 15) / 16 * 16;
 
+    static constexpr int kCellRows = 48;
+
     alignas(16) uint16_t next[kBytes / 2];
     AutoGeom geom[kShapes];
+    uint16_t cells[kShapes / 2 * kCellRows * kCellRows];   // [t][delta][nr][s]
 
     template <int T, int DELTA, int COLUMNS>
     constexpr void fill()
@@ -165,6 +187,11 @@ struct AutoTable {
         g.dead = entry(0);
         g.a = (uint8_t)F::shape.a();
         g.fields = (uint8_t)(mb | fb << 4);
+        if (COLUMNS) return;
+        constexpr AutoCells<T, DELTA> c;
+        uint16_t* out = cells + index(T, DELTA, 0) / 2 * kCellRows * kCellRows;
+        for (int nr = 0; nr < kCellRows; ++nr)
+            for (int k = 0; k < kCellRows; ++k) out[nr * kCellRows + k] = c.cells[nr][k];
     }
     template <int T, int DELTA>
     constexpr void fill_from()
@@ -174,7 +201,7 @@ struct AutoTable {
         if constexpr (DELTA > 0) fill_from<T, DELTA - 1>();
         else if constexpr (T > 0) fill_from<T - 1, T - 1>();
     }
-    constexpr AutoTable() : next{}, geom{} { fill_from<TMAX, TMAX>(); }
+    constexpr AutoTable() : next{}, geom{}, cells{} { fill_from<TMAX, TMAX>(); }
 };
 
 }  // namespace pj

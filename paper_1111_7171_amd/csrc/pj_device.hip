@@ -1367,6 +1367,7 @@ __global__ __launch_bounds__(kBlock) void k_verify_segs(VerifyParams V, Div div,
     uint64_t my_cells = 0, my_miss = 0;
     // a wave's first chunk is its own, the others are taken as waves come free: lists differ in
     // work far more than chunks do in number
+    uint32_t tried = 0;
     uint64_t ch = wave;
     while (ch < nchunks) {
         uint64_t sg_i = ch * seg_chunk;
@@ -1605,11 +1606,7 @@ __global__ __launch_bounds__(kBlock) void k_verify_segs(VerifyParams V, Div div,
             ++h;
             sidx = 0;
         }
-        if (!ticket) break;                        // a chunk for every wave
-        unsigned long long t = 0;
-        if (lane == 0) t = atomicAdd(ticket, 1ull);
-        ch = nwaves + ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)t) |
-                       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(t >> 32)) << 32);
+        ch = next_chunk(ticket, tried, nwaves, nchunks);
     }
     block_flush(acc, V.out, V.out_cap, &V.counters[3]);
     unsigned long long* line = stat_line(V.counters, V.shards);
@@ -2660,7 +2657,7 @@ hipError_t launch_verify_segs(const VerifyParams& V, const Hit* big, const uint3
     const int w = V.tau + 1;
     const int lc = lane_cands;
     if (w <= 5 && lc == 1 && V.y_maxlen <= kAutoMaxLen)
-        return launch_verify_auto(V, big, segp, nseg, first, nchunks, c, (uint64_t)grid * kWaves,
+        return launch_verify_auto(V, big, nbig, segp, nseg, first, nchunks, c, (uint64_t)grid * kWaves,
                                   ticket, s);
     if (w <= 5) verify_segs_w<5>(V, big, segp, nbig, nseg, first, nchunks, c, lc, grid, ticket, s);
     else if (w <= 9) verify_segs_w<9>(V, big, segp, nbig, nseg, first, nchunks, c, lc, grid, ticket, s);

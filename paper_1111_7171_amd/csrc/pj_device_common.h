@@ -137,6 +137,34 @@ __device__ inline unsigned long long* stat_line(unsigned long long* counters, in
     return shards ? counters + kCounterLine * (1 + (int)(blockIdx.x % (unsigned)shards)) : counters;
 }
 
+// Chunks of the list kernels beyond a wave's first.  Tickets lie in kTicketLines counters, a line
+// apart: counter x gives out the chunks nwaves + x, nwaves + x + kTicketLines, ... .  A wave asks
+// its XCD's counter until that has no chunk left, then the others' in turn.  An atomic on one
+// address takes 6-10 ns whoever asks, so with a single counter 70,000 chunks (10^6 short strings at
+// tau = 2) took 0.5 ms however fast their waves were.
+// tried: counters found empty so far (0 at the start, the wave's).  Returns the next chunk, nchunks or
+// more when there is none.
+__device__ inline uint64_t next_chunk(unsigned long long* tickets, uint32_t& tried, uint64_t nwaves,
+                                      uint64_t nchunks)
+{
+    uint64_t c = nchunks;
+    if (tickets && (threadIdx.x & 63) == 0) {    // (no tickets: a chunk for every wave)
+        for (; tried < kTicketLines; ++tried) {
+            const uint32_t line = (blockIdx.x + tried) % kTicketLines;
+            unsigned long long* counter = tickets + (uint64_t)line * kCounterLine;
+            unsigned long long t = 0;
+            // (waves that look for the last chunks mostly find counters that are through)
+            if (tried) t = __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            c = nwaves + t * kTicketLines + line;
+            if (c < nchunks) c = nwaves + atomicAdd(counter, 1ull) * kTicketLines + line;
+            if (c < nchunks) break;
+        }
+    }
+    // lane 0's, known to be wave-uniform
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)c) |
+           (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(c >> 32)) << 32;
+}
+
 // adds the block's sum of v to *counter; every thread of the block calls this
 template <int NW = kWaves>
 __device__ inline void block_add(unsigned long long* counter, uint64_t v)

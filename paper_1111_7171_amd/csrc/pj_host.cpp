@@ -32,13 +32,12 @@ constexpr size_t kPinnedOutputMin = 1u << 20;
 // Below this many candidates the batched path verifies the hits in probe order, in one launch.
 constexpr uint64_t kBucketMinCandidates = 1ull << 20;
 
-// List segments per wave chunk without a tuned setting.  A chunk sets a hit up anew where it begins
-// inside one, and its ticket is an atomic on one address (some 10 ns each, one after another):
-// up to 32 segments a chunk, all of them are handed out at the start, a chunk per wave of a full
-// chip; beyond, waves take more by ticket, and long runs take longer chunks.  Measured on short
-// strings, list kernel, with 4 / 8 / 32 / 128 segments: 10^6 at tau = 1 0.06, 0.04, 0.09, 0.30 ms;
-// 10^5 at tau = 3 0.52, 0.28, 0.16, 0.39; 2x10^5 at tau = 4 18.5, 9.3, 2.6, 2.7; 10^6 at tau = 4 with
-// 32 / 128 / 256: 50, 48.7, 47.5.
+// List segments per wave chunk without a tuned setting.  A chunk sets its hits up anew, and its ticket
+// is an atomic on one of eight addresses (6-10 ns each, one after another): up to 32 segments a
+// chunk, all of them are handed out at the start, a chunk per wave of a full chip; beyond, waves take
+// more by ticket, and long runs take longer chunks.  Measured on short strings, list kernel, with 4 /
+// 8 / 32 / 128 segments: 10^6 at tau = 1 0.02, 0.03, 0.07, 0.19 ms; 10^5 at tau = 3 0.16, 0.13, 0.11,
+// 0.27; 2x10^5 at tau = 4 3.5, 1.9, 1.4, 1.4; 10^6 at tau = 4 with 32 / 128 / 256: 28.5, 25.8, 25.3.
 static int auto_seg_chunk(uint64_t nseg)
 {
     const uint64_t even = std::max<uint64_t>(4, std::min<uint64_t>((nseg + 8191) / 8192, 32));
@@ -1174,7 +1173,8 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
                     hip_check(launch_verify_segs(vc, bigp + o, segp + o + c, nb, nseg, first2,
                                                  chunk_c[c], J.tp.lane_cands,
                                                  (int)((waves + 3) / 4),
-                                                 waves < nchunks ? J.counters + kTicketWord + c
+                                                 waves < nchunks ? J.counters + kCounterLine +
+                                                                       kTicketWord + c
                                                                  : nullptr, st),
                               "verify_segs");
                     const int s1 = tm.mark();

@@ -196,11 +196,12 @@ struct VerifyParams {
     int self;
 };
 // Join counters: a line of kCounterLine words ([0] hits, [3] accepted: positions that blocks
-// reserve; [10 + c] the chunk ticket of length class c's list kernel), then kStatShards lines of
-// statistics in the same places, which the host adds up.  [8] rows and [9] cells that shared-prefix
-// verification took from an earlier member's DP instead of computing them.
+// reserve), then kStatShards lines of statistics in the same places, which the host adds up.  Words
+// 10 + c of the first kTicketLines of these are the chunk tickets of length class c's list kernel.
+// [8] rows and [9] cells that shared-prefix verification took from an earlier member's DP instead
+// of computing them.
 constexpr int kCounterLine = 16, kStatShards = 32;
-constexpr int kTicketWord = 10;
+constexpr int kTicketWord = 10, kTicketLines = 8;
 constexpr int kJoinCounters = kCounterLine * (1 + kStatShards);
 
 // ---- launchers (pj_device.hip) ----
@@ -257,16 +258,16 @@ hipError_t launch_slot_bucket(const Hit* hits, const unsigned long long* nh_dev,
                               size_t scan_bytes, Hit* out, hipStream_t s);
 // list-segment verification of the lists with >= big candidates (hits big[0 .. nbig), segp =
 // exclusive scan of ceil(count / seg_members), nseg segments, `chunk` segments per wave chunk; first:
-// seg_chunks(nseg, chunk) u32 of scratch; ticket: a zeroed word, or nullptr when the grid has a wave
-// for every chunk)
+// seg_chunks(nseg, chunk) u32 of scratch; ticket: the zeroed word of the first of kTicketLines counter
+// lines, or nullptr when the grid has a wave for every chunk)
 // list segments of `members` candidates each (seg_members: what k_verify_segs expects)
 int seg_members(int y_maxlen, int tau, int lane_cands);
 hipError_t launch_seg_counts(const Hit* big, uint64_t nbig, int members, uint32_t* segs,
                              hipStream_t s);
 // the same through the parts' automata: tau <= 4, one candidate per lane, strings of up to kAutoMaxLen
 constexpr int kAutoMaxLen = 47;
-hipError_t launch_verify_auto(const VerifyParams& V, const Hit* big, const uint32_t* segp,
-                              uint64_t nseg, const uint32_t* first, uint64_t nchunks,
+hipError_t launch_verify_auto(const VerifyParams& V, const Hit* big, uint64_t nbig,
+                              const uint32_t* segp, uint64_t nseg, const uint32_t* first, uint64_t nchunks,
                               uint32_t chunk, uint64_t waves, unsigned long long* ticket,
                               hipStream_t s);
 hipError_t launch_verify_segs(const VerifyParams& V, const Hit* big, const uint32_t* segp,
