@@ -23,8 +23,7 @@ namespace pj {
 // Few blocks: each adds its counts to the shared ones, an atomic per length present (10^6 short
 // strings: 46 us with a block per 256 strings, 9 us so)
 __global__ __launch_bounds__(kBlock) void k_length_hist(const int32_t* __restrict__ offs,
-                                                        int64_t n, int32_t* __restrict__ lcount,
-                                                        int32_t* __restrict__ err)
+                                                        int64_t n, int32_t* __restrict__ lcount)
 {
     __shared__ int32_t h[kLenTab];
     for (int k = threadIdx.x; k < kLenTab; k += kBlock) h[k] = 0;
@@ -40,10 +39,47 @@ __global__ __launch_bounds__(kBlock) void k_length_hist(const int32_t* __restric
         else if (l > kLenMax) e |= 4;
         else atomicAdd(&h[l], 1);
     }
-    if (e) atomicOr(err, e);
+    if (e) atomicOr(&lcount[kLenTab], e);
     __syncthreads();
     for (int k = threadIdx.x; k < kLenTab; k += kBlock)
         if (h[k]) atomicAdd(&lcount[k], h[k]);
+}
+
+// One block: the tables by length from the counts, strings and arena bytes before each length.
+// (Uploads of host-made tables took the host 10-20 us each, with the device waiting; made by the last
+// block of k_length_hist they cost that kernel 19 us for its fences.)  It also clears what the packing
+// and the index fill in: the bitmap of bytes present and the codes.
+__global__ __launch_bounds__(kBlock) void k_length_tables(const int32_t* __restrict__ lcount,
+                                                          int32_t* __restrict__ lenstart,
+                                                          int64_t* __restrict__ gbase,
+                                                          uint32_t* __restrict__ bitmap,
+                                                          uint16_t* __restrict__ code)
+{
+    __shared__ uint64_t s_wave[kWaves];
+    if (bitmap) {
+        if (threadIdx.x < 8) bitmap[threadIdx.x] = 0;
+        code[threadIdx.x] = 0;
+    }
+    constexpr int kEach = (kLenTab + kBlock - 1) / kBlock;
+    const int l0 = threadIdx.x * kEach;
+    uint64_t strings = 0, bytes = 0, total;
+    int32_t c[kEach];
+#pragma unroll
+    for (int k = 0; k < kEach; ++k) {
+        c[k] = l0 + k < kLenTab ? lcount[l0 + k] : 0;
+        strings += (uint64_t)c[k];
+        bytes += (uint64_t)c[k] * (uint64_t)stride_of(l0 + k);
+    }
+    strings = block_excl_scan(strings, s_wave, &total);
+    bytes = block_excl_scan(bytes, s_wave, &total);
+#pragma unroll
+    for (int k = 0; k < kEach; ++k) {
+        if (l0 + k > kLenTab) break;
+        lenstart[l0 + k] = (int32_t)strings;
+        if (l0 + k < kLenTab) gbase[l0 + k] = (int64_t)bytes;
+        strings += (uint64_t)c[k];
+        bytes += (uint64_t)c[k] * (uint64_t)stride_of(l0 + k);
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void k_len_keys(const int32_t* __restrict__ offs, int64_t n,
@@ -128,33 +164,55 @@ __global__ __launch_bounds__(kBlock) void k_pack_arena(const uint8_t* __restrict
 // Segment index
 // ------------------------------------------------------------------------------------------
 
-// One thread per (indexed string, slot): emits (key, g) at a position grouped by (l, i) and
-// ordered by g inside the group, so a stable sort by key keeps lists in ascending g.
+// One thread per (indexed string, slot), a string's slots together: emits (key, g) at a position
+// grouped by (l, i) and ordered by g inside the group, so a stable sort by key keeps lists in
+// ascending g.  Every block makes the symbol map from the bitmap of bytes present (bits and longest
+// exact segment included, so the host need not wait for them here); the first writes it to `code`,
+// and, with inl_base, where each length's inline copies begin.
 __global__ __launch_bounds__(kBlock) void k_emit_segments(const uint8_t* __restrict__ sarena,
                                                           const uint16_t* __restrict__ slen,
                                                           const int32_t* __restrict__ lenstart,
                                                           const int64_t* __restrict__ gbase,
-                                                          const int64_t* __restrict__ ebase,
                                                           int tau, int64_t g_first,
-                                                          int64_t g_count, Div div, SymMap sym,
+                                                          int64_t g_count, Div div,
+                                                          const uint32_t* __restrict__ bitmap,
+                                                          uint16_t* __restrict__ code,
+                                                          int64_t* __restrict__ inl_base,
                                                           uint64_t* __restrict__ keys,
                                                           uint32_t* __restrict__ vals)
 {
     __shared__ uint16_t s_sym[256];
-    s_sym[threadIdx.x] = sym.code[threadIdx.x];
-    __syncthreads();
     const int T1 = tau + 1;
-    int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (t >= g_count * T1) return;
-    int64_t g = g_first + t / T1;
-    int i = (int)(t % T1) + 1;
-    int l = slen[g];
-    Seg sg = partition_seg(l, i, tau, div);
-    const uint8_t* s = sarena + gbase[l] + (g - lenstart[l]) * stride_of(l);
-    uint64_t h = seg_code(s + sg.p - 1, sg.len, s_sym, sym.bits, sym.exact_len);
-    int64_t nl = lenstart[l + 1] - lenstart[l];
-    int64_t e = ebase[l] + (int64_t)(i - 1) * nl + (g - lenstart[l]);
-    keys[e] = make_key(l, i, tau, sg.len, h, sym.exact_len);
+    uint32_t sigma = 0, rank = 0;
+    for (int k = 0; k < 8; ++k) {
+        const uint32_t word = bitmap[k];
+        if (k == (int)(threadIdx.x >> 5))
+            rank = (word >> (threadIdx.x & 31)) & 1u
+                       ? sigma + (uint32_t)__popc(word & ((2u << (threadIdx.x & 31)) - 1u)) : 0u;
+        sigma += (uint32_t)__popc(word);
+    }
+    s_sym[threadIdx.x] = (uint16_t)rank;
+    const int bits = sigma < 2 ? 1 : 32 - __clz((int)sigma), exact_len = kHashBits / bits;
+    if (blockIdx.x == 0) {
+        code[threadIdx.x] = (uint16_t)rank;
+        if (inl_base)
+            for (int l = threadIdx.x; l < kLenTab; l += kBlock)
+                inl_base[l] = l < T1 ? 0 : (gbase[l] - gbase[T1]) * T1 -
+                                               (int64_t)(lenstart[l] - lenstart[T1]) * T1 * stride_of(l);
+    }
+    __syncthreads();
+    const uint64_t t = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (t >= (uint64_t)g_count * (uint32_t)T1) return;       // (fewer than 2^32 entries)
+    const uint32_t at = (uint32_t)t / (uint32_t)T1;
+    const int64_t g = g_first + at;
+    const int i = (int)((uint32_t)t - at * (uint32_t)T1) + 1;
+    const int l = slen[g];
+    const Seg sg = partition_seg(l, i, tau, div);
+    const int64_t ls = lenstart[l], nl = lenstart[l + 1] - ls;
+    const uint8_t* s = sarena + gbase[l] + (g - ls) * stride_of(l);
+    const uint64_t h = seg_code(s + sg.p - 1, sg.len, s_sym, bits, exact_len);
+    const int64_t e = (ls - g_first) * T1 + (int64_t)(i - 1) * nl + (g - ls);
+    keys[e] = make_key(l, i, tau, sg.len, h, exact_len);
     vals[e] = (uint32_t)g;
 }
 
@@ -171,7 +229,7 @@ __global__ __launch_bounds__(kBlock) void k_gather_inline(
     const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (j >= E) return;
     const int T1 = tau + 1;
-    const int l = (int)((keys[j] >> kHashBits) / (uint64_t)T1) + T1;
+    const int l = (int)((uint32_t)(keys[j] >> kHashBits) / (uint32_t)T1) + T1;
     const uint32_t g = vals[j];
     const int64_t st = stride_of(l);
     const uint4* src = reinterpret_cast<const uint4*>(sarena + gbase[l] +
@@ -2316,12 +2374,17 @@ __global__ __launch_bounds__(kBlock) void k_gather_i32(const int32_t* __restrict
 
 static inline unsigned blocks_for(uint64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
-hipError_t launch_length_hist(const int32_t* offs, int64_t n, int32_t* lcount, int32_t* err,
-                              hipStream_t s)
+hipError_t launch_length_hist(const int32_t* offs, int64_t n, int32_t* lcount, int32_t* lenstart,
+                              int64_t* gbase, uint32_t* bitmap, uint16_t* code, hipStream_t s)
 {
-    if (n <= 0) return hipSuccess;
-    const unsigned grid = (unsigned)std::min<uint64_t>(blocks_for((uint64_t)n), 256);
-    hipLaunchKernelGGL(k_length_hist, dim3(grid), dim3(kBlock), 0, s, offs, n, lcount, err);
+    if ((bitmap == nullptr) != (code == nullptr)) return hipErrorInvalidValue;
+    // a block also for no strings: the tables are always written
+    const unsigned grid =
+        (unsigned)std::min<uint64_t>(((uint64_t)n + kBlock - 1) / kBlock, 256);
+    if (grid > 0)
+        hipLaunchKernelGGL(k_length_hist, dim3(grid), dim3(kBlock), 0, s, offs, n, lcount);
+    hipLaunchKernelGGL(k_length_tables, dim3(1), dim3(kBlock), 0, s, lcount, lenstart, gbase, bitmap,
+                       code);
     return hipGetLastError();
 }
 
@@ -2349,17 +2412,14 @@ hipError_t launch_pack_arena(const uint8_t* bytes, const int32_t* offs, const in
     return hipGetLastError();
 }
 
-hipError_t launch_emit_segments(const DevSet& S, int tau, const int64_t* ebase_dev,
-                                int64_t g_first, int64_t g_count, const SymMap& sym,
-                                uint64_t* keys, uint32_t* vals, hipStream_t s)
+hipError_t launch_emit_segments(const DevSet& S, int tau, int64_t g_first, int64_t g_count,
+                                int64_t* inl_base, uint64_t* keys, uint32_t* vals, hipStream_t s)
 {
     if (g_count <= 0) return hipSuccess;
-    if (!sym.code || sym.bits < 1 || sym.bits > 9 || sym.exact_len * sym.bits > kHashBits)
-        return hipErrorInvalidValue;
-    uint64_t threads = (uint64_t)g_count * (tau + 1);
-    hipLaunchKernelGGL(k_emit_segments, dim3(blocks_for(threads)), dim3(kBlock), 0, s, S.sarena,
-                       S.slen, S.lenstart, S.gbase, ebase_dev, tau, g_first, g_count,
-                       make_div(tau + 1), sym, keys, vals);
+    if (!S.bitmap || !S.code) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_emit_segments, dim3(blocks_for((uint64_t)g_count * (uint64_t)(tau + 1))),
+                       dim3(kBlock), 0, s, S.sarena, S.slen, S.lenstart, S.gbase, tau, g_first,
+                       g_count, make_div(tau + 1), S.bitmap, S.code, inl_base, keys, vals);
     return hipGetLastError();
 }
 

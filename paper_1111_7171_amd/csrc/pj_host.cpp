@@ -547,11 +547,18 @@ void build_set(const pj_strings* S, bool on_device, Alloc& A, const std::string&
         d_bytes = bb;
     }
 
-    // length histogram (+ validation of device inputs)
-    int32_t* lcount =
-        (int32_t*)thread_workspace().get(nm("lcount").c_str(), sizeof(int32_t) * (kLenTab + 1));
+    // length histogram (+ validation of device inputs) and the tables by length
+    Workspace& W = thread_workspace();
+    D.lenstart = (int32_t*)A.get(nm("lenstart").c_str(), sizeof(int32_t) * (kLenTab + 1));
+    D.gbase = (int64_t*)A.get(nm("gbase").c_str(), sizeof(int64_t) * kLenTab);
+    if (with_sym) {
+        D.bitmap = (uint32_t*)W.get("set.bytemap", 8 * sizeof(uint32_t));
+        D.code = (uint16_t*)A.get(nm("sym").c_str(), 256 * sizeof(uint16_t));
+    }
+    int32_t* lcount = (int32_t*)W.get(nm("lcount").c_str(), sizeof(int32_t) * (kLenTab + 1));
     zero_words(lcount, sizeof(int32_t) * (kLenTab + 1), st);
-    hip_check(launch_length_hist(d_offs, n, lcount, lcount + kLenTab, st), "length_hist");
+    hip_check(launch_length_hist(d_offs, n, lcount, D.lenstart, D.gbase, D.bitmap, D.code, st),
+              "length_hist");
     std::vector<int32_t> h(kLenTab + 1);
     int32_t dev_total = 0;
     readback(h.data(), lcount, sizeof(int32_t) * (kLenTab + 1), st);
@@ -587,20 +594,9 @@ void build_set(const pj_strings* S, bool on_device, Alloc& A, const std::string&
     if (D.lmax < 0) D.lmin = 0;
     D.arena_bytes = bytes;
 
-    D.lenstart = (int32_t*)A.get(nm("lenstart").c_str(), sizeof(int32_t) * (kLenTab + 1));
-    D.gbase = (int64_t*)A.get(nm("gbase").c_str(), sizeof(int64_t) * kLenTab);
-    upload(D.lenstart, D.h_lenstart, sizeof(int32_t) * (kLenTab + 1), st);
-    upload(D.gbase, D.h_gbase, sizeof(int64_t) * kLenTab, st);
-
     D.perm = (int32_t*)A.get(nm("perm").c_str(), sizeof(int32_t) * (size_t)std::max<int64_t>(n, 1));
     D.slen = (uint16_t*)A.get(nm("slen").c_str(), sizeof(uint16_t) * (size_t)std::max<int64_t>(n, 1));
     D.sarena = (uint8_t*)A.get(nm("sarena").c_str(), (size_t)bytes + 64);
-    Workspace& W = thread_workspace();
-    uint32_t* bitmap = nullptr;
-    if (with_sym) {
-        bitmap = (uint32_t*)W.get("set.bytemap", 8 * sizeof(uint32_t));
-        zero_words(bitmap, 8 * sizeof(uint32_t), st);
-    }
     if (n > 0) {
         // stable sort of ids by length -> perm
         size_t tb = radix_tmp_bytes((uint64_t)n);
@@ -618,22 +614,7 @@ void build_set(const pj_strings* S, bool on_device, Alloc& A, const std::string&
                                      st), "radix(len)");
         }
         hip_check(launch_pack_arena(d_bytes, d_offs, D.perm, n, D.lenstart, D.gbase, D.sarena,
-                                    D.slen, D.lmax, bitmap, st), "pack_arena");
-    }
-    if (with_sym) {
-        // symbol map of the bytes the set contains: codes 1..sigma, 0 for absent bytes
-        uint32_t hb[8];
-        readback(hb, bitmap, sizeof hb, st);
-        sync_readback(st);
-        uint16_t code[256];
-        int sigma = 0;
-        for (int b = 0; b < 256; ++b)
-            code[b] = (hb[b >> 5] >> (b & 31)) & 1u ? (uint16_t)(++sigma) : (uint16_t)0;
-        const int sbits = std::max(1, bitlen((uint64_t)sigma));
-        uint16_t* dcode = (uint16_t*)A.get(nm("sym").c_str(), sizeof code);
-        upload(dcode, code, sizeof code, st);
-        sync_readback(st);                  // code[] is on this stack frame
-        D.sym = SymMap{dcode, sbits, kHashBits / sbits};
+                                    D.slen, D.lmax, D.bitmap, st), "pack_arena");
     }
 }
 
@@ -653,7 +634,7 @@ void build_index(const DevSet& D, int tau, Alloc& A, const std::string& tag, Dev
     int64_t E = g_count * T1;
     if (E >= (int64_t)UINT32_MAX) throw Error(PJ_ERANGE, "index too large (%lld entries)", (long long)E);
     X.entries = E;
-    X.sym = D.sym;
+    X.sym = SymMap{D.code, 1, kHashBits};
     if (E == 0) {
         X.vals = (uint32_t*)A.get(nm("vals").c_str(), 16);
         // no list and no group: nothing reads the directory
@@ -663,15 +644,7 @@ void build_index(const DevSet& D, int tau, Alloc& A, const std::string& tag, Dev
         X.lists = 0;
         return;
     }
-    std::vector<int64_t> ebase(kLenTab, 0);
-    int64_t run = 0;
-    for (int l = 0; l < kLenTab; ++l) {
-        ebase[l] = run;
-        if (l >= T1) run += (int64_t)(D.h_lenstart[l + 1] - D.h_lenstart[l]) * T1;
-    }
     Workspace& W = thread_workspace();
-    int64_t* d_ebase = (int64_t*)W.get("index.ebase", sizeof(int64_t) * kLenTab);
-    upload(d_ebase, ebase.data(), sizeof(int64_t) * kLenTab, st);
     uint64_t* keys = (uint64_t*)W.get("index.keys", sizeof(uint64_t) * (size_t)E);
     uint32_t* vals = (uint32_t*)A.get(nm("vals").c_str(), sizeof(uint32_t) * (size_t)E);
     uint64_t* keys2 = (uint64_t*)W.get("index.keys2", sizeof(uint64_t) * (size_t)E);
@@ -682,33 +655,28 @@ void build_index(const DevSet& D, int tau, Alloc& A, const std::string& tag, Dev
     const bool odd = radix_passes(bits) & 1;
     uint64_t *ka = odd ? keys2 : keys, *kb = odd ? keys : keys2;
     uint32_t *va = odd ? vals2 : vals, *vb = odd ? vals : vals2;
-    hip_check(launch_emit_segments(D, tau, d_ebase, g_first, g_count, X.sym, ka, va, st), "emit");
-    size_t tb = radix_tmp_bytes((uint64_t)E);
+    const size_t tb = radix_tmp_bytes((uint64_t)E);
     void* tmp = W.get("radix.tmp", tb);
-    bool alt = false;
-    hip_check(radix_sort_u64(ka, va, kb, vb, (uint64_t)E, bits, tmp, tb, &alt, st),
-              "radix(index)");
-    X.vals = vals;
     // inline copies of the members' strings (short strings only, and only within the budget):
     // the list-segment kernel then reads a list's strings contiguously
-    std::vector<int64_t> inl_base(kLenTab, 0);
     if (with_inline && D.lmax <= kInlineMaxLen) {
-        int64_t bytes = 0;
-        for (int l = T1; l < kLenTab; ++l) {
-            inl_base[l] = bytes - ebase[l] * stride_of(l);
-            bytes += (int64_t)(D.h_lenstart[l + 1] - D.h_lenstart[l]) * T1 * stride_of(l);
-        }
+        const int64_t bytes = (D.arena_bytes - D.h_gbase[T1]) * T1;
         auto held = [](size_t b) { return (b + 255) & ~(size_t)255; };
         const size_t need = held((size_t)bytes + 64) + held(sizeof(int64_t) * kLenTab);
         if (A.budget == 0 || (long long)(A.used + need) <= A.budget) {
             // (64 bytes more: a part's characters are read 16 at a time from any position)
             X.inl = (uint8_t*)A.get(nm("inl").c_str(), (size_t)bytes + 64);
             X.inl_base = (int64_t*)A.get(nm("inl_base").c_str(), sizeof(int64_t) * kLenTab);
-            upload(X.inl_base, inl_base.data(), sizeof(int64_t) * kLenTab, st);
-            hip_check(launch_gather_inline(D, keys, vals, E, tau, X.inl_base, X.inl, st),
-                      "gather_inline");
         }
     }
+    hip_check(launch_emit_segments(D, tau, g_first, g_count, X.inl_base, ka, va, st), "emit");
+    bool alt = false;
+    hip_check(radix_sort_u64(ka, va, kb, vb, (uint64_t)E, bits, tmp, tb, &alt, st),
+              "radix(index)");
+    X.vals = vals;
+    if (X.inl)
+        hip_check(launch_gather_inline(D, keys, vals, E, tau, X.inl_base, X.inl, st),
+                  "gather_inline");
     // lists = runs of equal keys
     uint32_t* runstart = (uint32_t*)W.get("index.runstart", sizeof(uint32_t) * (size_t)E);
     uint32_t* run_count = (uint32_t*)W.get("index.runs", sizeof(uint32_t));
@@ -717,8 +685,14 @@ void build_index(const DevSet& D, int tau, Alloc& A, const std::string& tag, Dev
     hip_check(launch_run_starts(keys, (uint64_t)E, stmp, sb, runstart, run_count, st), "run_starts");
     uint32_t nruns = 0;
     readback(&nruns, run_count, sizeof(uint32_t), st);
+    uint32_t present[8];                      // symbols: what the emitting kernel found
+    readback(present, D.bitmap, sizeof present, st);
     sync_readback(st);
     X.lists = nruns;
+    int sigma = 0;
+    for (uint32_t word : present) sigma += __builtin_popcount(word);
+    const int sbits = std::max(1, bitlen((uint64_t)sigma));
+    X.sym = SymMap{D.code, sbits, kHashBits / sbits};
     // records and directory of the lists: an entry for every one or two lists of a group, at
     // least one a group
     const uint32_t ngroups = (uint32_t)((D.lmax - T1 + 1) * T1);

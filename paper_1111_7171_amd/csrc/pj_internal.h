@@ -66,7 +66,10 @@ struct DevSet {
     uint8_t* sarena = nullptr;          // padded, length-sorted bytes
     int32_t* perm = nullptr;            // [n] sorted position -> id
     uint16_t* slen = nullptr;           // [n] sorted position -> length
-    SymMap sym;                         // the set's symbol map (sets to be indexed)
+    // sets to be indexed: the bytes present (bitmap of 8 words, scratch) and their symbol codes,
+    // which the first index writes
+    uint32_t* bitmap = nullptr;
+    uint16_t* code = nullptr;
     int32_t* lenstart = nullptr;        // [kLenTab + 1] first sorted position of each length
     int64_t* gbase = nullptr;           // [kLenTab] byte base of each length group
     // host copies of the per-length tables
@@ -205,8 +208,11 @@ constexpr int kTicketWord = 10, kTicketLines = 8;
 constexpr int kJoinCounters = kCounterLine * (1 + kStatShards);
 
 // ---- launchers (pj_device.hip) ----
-hipError_t launch_length_hist(const int32_t* offs, int64_t n, int32_t* lcount, int32_t* err,
-                              hipStream_t s);
+// lcount: kLenTab + 1 zeroed words: strings per length, errors found (1 first offset not 0, 2 offsets
+// decrease, 4 a string too long); also writes lenstart [kLenTab + 1] and gbase [kLenTab],
+// and clears bitmap [8] and code [256] (both or neither nullptr)
+hipError_t launch_length_hist(const int32_t* offs, int64_t n, int32_t* lcount, int32_t* lenstart,
+                              int64_t* gbase, uint32_t* bitmap, uint16_t* code, hipStream_t s);
 hipError_t launch_iota_len_keys(const int32_t* offs, int64_t n, uint32_t* keys, uint32_t* vals,
                                 hipStream_t s);
 hipError_t launch_pack_arena(const uint8_t* bytes, const int32_t* offs, const int32_t* perm,
@@ -216,9 +222,8 @@ hipError_t launch_pack_arena(const uint8_t* bytes, const int32_t* offs, const in
 // stable sort of the ids by length (strings of at most 255 bytes; hist: strings per length)
 hipError_t launch_length_sort(const int32_t* offs, int64_t n, const int32_t* hist, int32_t* perm,
                               void* tmp, size_t tmp_bytes, hipStream_t s);
-hipError_t launch_emit_segments(const DevSet& S, int tau, const int64_t* ebase_dev,
-                                int64_t g_first, int64_t g_count, const SymMap& sym,
-                                uint64_t* keys, uint32_t* vals, hipStream_t s);
+hipError_t launch_emit_segments(const DevSet& S, int tau, int64_t g_first, int64_t g_count,
+                                int64_t* inl_base, uint64_t* keys, uint32_t* vals, hipStream_t s);
 hipError_t launch_gather_inline(const DevSet& S, const uint64_t* keys, const uint32_t* vals,
                                 int64_t E, int tau, const int64_t* inl_base, uint8_t* inl,
                                 hipStream_t s);

@@ -74,3 +74,18 @@ def test_large_sets(n):
     pj = O.self_join_pj(S, 1)
     assert len(pj.pairs) >= (n - 1) // 1000
     assert np.array_equal(P.pj_self_join(S, 1), pj.pairs)
+
+
+# strings too short for the larger thresholds: the index at tau = 4 is empty, those below are not, and
+# the symbol codes are the set's for all of them
+@pytest.mark.parametrize("longest", [0, 1, 2, 4, 5])
+def test_short_sets(longest):
+    rng = np.random.default_rng(longest)
+    strings = [bytes(97 + rng.integers(0, 3, size=int(ln)).astype(np.uint8))
+               for ln in rng.integers(0, longest + 1, size=200)]
+    S = W.from_list(strings)
+    index = P.pj_build_index(S, 0, 4)
+    for tau in range(5):
+        assert np.array_equal(P.pj_query(index, S, np.full(S.n, tau)), O.join_pj(S, S, tau).pairs)
+        assert np.array_equal(P.pj_self_join(S, tau), O.self_join_pj(S, tau).pairs)
+    index.free()
