@@ -1846,21 +1846,17 @@ __global__ __launch_bounds__(kBlock) void k_run_lengths(const uint32_t* __restri
 }
 
 // ------------------------------------------------------------------------------------------
-// Long-string verification by row blocks.  A candidate's part DP runs for hundreds of rows
-// when it passes and stops after a few when it does not, so 64 candidates in lockstep leave
-// most lanes idle.  Here the candidates of the small lists are materialised in slot order (one
-// (tau_l, tau_r) per slot, so a wave's 64 tasks share the band width class), and the DPs run in
-// passes: a pass takes up to K rows of every live task, and the tasks still running after them
-// go, with their band row (values min(M, t+1) in bytes: min(., t+1) commutes with the
-// recurrence and every decision compares with t), to a compacted queue for the next pass.
-// Left parts run first; candidates whose left part passes become right-part tasks (Algorithm
-// 3 examines right parts only after the left parts pass).  A pass stages its rows' characters
-// in LDS first, so the row loop reads no global memory.
+// Long-string verification.  A candidate's part DP runs for hundreds of rows when it passes and
+// stops after a few when it does not, so 64 candidates in lockstep leave most lanes idle.  Here the
+// candidates of the small lists are materialised in slot order (one (tau_l, tau_r) per slot, so a
+// wave's 64 tasks share the band width class).  Their left parts' first rows run a candidate a lane
+// (k_verify_first), which ends most; the others, and the right parts, are taken a diagonal a lane
+// (k_verify_far), which costs by differences and not by rows.
 // ------------------------------------------------------------------------------------------
 
-constexpr int kContMaxRows = 64;     // rows of one pass (at most)
+constexpr int kContMaxRows = 64;     // rows staged at a time
 constexpr int kContW = 33;           // widest band class
-// 16-byte blocks staged per lane and pass: A needs K + 15 bytes, B up to kContW + K + 15 + 15
+// 16-byte blocks staged per lane: A needs kContMaxRows + 15 bytes, B kContW + kContMaxRows + 15 + 15
 constexpr int kStageA = (kContMaxRows + 15 + 15) / 16;
 constexpr int kStageB = (kContW + kContMaxRows + 15 + 15) / 16;
 
@@ -1869,12 +1865,6 @@ struct LongRec {
     uint4 a;        // gx, gy, meta (p, i, l), n = |x|
     uint4 b;        // x offset (lo, hi), y offset (lo, hi)
 };
-// A task that continues: the task, the rows done, its band row as bytes.
-struct ContRec {
-    LongRec rec;
-    uint4 st[3];    // st[0].x = rows done; bytes 4 .. 4 + kContW - 1 = min(M[k], t + 1)
-};
-
 // per slot (i - 1): number of candidates of the small-list hits
 __global__ __launch_bounds__(kBlock) void k_long_slot_counts(const Hit* __restrict__ hits, uint64_t nh,
                                                              uint32_t* __restrict__ slot_cnt)
@@ -1947,24 +1937,57 @@ __global__ __launch_bounds__(kBlock) void k_long_scatter(const Hit* __restrict__
     }
 }
 
-// The tasks [b0, b1) of one slot for one wave (one task per lane): up to K rows of each task's
+// Chunks of the slots' tasks: counts by slot (lane = slot), `per` tasks a chunk (by slot too); finds a
+// chunk's slot and its range in the slot's region.
+struct SlotChunks {
+    uint32_t count, per, chunks, incl, total;
+    __device__ SlotChunks(const uint32_t* counts, int slots, uint32_t per_) : per(per_)
+    {
+        const int lane = threadIdx.x & 63;
+        count = lane < slots ? counts[lane] : 0u;
+        chunks = (count + per - 1) / per;
+        incl = wave_incl_scan(chunks);
+        total = __shfl(incl, 63, 64);
+    }
+    __device__ int find(uint32_t ch, uint32_t* b0, uint32_t* b1) const
+    {
+        const int slot = __popcll(__ballot(incl <= ch));
+        const uint32_t p = __shfl(per, slot, 64);
+        *b0 = (ch - __shfl(incl - chunks, slot, 64)) * p;
+        *b1 = min(*b0 + p, (uint32_t)__shfl(count, slot, 64));
+        return slot;
+    }
+};
+
+// rec of the flagged lanes to the slot's region of out
+__device__ inline void append_tasks(bool flag, const LongRec& rec, LongRec* __restrict__ out,
+                                    uint32_t* count)
+{
+    const uint64_t m = __ballot(flag);
+    if (!m) return;
+    uint32_t base = 0;
+    if ((threadIdx.x & 63) == 0) base = atomicAdd(count, (uint32_t)__popcll(m));
+    base = __shfl(base, 0, 64);
+    if (flag) out[base + (uint32_t)__popcll(m & lanemask_lt())] = rec;
+}
+
+// The candidates [b0, b1) of one slot for one wave (one per lane): up to K rows of each one's left
 // part DP on M values in diagonal coordinates (band index k holds column j = i - a + k of row i;
 // up = index k + 1, left = k - 1 of this row, diagonal = k; cells outside the band or left of
 // column 0 start large and only see large inputs, so column 0 follows from the recurrence;
 // indices right of column nc never feed a cell inside the matrix).  The expected distance of
 // index k is M + |b - k| (b = a + Delta, the final cell's index); a row whose smallest one
 // exceeds t stops the DP (Lemma 4).  The characters come from the lane's LDS stage (element q at
-// stage[q * 64]): A[row + q] for q < kContMaxRows, then B[row - a + q] (256 outside B).
+// stage[q * 64]): A[row + q] for q < kContMaxRows, then B[row - a + q] (256 outside B).  Parts that
+// pass go to rout, parts that are not done to cout (whole, k_verify_far starts them anew).
 template <int MAXW>
-__device__ inline void cont_chunk(const VerifyParams& V, const Div& div, int side, int slot,
-                                  bool fresh, const LongRec* __restrict__ fin,
-                                  const ContRec* __restrict__ cin, uint32_t b0, uint32_t b1, int K,
-                                  ContRec* __restrict__ cout, uint32_t* __restrict__ cout_cnt,
+__device__ inline void first_rows(const VerifyParams& V, const Div& div, int slot,
+                                  const LongRec* __restrict__ fin, uint32_t b0, uint32_t b1, int K,
+                                  LongRec* __restrict__ cout, uint32_t* __restrict__ cout_cnt,
                                   LongRec* __restrict__ rout, uint32_t* __restrict__ rout_cnt,
                                   uint32_t qbase,
                                   __attribute__((address_space(3))) uint32_t* stage32,
-                                  WaveAppender<uint64_t, kAppendCap>& acc, uint64_t& my_cells,
-                                  uint64_t& my_miss)
+                                  uint64_t& my_cells, uint64_t& my_miss)
 {
     constexpr int BIG = 1 << 20;
     const int lane = threadIdx.x & 63;
@@ -1972,7 +1995,7 @@ __device__ inline void cont_chunk(const VerifyParams& V, const Div& div, int sid
     const __attribute__((address_space(3))) uint8_t* stage8 =
         (const __attribute__((address_space(3))) uint8_t*)stage32;
     const int i = slot + 1;
-    const int t = side == 0 ? i - 1 : V.tau + 1 - i;
+    const int t = i - 1;
     const uint32_t k = b0 + (uint32_t)lane;
     bool act = k < b1;
     LongRec rec;
@@ -1987,9 +2010,7 @@ __device__ inline void cont_chunk(const VerifyParams& V, const Div& div, int sid
     const uint8_t* A_end = nullptr;     // end of the padded slot of A's / B's string
     const uint8_t* B_end = nullptr;
     if (act) {
-        ContRec cr;
-        if (fresh) rec = fin[k];
-        else { cr = cin[k]; rec = cr.rec; }
+        rec = fin[k];
         const uint32_t meta = rec.a.z;
         const int p = (int)(meta & 2047u) + 1;
         const int l = (int)(meta >> 17);
@@ -1997,41 +2018,29 @@ __device__ inline void cont_chunk(const VerifyParams& V, const Div& div, int sid
         const uint8_t* x = V.x_arena + ((uint64_t)rec.b.y << 32 | rec.b.x);
         const uint8_t* y = V.y_arena + ((uint64_t)rec.b.w << 32 | rec.b.z);
         const Seg sg = partition_seg(l, i, V.tau, div);
-        const uint8_t* r = side == 0 ? y : y + sg.p - 1 + sg.len;
-        const uint8_t* s = side == 0 ? x : x + p - 1 + sg.len;
-        const int lr = side == 0 ? sg.p - 1 : l - (sg.p - 1 + sg.len);
-        const int ls = side == 0 ? p - 1 : n - (p - 1 + sg.len);
+        const int lr = sg.p - 1, ls = p - 1;
         const uint8_t* yend = y + stride_of(l);
         const uint8_t* xend = x + stride_of(n);
-        if (lr <= ls) { A = r; nr = lr; B = s; nc = ls; A_end = yend; B_end = xend; }
-        else          { A = s; nr = ls; B = r; nc = lr; A_end = xend; B_end = yend; }
+        if (lr <= ls) { A = y; nr = lr; B = x; nc = ls; A_end = yend; B_end = xend; }
+        else          { A = x; nr = ls; B = y; nc = lr; A_end = xend; B_end = yend; }
         const int delta = nc - nr;
         a = (t - delta) >> 1;
         b = (t + delta) >> 1;
-        if (fresh) {
-            bool ok = true;
-            if (side == 0 && sg.len > V.exact_len) {
-                for (int q = 0; q < sg.len; ++q) ok &= (x[p - 1 + q] == y[sg.p - 1 + q]);
-                if (!ok) my_miss += 1;
-            }
-            if (!ok) st = 3;                               // not a candidate
-            else if (delta > t) st = 2;                    // no row
-            else if (nr == 0) st = (nc <= t) ? 1 : 2;
+        bool ok = true;
+        if (sg.len > V.exact_len) {
+            for (int q = 0; q < sg.len; ++q) ok &= (x[p - 1 + q] == y[sg.p - 1 + q]);
+            if (!ok) my_miss += 1;
+        }
+        if (!ok) st = 3;                                   // not a candidate
+        else if (delta > t) st = 2;                        // no row
+        else if (nr == 0) st = (nc <= t) ? 1 : 2;
 #pragma unroll
-            for (int q = 0; q < MAXW; ++q) {
-                const int j = q - a;
-                M[q] = (j >= 0 && j <= min(nc, b)) ? j : BIG;
-            }
-        } else {
-            row = (int)cr.st[0].x;
-            const uint32_t wv[12] = {cr.st[0].x, cr.st[0].y, cr.st[0].z, cr.st[0].w,
-                                     cr.st[1].x, cr.st[1].y, cr.st[1].z, cr.st[1].w,
-                                     cr.st[2].x, cr.st[2].y, cr.st[2].z, cr.st[2].w};
-#pragma unroll
-            for (int q = 0; q < MAXW; ++q) M[q] = (int)((wv[1 + q / 4] >> (8 * (q % 4))) & 255u);
+        for (int q = 0; q < MAXW; ++q) {
+            const int j = q - a;
+            M[q] = (j >= 0 && j <= min(nc, b)) ? j : BIG;
         }
     }
-    // the pass's rows in sub-blocks of kContMaxRows: each stages its characters (the 16-byte
+    // the rows in sub-blocks of kContMaxRows: each stages its characters (the 16-byte
     // blocks holding A[row .. row + 64) and B[max(row - a, 0) .. row - a + MAXW + 64), each block
     // only if it starts inside its string's padded slot, 16-byte aligned; all loads are issued
     // before the first LDS write) and runs its rows
@@ -2138,134 +2147,39 @@ __device__ inline void cont_chunk(const VerifyParams& V, const Div& div, int sid
         }
     }
     if (run && (st == 1 || st == 2)) my_cells += (uint64_t)band_cells(row, nc, a, b);
-    // outcomes
-    const bool cont = run && st == 0;
-    {
-        const uint64_t m = __ballot(cont);
-        if (m) {
-            uint32_t base = 0;
-            if (lane == 0) base = atomicAdd(&cout_cnt[slot], (uint32_t)__popcll(m));
-            base = __shfl(base, 0, 64);
-            if (cont) {
-                ContRec c;
-                c.rec = rec;
-                uint32_t wds[12];
-                wds[0] = (uint32_t)row;
-#pragma unroll
-                for (int q = 1; q < 12; ++q) wds[q] = 0;
-#pragma unroll
-                for (int q = 0; q < MAXW; ++q) {
-                    const uint32_t v = (uint32_t)min(M[q], t + 1);
-                    wds[1 + q / 4] |= v << (8 * (q % 4));
-                }
-                c.st[0] = make_uint4(wds[0], wds[1], wds[2], wds[3]);
-                c.st[1] = make_uint4(wds[4], wds[5], wds[6], wds[7]);
-                c.st[2] = make_uint4(wds[8], wds[9], wds[10], wds[11]);
-                cout[qbase + base + (uint32_t)__popcll(m & lanemask_lt())] = c;
-            }
-        }
-    }
-    if (side == 0) {
-        const bool pass = act && st == 1;
-        const uint64_t m = __ballot(pass);
-        if (m) {
-            uint32_t base = 0;
-            if (lane == 0) base = atomicAdd(&rout_cnt[slot], (uint32_t)__popcll(m));
-            base = __shfl(base, 0, 64);
-            if (pass) rout[qbase + base + (uint32_t)__popcll(m & lanemask_lt())] = rec;
-        }
-    } else {
-        acc.push(act && st == 1, ((uint64_t)rec.a.x << 32) | rec.a.y, V.out, V.out_cap,
-                 &V.counters[3]);
-    }
+    append_tasks(run && st == 0, rec, cout + qbase, &cout_cnt[slot]);
+    append_tasks(act && st == 1, rec, rout + qbase, &rout_cnt[slot]);
 }
 
-// One pass over the tasks of both sides, so that a candidate's right part starts in the pass
-// after its left part passes and runs beside the other candidates' left parts.  Three groups of
-// tasks, each in per-slot regions that start at off[slot]:
-//  0: left parts (side 0), fresh from fin_l (counts cnt_l; the first pass) or continuing from
-//     cin_l (counts cnt_l); cnt_l null when no left part is left;
-//  1: right parts new in this pass: fin_r[lo_r[slot], hi_r[slot]) (lo_r null: none);
-//  2: right parts continuing from cin_r (counts cnt_r; null: none).
-// Continuing tasks go to cout_l / cout_r (counts cout_l_cnt / cout_r_cnt); left parts that pass
-// are appended to rout (counts rout_cnt), right parts that pass to the pair buffer.
-struct ContPass {
-    const LongRec* fin_l;
-    const ContRec* cin_l;
-    const uint32_t* cnt_l;
-    const LongRec* fin_r;
-    const uint32_t* lo_r;
-    const uint32_t* hi_r;
-    const ContRec* cin_r;
-    const uint32_t* cnt_r;
-    const uint32_t* off;
-    ContRec* cout_l;
-    uint32_t* cout_l_cnt;
-    ContRec* cout_r;
-    uint32_t* cout_r_cnt;
-    LongRec* rout;
-    uint32_t* rout_cnt;
-    uint32_t* zero_l;        // count buffers the next pass writes (read by the previous pass
-    uint32_t* zero_r;        // only): cleared here
-    int K;
-};
-
-__global__ __launch_bounds__(64) void k_verify_cont(VerifyParams V, Div div, ContPass P)
+__global__ __launch_bounds__(64) void k_verify_first(VerifyParams V, Div div,
+                                                     const LongRec* __restrict__ cands,
+                                                     const uint32_t* __restrict__ slot_cnt,
+                                                     const uint32_t* __restrict__ off, int K,
+                                                     LongRec* __restrict__ cout, uint32_t* cout_cnt,
+                                                     LongRec* __restrict__ rout, uint32_t* rout_cnt)
 {
-    if (blockIdx.x == 0) {
-        if (P.zero_l) P.zero_l[threadIdx.x] = 0u;
-        if (P.zero_r) P.zero_r[threadIdx.x] = 0u;
-    }
-    __shared__ uint64_t s_acc[kAppendCap];
     __shared__ uint4 s_stage[(kStageA + kStageB) * 64];
-    WaveAppender<uint64_t, kAppendCap> acc{s_acc, 0};
     const int lane = threadIdx.x & 63;
     __attribute__((address_space(3))) uint32_t* stage =
         (__attribute__((address_space(3))) uint32_t*)s_stage + 4 * lane;
     uint64_t my_cells = 0, my_miss = 0;
-    // chunks of 64 tasks: group 0's slots, then group 1's, then group 2's (lane = slot)
-    const bool sl = lane <= V.tau;
-    const uint32_t c0 = (sl && P.cnt_l) ? P.cnt_l[lane] : 0u;
-    const uint32_t c1 = (sl && P.lo_r) ? P.hi_r[lane] - P.lo_r[lane] : 0u;
-    const uint32_t c2 = (sl && P.cnt_r) ? P.cnt_r[lane] : 0u;
-    const uint32_t n0 = (c0 + 63u) / 64u, n1 = (c1 + 63u) / 64u, n2 = (c2 + 63u) / 64u;
-    const uint32_t i0 = wave_incl_scan(n0), i1 = wave_incl_scan(n1), i2 = wave_incl_scan(n2);
-    const uint32_t T0 = __shfl(i0, 63, 64), T1 = __shfl(i1, 63, 64), T2 = __shfl(i2, 63, 64);
-    const uint32_t total = T0 + T1 + T2;
-    for (uint32_t ch = blockIdx.x; ch < total; ch += gridDim.x) {
-        const int g = ch < T0 ? 0 : (ch < T0 + T1 ? 1 : 2);
-        const uint32_t loc = g == 0 ? ch : (g == 1 ? ch - T0 : ch - T0 - T1);
-        const uint32_t incl = g == 0 ? i0 : (g == 1 ? i1 : i2);
-        const uint32_t nch = g == 0 ? n0 : (g == 1 ? n1 : n2);
-        const uint32_t cc = g == 0 ? c0 : (g == 1 ? c1 : c2);
-        const int slot = __popcll(__ballot(incl <= loc));
-        const uint32_t first = __shfl(incl - nch, slot, 64);
-        const uint32_t cs = __shfl(cc, slot, 64);
-        const uint32_t base = P.off[slot];
-        const uint32_t b0 = (loc - first) * 64u;
-        const uint32_t b1 = min(b0 + 64u, cs);
-        const int side = g == 0 ? 0 : 1;
-        const bool fresh = g == 0 ? P.cin_l == nullptr : g == 1;
-        const LongRec* fi = g == 0 ? (fresh ? P.fin_l + base : nullptr)
-                                   : (g == 1 ? P.fin_r + base + P.lo_r[slot] : nullptr);
-        const ContRec* ci = g == 0 ? (fresh ? nullptr : P.cin_l + base)
-                                   : (g == 2 ? P.cin_r + base : nullptr);
-        ContRec* cout = side == 0 ? P.cout_l : P.cout_r;
-        uint32_t* cout_cnt = side == 0 ? P.cout_l_cnt : P.cout_r_cnt;
-        const int t = side == 0 ? slot : V.tau - slot;
-#define PJ_CONT(W) cont_chunk<W>(V, div, side, slot, fresh, fi, ci, b0, b1, P.K, cout, cout_cnt,  \
-                                 P.rout, P.rout_cnt, base, stage, acc, my_cells, my_miss)
-        if (t + 1 <= 5) PJ_CONT(5);
-        else if (t + 1 <= 9) PJ_CONT(9);
-        else if (t + 1 <= 13) PJ_CONT(13);
-        else if (t + 1 <= 17) PJ_CONT(17);
-        else if (t + 1 <= 21) PJ_CONT(21);
-        else if (t + 1 <= 25) PJ_CONT(25);
-        else if (t + 1 <= 29) PJ_CONT(29);
-        else PJ_CONT(33);
-#undef PJ_CONT
+    const SlotChunks S(slot_cnt, V.tau + 1, 64u);
+    for (uint32_t ch = blockIdx.x; ch < S.total; ch += gridDim.x) {
+        uint32_t b0, b1;
+        const int slot = S.find(ch, &b0, &b1);
+        const uint32_t base = off[slot];
+#define PJ_FIRST(W) first_rows<W>(V, div, slot, cands + base, b0, b1, K, cout, cout_cnt, rout,     \
+                                  rout_cnt, base, stage, my_cells, my_miss)
+        if (slot + 1 <= 5) PJ_FIRST(5);
+        else if (slot + 1 <= 9) PJ_FIRST(9);
+        else if (slot + 1 <= 13) PJ_FIRST(13);
+        else if (slot + 1 <= 17) PJ_FIRST(17);
+        else if (slot + 1 <= 21) PJ_FIRST(21);
+        else if (slot + 1 <= 25) PJ_FIRST(25);
+        else if (slot + 1 <= 29) PJ_FIRST(29);
+        else PJ_FIRST(33);
+#undef PJ_FIRST
     }
-    acc.flush(V.out, V.out_cap, &V.counters[3]);
     my_cells = wave_sum(my_cells);
     my_miss = wave_sum(my_miss);
     if (lane == 0) {
@@ -2273,6 +2187,123 @@ __global__ __launch_bounds__(64) void k_verify_cont(VerifyParams V, Div div, Con
         if (my_cells) atomicAdd(&line[4], (unsigned long long)my_cells);
         if (my_miss) atomicAdd(&line[5], (unsigned long long)my_miss);
     }
+}
+
+// A part's DP by furthest rows (Ukkonen 1985; Landau and Vishkin 1989), L lanes a candidate and a band
+// diagonal each: f(e, k) = the last row on diagonal k with distance up to e, found from the
+// neighbours' rows at e - 1 and the characters that then agree, 32 at a time.  A diagonal is followed
+// while e + |b - k| <= t, the cells the band's rows keep alive; a row passes Lemma 4's test exactly if
+// some followed diagonal reaches it, so the rows the DP would have run, and its cells, are known
+// without running them.  A part whose strings differ in d places costs d + 1 steps and a 32nd of its
+// length.  Sets rows (run by the DP) and returns whether the part passes; the same in all L lanes.
+struct __attribute__((packed)) Chars32 {
+    uint64_t w[4];
+};
+
+template <int L>
+__device__ inline bool far_part(const uint8_t* A, int nr, const uint8_t* B, int nc, int t, bool act,
+                                int* rows)
+{
+    const int lane = threadIdx.x & 63, k = lane & (L - 1);
+    constexpr int NONE = -(1 << 20);
+    constexpr uint64_t kGroup = L == 64 ? ~0ull : (1ull << (L & 63)) - 1ull;
+    const int delta = nc - nr, a = (t - delta) >> 1, b = (t + delta) >> 1;
+    const int d = k - a, away = abs(b - k);
+    const int lim = min(nr, nc - d);               // the diagonal's last row
+    const bool in_band = k <= a + b;
+    int f = NONE;
+    bool done = !act || delta > t, pass = false;
+    for (int e = 0; __ballot(!done) != 0; ++e) {
+        const int from_left = __shfl_up(f, 1, L), from_right = __shfl_down(f, 1, L);
+        const bool on = !done && in_band && e + away <= t;
+        int row = e == 0 ? (d == 0 ? 0 : NONE)
+                         : max(f + 1, max(k > 0 ? from_left : NONE, k < a + b ? from_right + 1 : NONE));
+        row = min(row, lim);
+        bool more = on && row >= 0 && row < lim;
+        while (__ballot(more) != 0) {
+            if (more) {
+                const Chars32 u = *reinterpret_cast<const Chars32*>(A + row);
+                const Chars32 v = *reinterpret_cast<const Chars32*>(B + row + d);
+                int same = 32;
+#pragma unroll
+                for (int q = 3; q >= 0; --q) {
+                    const uint64_t x = u.w[q] ^ v.w[q];
+                    same = x ? 8 * q + (__builtin_ctzll(x) >> 3) : same;
+                }
+                row = min(row + same, lim);
+                more = same == 32 && row < lim;
+            }
+        }
+        if (on) f = row >= 0 ? row : NONE;
+        const uint64_t ends = __ballot(on && k == b && f >= nr);
+        if ((ends >> (lane & ~(L - 1))) & kGroup) pass = done = true;
+        if (e >= t) done = true;
+    }
+    int far = in_band ? max(f, 0) : 0;
+#pragma unroll
+    for (int m = 1; m < L; m <<= 1) far = max(far, __shfl_xor(far, m, 64));
+    *rows = pass ? nr : min(far + 1, nr);
+    return pass;
+}
+
+// lanes a candidate: as many as a band of threshold t has diagonals, a power of two from 8
+__device__ inline uint32_t far_lanes(int t) { return t < 8 ? 8u : t < 16 ? 16u : t < 32 ? 32u : 64u; }
+
+// Side 0: the left parts that k_verify_first left; those that pass become right tasks.  Side 1: the
+// right parts; those that pass are results.  A chunk is one slot's, so one threshold's.  In place of
+// twelve more passes by rows, each with its queue of band rows: first rows and this, 10^5 long
+// strings at tau = 16, 0.98 -> 0.28 ms; at tau = 32, where most candidates are not similar, 2.6 ->
+// 2.1.  Bound by the latency of a step's two reads and two lane exchanges.
+__global__ __launch_bounds__(kBlock) void k_verify_far(VerifyParams V, Div div, int side,
+                                                       const LongRec* __restrict__ tasks,
+                                                       const uint32_t* __restrict__ counts,
+                                                       const uint32_t* __restrict__ off,
+                                                       LongRec* __restrict__ rout,
+                                                       uint32_t* rout_cnt)
+{
+    constexpr int kCap = 64;
+    __shared__ uint64_t s_acc[kWaves][kCap];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    WaveAppender<uint64_t, kCap> acc{s_acc[w], 0};
+    uint64_t my_cells = 0;
+    auto threshold = [&](int slot) { return side == 0 ? slot : V.tau - slot; };
+    const SlotChunks S(counts, V.tau + 1, 64u / far_lanes(max(threshold(lane), 0)));
+    for (uint32_t ch = blockIdx.x * kWaves + (uint32_t)w; ch < S.total; ch += gridDim.x * kWaves) {
+        uint32_t b0, b1;
+        const int slot = __builtin_amdgcn_readfirstlane(S.find(ch, &b0, &b1));
+        const int i = slot + 1, t = threshold(slot);
+        const uint32_t lanes = far_lanes(t);
+        const uint32_t k = b0 + (uint32_t)lane / lanes;
+        const bool act = k < b1, first = ((uint32_t)lane & (lanes - 1)) == 0;
+        // (groups past the end read the chunk's first task)
+        const LongRec rec = tasks[off[slot] + (act ? k : b0)];
+        const uint32_t meta = rec.a.z;
+        const int p = (int)(meta & 2047u) + 1, l = (int)(meta >> 17), n = (int)rec.a.w;
+        const uint8_t* x = V.x_arena + ((uint64_t)rec.b.y << 32 | rec.b.x);
+        const uint8_t* y = V.y_arena + ((uint64_t)rec.b.w << 32 | rec.b.z);
+        const Seg sg = partition_seg(l, i, V.tau, div);
+        const int ry = sg.p - 1 + sg.len, rx = p - 1 + sg.len;
+        const uint8_t* r = side == 0 ? y : y + ry;
+        const uint8_t* s = side == 0 ? x : x + rx;
+        const int lr = side == 0 ? sg.p - 1 : l - ry, ls = side == 0 ? p - 1 : n - rx;
+        const bool yrows = lr <= ls;
+        const uint8_t* A = yrows ? r : s;
+        const uint8_t* B = yrows ? s : r;
+        const int nr = yrows ? lr : ls, nc = yrows ? ls : lr, delta = nc - nr;
+        int rows = 0;
+        bool pass;
+        if (lanes == 8) pass = far_part<8>(A, nr, B, nc, t, act, &rows);
+        else if (lanes == 16) pass = far_part<16>(A, nr, B, nc, t, act, &rows);
+        else if (lanes == 32) pass = far_part<32>(A, nr, B, nc, t, act, &rows);
+        else pass = far_part<64>(A, nr, B, nc, t, act, &rows);
+        if (act && first && delta <= t)
+            my_cells += (uint64_t)band_cells(rows, nc, (t - delta) >> 1, (t + delta) >> 1);
+        if (side == 0) append_tasks(pass && first, rec, rout + off[slot], &rout_cnt[slot]);
+        else acc.push(pass && first, (uint64_t)rec.a.x << 32 | rec.a.y, V.out, V.out_cap,
+                      &V.counters[3]);
+    }
+    block_flush(acc, V.out, V.out_cap, &V.counters[3]);
+    block_add(&stat_line(V.counters, V.shards)[4], my_cells);
 }
 
 __global__ void k_fill_u32(uint32_t* __restrict__ p, int n, uint32_t v)
@@ -2791,43 +2822,32 @@ hipError_t launch_run_lengths(const uint32_t* runstart, uint32_t nruns, uint32_t
     return hipGetLastError();
 }
 
-// count arrays of 256 u32: slot counts, offsets, cursors, right tasks, three left and three right
-// continuation counts, two snapshots of the right-task counts
-constexpr int kLongCounts = 12;
+// count arrays of 256 u32: slot counts, offsets, cursors, right tasks, left tasks not done
+constexpr int kLongCounts = 5;
 
 size_t long_scratch_bytes(uint64_t ncand)
 {
     const uint64_t rc = (ncand * sizeof(LongRec) + 255) & ~(uint64_t)255;
-    const uint64_t cc = (ncand * sizeof(ContRec) + 255) & ~(uint64_t)255;
-    // candidates, right tasks, two left and two right continuation queues
-    return kLongCounts * 256 * sizeof(uint32_t) + 2 * rc + 4 * cc;
+    // candidates, right tasks, left tasks not done
+    return kLongCounts * 256 * sizeof(uint32_t) + 3 * rc;
 }
 
-__global__ void k_copy_u32(uint32_t* __restrict__ dst, const uint32_t* __restrict__ src, int n)
-{
-    for (int k = threadIdx.x; k < n; k += blockDim.x) dst[k] = src[k];
-}
-
-hipError_t launch_verify_long(const VerifyParams& V, uint64_t ncand, int max_rows, void* scratch,
-                              int grid, hipStream_t s)
+hipError_t launch_verify_long(const VerifyParams& V, uint64_t ncand, void* scratch, int grid,
+                              hipStream_t s)
 {
     if (V.nhits == 0 || ncand == 0) return hipSuccess;
-    if (V.tau + 1 > kContW || grid < 1 || V.q_tau || max_rows < 0) return hipErrorInvalidValue;
+    if (V.tau + 1 > kContW || grid < 1 || V.q_tau) return hipErrorInvalidValue;
     uint8_t* p = (uint8_t*)scratch;
     uint32_t* slot_cnt = (uint32_t*)p;
     uint32_t* off = slot_cnt + 256;
     uint32_t* cursor = off + 256;
     uint32_t* right_cnt = cursor + 256;
-    uint32_t* cl[3] = {right_cnt + 256, right_cnt + 512, right_cnt + 768};
-    uint32_t* cr[3] = {right_cnt + 1024, right_cnt + 1280, right_cnt + 1536};
-    uint32_t* snap[2] = {right_cnt + 1792, right_cnt + 2048};
+    uint32_t* left_cnt = right_cnt + 256;
     const uint64_t rc = (ncand * sizeof(LongRec) + 255) & ~(uint64_t)255;
-    const uint64_t cc = (ncand * sizeof(ContRec) + 255) & ~(uint64_t)255;
     uint8_t* q = p + kLongCounts * 256 * sizeof(uint32_t);
     LongRec* cands = (LongRec*)q;
     LongRec* right = (LongRec*)(q + rc);
-    ContRec* cont_l[2] = {(ContRec*)(q + 2 * rc), (ContRec*)(q + 2 * rc + cc)};
-    ContRec* cont_r[2] = {(ContRec*)(q + 2 * rc + 2 * cc), (ContRec*)(q + 2 * rc + 3 * cc)};
+    LongRec* left = (LongRec*)(q + 2 * rc);
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, s, slot_cnt, kLongCounts * 256, 0u);
     const unsigned hb = (unsigned)std::min<uint64_t>(blocks_for(V.nhits), 4096);
     hipLaunchKernelGGL(k_long_slot_counts, dim3(hb), dim3(kBlock), 0, s, V.hits, V.nhits, slot_cnt);
@@ -2836,63 +2856,20 @@ hipError_t launch_verify_long(const VerifyParams& V, uint64_t ncand, int max_row
                        V.nhits, V.vals, V.x_slen, V.x_lenstart, V.x_gbase, V.y_lenstart,
                        V.y_gbase, cursor, cands);
     const Div div = make_div(V.tau + 1);
-    // pass lengths: 16, 16, 32, 64, ..., 512 rows; PJ_LONG_PASSES (a comma list, the last entry
-    // repeated) sets them (tests and tuning; it changes no result)
-    int sched[16], nsched = 0;
+    // rows of the first pass (10^5 long strings, ms in all with 16 / 32 / 64: tau = 8 0.16, 0.16,
+    // 0.17; 16 0.30, 0.30, 0.31; 24 0.81, 0.77, 0.79; 32 2.88, 2.28, 2.41); PJ_LONG_PASSES sets
+    // them (tests and tuning; it changes no result)
+    int K = 32;
     if (const char* e = getenv("PJ_LONG_PASSES")) {
-        for (const char* c = e; *c && nsched < 16;) {
-            const int v = atoi(c);
-            if (v < 1 || v > 4096) return hipErrorInvalidValue;
-            sched[nsched++] = v;
-            while (*c && *c != ',') ++c;
-            if (*c == ',') ++c;
-        }
+        K = atoi(e);
+        if (K < 1 || K > 4096) return hipErrorInvalidValue;
     }
-    // Pass j runs the left parts (until every left part has had max_rows rows), the right parts
-    // appended by passes before j (the range between the snapshots of the right-task counts taken
-    // before passes j - 1 and j) and the right parts continuing from pass j - 1; it ends when the
-    // right parts appended by the last left pass have had max_rows rows.  Continuation counts
-    // rotate over three buffers per side: pass j reads c[j % 3], writes c[(j + 1) % 3] (cleared
-    // by pass j - 1, or at the start) and clears c[(j + 2) % 3] (read by pass j - 1).
-    bool left = true;
-    int done_l = 0, done_r = 0;
-    for (int pass = 0;; ++pass) {
-        const int K = nsched ? sched[pass < nsched ? pass : nsched - 1]
-                             : (pass == 0 ? 16 : std::min(512, 16 << (pass - 1)));
-        if (pass > 0)
-            hipLaunchKernelGGL(k_copy_u32, dim3(1), dim3(256), 0, s, snap[pass % 2], right_cnt, 256);
-        ContPass P{};
-        if (left) {
-            P.fin_l = pass == 0 ? cands : nullptr;
-            P.cin_l = pass == 0 ? nullptr : cont_l[pass % 2];
-            P.cnt_l = pass == 0 ? slot_cnt : cl[pass % 3];
-            P.cout_l = cont_l[(pass + 1) % 2];
-            P.cout_l_cnt = cl[(pass + 1) % 3];
-            P.zero_l = cl[(pass + 2) % 3];
-            P.rout = right;
-            P.rout_cnt = right_cnt;
-        }
-        if (pass > 0) {
-            P.fin_r = right;
-            P.lo_r = snap[(pass + 1) % 2];      // snap[0] is zero before pass 2
-            P.hi_r = snap[pass % 2];
-            P.cin_r = cont_r[pass % 2];
-            P.cnt_r = cr[pass % 3];
-        }
-        P.cout_r = cont_r[(pass + 1) % 2];
-        P.cout_r_cnt = cr[(pass + 1) % 3];
-        P.zero_r = cr[(pass + 2) % 3];
-        P.off = off;
-        P.K = K;
-        hipLaunchKernelGGL(k_verify_cont, dim3(grid), dim3(64), 0, s, V, div, P);
-        if (left) {
-            done_l += K;
-            if (done_l >= max_rows) left = false;
-        } else {
-            done_r += K;
-            if (done_r >= max_rows) break;
-        }
-    }
+    hipLaunchKernelGGL(k_verify_first, dim3(grid), dim3(64), 0, s, V, div, cands, slot_cnt, off, K,
+                       left, left_cnt, right, right_cnt);
+    hipLaunchKernelGGL(k_verify_far, dim3(grid), dim3(kBlock), 0, s, V, div, 0, left, left_cnt, off,
+                       right, right_cnt);
+    hipLaunchKernelGGL(k_verify_far, dim3(grid), dim3(kBlock), 0, s, V, div, 1, right, right_cnt, off,
+                       (LongRec*)nullptr, (uint32_t*)nullptr);
     return hipGetLastError();
 }
 

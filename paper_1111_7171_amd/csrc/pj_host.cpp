@@ -1093,8 +1093,8 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
                     vs.ncand = nc;
                     vs.y_maxlen = class_maxlen(c, Y.lmax);
                     if (long_c[c]) {
-                        hip_check(launch_verify_long(vs, nc, std::max(P.lmax, Y.lmax), lsc,
-                                                     device_cus() * 8, st), "verify_long");
+                        hip_check(launch_verify_long(vs, nc, lsc, device_cus() * 8, st),
+                                  "verify_long");
                     } else {
                         vs.wave_rounds = rounds_c[c];
                         const uint64_t nchunks = batched_chunks(nc, vs.wave_rounds);
