@@ -3179,10 +3179,11 @@ hipError_t launch_fill_words(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s)
     return hipGetLastError();
 }
 
-// Checksum of a device string set: offsets[0 .. n] and bytes[0 .. min(offsets[n], cap)), each
-// element mixed with its index (SplitMix64's finaliser) and summed.  A plan compares it with the
-// value taken when it was made; cap (the bytes allocation measured then) bounds the reads
-// whatever offsets[n] holds now.
+// Checksum of a device string set: offsets[0 .. n] and bytes[0 .. min(offsets[n], cap)) as 8-byte words
+// (the last padded with zeros), each element mixed (SplitMix64's finaliser; words before and after
+// their index is added) and summed.  A plan compares it with the value taken when it was made; cap
+// (the bytes allocation measured then) bounds the reads whatever offsets[n] holds now.  10^6 short
+// strings: byte by byte, with an atomic a wave, 114 us, 16 bytes at a time and an atomic a block 19.
 __global__ __launch_bounds__(kBlock) void k_set_checksum(const int32_t* __restrict__ offs, int64_t n,
                                                          const uint8_t* __restrict__ bytes,
                                                          int64_t cap,
@@ -3194,10 +3195,23 @@ __global__ __launch_bounds__(kBlock) void k_set_checksum(const int32_t* __restri
     const int64_t stride = (int64_t)gridDim.x * kBlock;
     for (int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x; k <= n; k += stride)
         acc += mix64((uint64_t)(uint32_t)offs[k] ^ ((uint64_t)k << 32) ^ 0x243F6A8885A308D3ull);
-    for (int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x; k < total; k += stride)
-        acc += mix64((uint64_t)bytes[k] ^ ((uint64_t)k << 8) ^ 0x13198A2E03707344ull);
-    acc = wave_sum(acc);
-    if ((threadIdx.x & 63) == 0 && acc) atomicAdd(sum, (unsigned long long)acc);
+    auto word = [&](uint64_t v, uint64_t index) {
+        acc += mix64(mix64(v ^ 0x13198A2E03707344ull) + index * 0x9E3779B97F4A7C15ull);
+    };
+    for (int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x; 16 * k < total; k += stride) {
+        uint64_t v[2] = {0, 0};
+        if (16 * k + 16 <= total) {
+            const Unaligned16 c = *reinterpret_cast<const Unaligned16*>(bytes + 16 * k);
+            v[0] = (uint64_t)c.w[1] << 32 | c.w[0];
+            v[1] = (uint64_t)c.w[3] << 32 | c.w[2];
+        } else {
+            for (int64_t q = 16 * k; q < total; ++q)
+                v[(q >> 3) & 1] |= (uint64_t)bytes[q] << (8 * (q & 7));
+        }
+        word(v[0], (uint64_t)(2 * k));
+        word(v[1], (uint64_t)(2 * k + 1));
+    }
+    block_add(sum, acc);
 }
 
 hipError_t launch_set_checksum(const int32_t* offs, int64_t n, const uint8_t* bytes, int64_t cap,
@@ -3205,7 +3219,7 @@ hipError_t launch_set_checksum(const int32_t* offs, int64_t n, const uint8_t* by
 {
     hipLaunchKernelGGL(k_fill_words, dim3(1), dim3(kBlock), 0, s, (uint32_t*)sum, (uint64_t)2, 0u);
     const unsigned grid = (unsigned)std::max<uint64_t>(
-        1, std::min<uint64_t>(blocks_for((uint64_t)n + 1), 2048));
+        1, std::min<uint64_t>(blocks_for((uint64_t)n + 1), 1024));
     hipLaunchKernelGGL(k_set_checksum, dim3(grid), dim3(kBlock), 0, s, offs, n, bytes, cap, sum);
     return hipGetLastError();
 }
