@@ -523,17 +523,19 @@ __global__ __launch_bounds__(kBlock) void k_probe(ProbeParams P, Div div)
 // waves look into the groups of a few lengths, whose directory and records stay in L2.  The strings
 // are staged in lane slots of an odd number of words, so reads at one offset hit distinct banks.
 // What bounds it is the random 8- and 16-byte reads of directory and records and, where most
-// lookups hit, the atomic per 256 hits that reserves their place.  Probe of 10^6 short strings at
-// tau = 1 / 2 / 4: 0.37 / 0.64 / 2.62 ms string-major, 0.09 / 0.30 / 2.17 here; 5x10^5 query lines at
-// tau = 6 1.48 -> 0.67 ms.
+// lookups hit, the atomic that reserves the places of a wave's HITS hits (6 ns each on one address):
+// 512 from tau = 2 on in slots of up to 64 bytes, although a CU then holds three blocks and not six.
+// Probe of 10^6 short strings at tau = 1 / 2 / 4: 0.37 / 0.64 / 2.62 ms string-major, here 0.096 /
+// 0.30 / 2.17 with 256 hits and 0.108 / 0.22 / 1.14 with 512; 5x10^5 query lines at tau = 6 1.48 ms,
+// 0.67 and 0.62, at tau = 8 2.04 and 1.46.
 constexpr int kTileStep = 4;       // window positions in flight
 constexpr uint32_t kStripes = 32;  // four an XCD: lengths differ in work
 
-template <int MAXQ>
+template <int MAXQ, int HITS>
 __global__ __launch_bounds__(kBlock) void k_probe_tiles(ProbeParams P, Div div, ProbeTiles T)
 {
     constexpr int SW = 4 * MAXQ + 1;               // words of a lane's slot
-    __shared__ Hit s_hits[kWaves][kAppendCap];
+    __shared__ Hit s_hits[kWaves][HITS];
     __shared__ uint32_t s_x[kWaves][64 * SW];
     __shared__ uint16_t s_sym[256];
     s_sym[threadIdx.x] = P.sym.code[threadIdx.x];
@@ -541,7 +543,7 @@ __global__ __launch_bounds__(kBlock) void k_probe_tiles(ProbeParams P, Div div, 
     const int sym_bits = P.sym.bits, exact_len = P.sym.exact_len;
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    WaveAppender<Hit, kAppendCap> app{s_hits[w], 0};
+    WaveAppender<Hit, HITS> app{s_hits[w], 0};
     uint32_t* slot = s_x[w] + lane * SW;
     using LdsU8 = const __attribute__((address_space(3))) uint8_t*;
     const LdsU8 xs = (LdsU8)slot;
@@ -2612,9 +2614,13 @@ hipError_t launch_probe_tiles(const ProbeParams& P, const ProbeTiles& T, int max
     const dim3 grid((unsigned)std::min<uint64_t>(((units + kWaves - 1) / kWaves + 7) / 8 * 8,
                                                  (uint64_t)std::max(max_blocks / 8 * 8, 8)));
     const Div div = make_div(P.tau + 1);
-    if (T.maxlen <= 32) hipLaunchKernelGGL(k_probe_tiles<2>, grid, dim3(kBlock), 0, s, P, div, T);
-    else if (T.maxlen <= 64) hipLaunchKernelGGL(k_probe_tiles<4>, grid, dim3(kBlock), 0, s, P, div, T);
-    else hipLaunchKernelGGL(k_probe_tiles<8>, grid, dim3(kBlock), 0, s, P, div, T);
+#define PJ_TILES(MAXQ, HITS)                                                                       \
+    hipLaunchKernelGGL((k_probe_tiles<MAXQ, HITS>), grid, dim3(kBlock), 0, s, P, div, T)
+    const bool many = P.tau >= 2;              // hits: see the kernel
+    if (T.maxlen <= 32) { if (many) PJ_TILES(2, 512); else PJ_TILES(2, 256); }
+    else if (T.maxlen <= 64) { if (many) PJ_TILES(4, 512); else PJ_TILES(4, 256); }
+    else PJ_TILES(8, 256);
+#undef PJ_TILES
     return hipGetLastError();
 }
 
