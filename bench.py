@@ -48,7 +48,8 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-DEVICE_SOURCES = ("pj_device.hip", "pj_device_common.h", "pj_internal.h")
+DEVICE_SOURCES = ("pj_device.hip", "pj_sort.hip", "pj_automaton.hip", "pj_automaton.h",
+                  "pj_device_common.h", "pj_internal.h")
 
 
 def kernel_source_sha() -> str:
@@ -398,7 +399,7 @@ def main():
     cells = sum(s["cells"] for _, s in stats)
     verify_ms = sum(s["ms_verify_kernel"] for _, s in stats)
     probe_ms = sum(s["ms_probe_kernel"] for _, s in stats)
-    # the dominant kernel: list-segment verification (k_verify_segs)
+    # the dominant kernel: list-segment verification (k_verify_auto or k_verify_segs)
     list_ms = sum(s["ms_list_kernel"] for _, s in stats)
     list_cells = sum(s["list_cells"] for _, s in stats)
     list_launches = sum(s["list_launches"] for _, s in stats)
@@ -467,16 +468,19 @@ def main():
         graph["host_syncs_per_call"] = 2
 
     sha = kernel_source_sha()
-    # dominant verification kernel: the list-segment kernel (k_verify_segs) when it takes most
-    # of the verification time, else candidate by candidate verification -- the long-string
-    # path (k_verify_cont passes, indexed strings longer than 128 bytes) or k_verify_batched.
-    # Algorithmic work = OPS_PER_CELL integer ops per DP cell the kernel evaluates (counted on
-    # the device per kernel).
+    # dominant verification kernel: the list-segment kernel (k_verify_auto, k_verify_segs) when
+    # it takes most of the verification time, else candidate by candidate verification -- the
+    # long-string path (k_verify_far, indexed strings longer than 128 bytes) or k_verify_batched.
+    # Algorithmic work = OPS_PER_CELL integer ops per DP cell of the rows a candidate's DP has
+    # (counted on the device per kernel; the table and furthest-row kernels get a row's outcome
+    # without its cells).
     other_ms = max(verify_ms - list_ms, 0.0)
     if list_ms >= other_ms and list_launches > 0:
-        rk, k_ms, k_cells, k_launches = "k_verify_segs", list_ms, list_cells, list_launches
+        # (tau <= 4 and strings of up to 47 bytes: the parts as table reads)
+        rk = "k_verify_auto" if max(taus) <= 4 else "k_verify_segs"
+        k_ms, k_cells, k_launches = list_ms, list_cells, list_launches
     else:
-        rk = "k_verify_cont" if int(col.lengths().max(initial=0)) > 128 else "k_verify_batched"
+        rk = "k_verify_far" if int(col.lengths().max(initial=0)) > 128 else "k_verify_batched"
         k_ms, k_cells = other_ms, cells - list_cells
         k_launches = len(stats)      # one verification call per self-join
     per_launch_s = k_ms / 1e3 / max(k_launches, 1)

@@ -1,5 +1,5 @@
 // pj_device_common.h -- device helpers of libpassjoin: even partition, multi-match windows,
-// segment hashing, index keys, bucket-table lookup and the banded verification DP.
+// segment hashing, index keys, directory lookup, chunk tickets and the banded verification DP.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -570,7 +570,7 @@ struct ByteStream<const uint8_t*> {
 // be any here).  The band's column characters sit in a register window that shifts by one per
 // row.  The cells of the rows evaluated follow in closed form.  P is a byte pointer into global
 // memory or LDS.  A byte load from global memory per row and string had bounded the rows of long
-// parts (0.5 us a row): 64 queries of a lookup service 70 -> 31 us in this kernel.
+// parts (0.5 us a row): k_verify_batched of 64 queries 79 -> 56 us.
 template <int MAXW, typename P>
 __device__ inline int vsp_fast(P r, int lr, P s, int ls, int t, int* cells)
 {

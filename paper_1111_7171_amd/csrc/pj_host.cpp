@@ -1051,8 +1051,8 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
             vp.shards = kStatShards;
             int k0 = tm.mark();
             if (batched) {
-                // small lists, one launch per length class: long strings by row blocks with
-                // compacted continuation queues, the others a candidate per lane
+                // small lists, one launch per length class: long strings by a first pass of rows and
+                // furthest rows, the others a candidate per lane
                 bool long_c[kLenClasses] = {};
                 int rounds_c[kLenClasses] = {};
                 uint64_t max_chunks = 0, max_long = 0;

@@ -78,7 +78,7 @@ int64_t query_selections(const pj_index* idx, int n, int tau);
 // A small batch as one upload, five kernels and one read-back: the phases of a serving slot's
 // pipeline, whose sizes stay on the device, in buffers of the thread's workspace (the general path
 // reads sizes back between its phases, 25 launches and 6 synchronisations; 64 queries against 5x10^5
-// strings 315 -> 150 us).  Returns false, with nothing added, when the batch does not fit: more
+// strings 315 -> 164 us).  Returns false, with nothing added, when the batch does not fit: more
 // than kSmallQueries queries or their selections, bytes, candidates or accepted candidates beyond
 // the buffers.  Candidates beyond the bucketing threshold are left to the general path, whose list
 // kernels are made for them.
