@@ -213,13 +213,13 @@ void* Owned::take(size_t bytes)
 {
     int device = 0;
     hip_check(hipGetDevice(&device), "hipGetDevice");
+    BlockPool& pool = block_pool();            // (made here at the latest: ~Owned must not throw)
     blocks.reserve(blocks.size() + 1);
     size_t want = bytes;
     if (bytes <= kPoolLargest) {
         size_t step = 64u << 10;
         while (step * 16 <= bytes) step *= 2;
         want = (bytes + step - 1) / step * step;
-        BlockPool& pool = block_pool();
         std::lock_guard<std::mutex> lk(pool.mu);
         size_t best = pool.blocks.size();
         for (size_t k = 0; !blocks.empty() && k < pool.blocks.size(); ++k) {
