@@ -294,17 +294,18 @@ int pj_server_stop(pj_server* srv);
  * lane verifies at once. */
 typedef struct {
     int32_t verify_waves_per_cu;   /* 8, 16, 32, ..., 1024, powers of two (default 32) */
-    int32_t seg_chunk;             /* 1, 2, 4, ..., 2048, powers of two (default 4; calls without
-                                      a tuned setting choose it by the number of segments) */
+    int32_t seg_chunk;             /* 1, 2, 4, ..., 2048, powers of two (default 4, which stands
+                                      for: by the number of segments, from 4 up) */
     int32_t big_list;              /* 16, 32, 64 or 128 (default 32) */
     int32_t probe_blocks_per_cu;   /* 4, 8 or 16 (default 8) */
     int32_t lane_cands;            /* list-segment candidates per lane: 1 or 2 (default 1) */
     int32_t probe_map;             /* probe threads: 0 a wave over consecutive (length, slot)
                                       pairs of a few probe strings, 1 a wave over 64 probe
-                                      strings with one pair (default 0) */
+                                      strings with one pair (default 1) */
     int32_t len_bucket;            /* key: bit length of the rounded mean string length */
     int32_t trials;                /* settings measured */
-    double ms_default;             /* probe + verification kernel time, built-in defaults */
+    double ms_default;             /* probe + verification time with the built-in defaults: what a
+                                      call without a setting takes */
     double ms_best;                /* the same for the chosen setting */
 } pj_tune_result;
 
@@ -312,10 +313,11 @@ typedef struct {
  * descent (repeated until a pass changes nothing, at most 3 passes), timing the probe and
  * verification phases on the device (best of two runs per setting), and
  * records the best setting under (this GPU's architecture, tau, length bucket of S's mean
- * length).  The record is kept for the rest of the process; when opt->tune_cache names a file
- * it is also merged into that file (plain text, one setting per line), which later calls with
- * the same tune_cache read.  opt->inputs_on_device must be 0.  Each trial runs the full
- * self-join, so the cost is about 40-100 joins of S.  Returns PJ_OK or a PJ_E* code. */
+ * length).  The search starts from the built-in defaults, which stay when nothing is faster.  The
+ * record is kept for the rest of the process; when opt->tune_cache names a file it is also merged
+ * into that file (plain text, one setting per line), which later calls with the same tune_cache
+ * read.  opt->inputs_on_device must be 0.  Each trial runs the full self-join, so the cost is about
+ * 40-100 joins of S.  Returns PJ_OK or a PJ_E* code. */
 int pj_tune(const pj_strings* S, int32_t tau, const pj_options* opt, pj_tune_result* out);
 
 /* Releases pairs (host or device memory as recorded in on_device) and zeroes the struct. */

@@ -32,14 +32,16 @@ constexpr size_t kPinnedOutputMin = 1u << 20;
 // Below this many candidates the batched path verifies the hits in probe order, in one launch.
 constexpr uint64_t kBucketMinCandidates = 1ull << 20;
 
-// List segments per wave chunk without a tuned setting.  A chunk sets its hits up anew, and its ticket
-// is an atomic on one of eight addresses (6-10 ns each, one after another): up to 32 segments a
-// chunk, all of them are handed out at the start, a chunk per wave of a full chip; beyond, waves take
-// more by ticket, and long runs take longer chunks.  Measured on short strings, list kernel, with 4 /
-// 8 / 32 / 128 segments: 10^6 at tau = 1 0.02, 0.03, 0.07, 0.19 ms; 10^5 at tau = 3 0.16, 0.13, 0.11,
-// 0.27; 2x10^5 at tau = 4 3.5, 1.9, 1.4, 1.4; 10^6 at tau = 4 with 32 / 128 / 256: 28.5, 25.8, 25.3.
-static int auto_seg_chunk(uint64_t nseg)
+// List segments per wave chunk: the setting, or for the default of 4 by the number of segments, from 4
+// up.  A chunk sets its hits up anew, and its ticket is an atomic on one of eight addresses (6-10 ns
+// each, one after another): up to 32 segments a chunk, all of them are handed out at the start, a
+// chunk per wave of a full chip; beyond, waves take more by ticket, and long runs take longer chunks.
+// Measured on short strings, list kernel, with 4 / 8 / 32 / 128 segments: 10^6 at tau = 1 0.02, 0.03,
+// 0.07, 0.19 ms; 10^5 at tau = 3 0.16, 0.13, 0.11, 0.27; 2x10^5 at tau = 4 3.5, 1.9, 1.4, 1.4; 10^6 at
+// tau = 4 with 32 / 128 / 256: 28.5, 25.8, 25.3.
+static int list_seg_chunk(const TuneParams& tp, uint64_t nseg)
 {
+    if (tp.seg_chunk != TuneParams{}.seg_chunk) return tp.seg_chunk;
     const uint64_t even = std::max<uint64_t>(4, std::min<uint64_t>((nseg + 8191) / 8192, 32));
     return (int)std::max<uint64_t>(even, std::min<uint64_t>(nseg / 131072, 256));
 }
@@ -818,10 +820,11 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
         pp.selection = spec.selection;
         // a uniform threshold: strings of up to kTileMaxLen bytes pair-major, a wave per 64 of one
         // length (unless a tuned setting or a test asks for the string-major kernel), longer ones a
-        // block each.  Query batches and the plain path take the string-major kernel.
+        // block each.  Query batches and the plain path take the string-major kernel.  The default
+        // is what the tuner starts from: 10^6 short strings, probe at tau = 1 / 4, string-major 0.37 /
+        // 2.62 ms, pair-major 0.10 / 1.14.
         const int max_blocks = device_cus() * J.tp.probe_blocks_per_cu;
-        bool split = !spec.q_tau && J.mode != PJ_MODE_PLAIN &&
-                     !(J.tp.tuned && J.tp.probe_map == 0);
+        bool split = !spec.q_tau && J.mode != PJ_MODE_PLAIN && J.tp.probe_map == 1;
         // tests force either kernel (it changes no result)
         if (const char* e = getenv("PJ_PROBE_XMAJOR")) split = atoi(e) != 0 && !spec.q_tau;
         if (!split && !spec.q_tau && spec.selection == PJ_SELECT_MULTIMATCH && J.mode != PJ_MODE_PLAIN) {
@@ -1127,7 +1130,7 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
                 uint64_t max_seg_chunks = 0;
                 for (int c = 0; c < kLenClasses; ++c) {
                     if (cls_nseg[c] == 0) continue;
-                    chunk_c[c] = J.tp.tuned ? J.tp.seg_chunk : auto_seg_chunk(cls_nseg[c]);
+                    chunk_c[c] = list_seg_chunk(J.tp, cls_nseg[c]);
                     max_seg_chunks = std::max<uint64_t>(max_seg_chunks,
                                                         seg_chunks(cls_nseg[c], chunk_c[c]));
                 }

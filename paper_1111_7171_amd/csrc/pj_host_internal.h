@@ -114,13 +114,13 @@ struct Timer {
 // Launch parameters of the batched path that do not change results (chosen by the autotuner,
 // pj_tune.cpp; these are the built-in defaults).
 struct TuneParams {
-    bool tuned = false;             // set by the autotuner: seg_chunk is taken as it is
     int verify_waves_per_cu = 32;   // persistent grid of the verification kernels
-    int seg_chunk = 4;              // list segments (64 members each) per wave chunk
+    int seg_chunk = 4;              // list segments (64 members each) per wave chunk; 4: by their
+                                    // number (list_seg_chunk)
     int big_list = 32;              // lists with at least this many candidates: list-segment kernel
     int probe_blocks_per_cu = 8;    // grid of the probe kernel
     int lane_cands = 1;             // list-segment candidates per lane (1 or 2)
-    int probe_map = 0;              // probe threads: 0 string-major, 1 pair-major (64 strings)
+    int probe_map = 1;              // probe threads: 0 string-major, 1 pair-major (64 strings)
 };
 
 bool tune_params_valid(const TuneParams& p);

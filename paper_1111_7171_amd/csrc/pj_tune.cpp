@@ -9,12 +9,16 @@
 // events; the result goes to an in-process table and, when pj_options.tune_cache names a file,
 // to that file, which later calls read back.  The file is plain text:
 //
-//   # passjoin tune cache v3: arch tau len_bucket verify_waves_per_cu seg_chunk big_list
+//   # passjoin tune cache v4: arch tau len_bucket verify_waves_per_cu seg_chunk big_list
 //   #   probe_blocks_per_cu lane_cands probe_map ms
-//   gfx950 4 4 32 4 32 8 2 0 112.300
+//   gfx950 4 4 32 4 32 8 1 1 31.300
 //
-// Lines of the v2 format (without probe_map) read as probe_map 0.  Unknown or out-of-range
-// lines are ignored.  A file that changes on disk is read again.
+// The search starts from what a call without a setting does (TuneParams), so a setting is only kept
+// if it is faster than that.  Files of the formats before v4 (v2 has no probe_map) were measured with
+// other list kernels, probe mappings and chunk rules: of their lines only a list threshold below the
+// default is taken.  (Probe and verification of 10^6 short strings at tau = 2 / 4: defaults 1.20 / 30.5
+// ms; 8 waves a CU 1.91 / 85.9; threshold 16, 64 and 128 1.16 / 29.9, 1.31 / 33.0 and 1.44 / 38.2.)
+// Unknown or out-of-range lines are ignored.  A file that changes on disk is read again.
 #include <sys/stat.h>
 
 #include <algorithm>
@@ -101,24 +105,34 @@ void parse_file(const char* path, std::map<Key, Entry>& table)
     FILE* f = fopen(path, "r");
     if (!f) return;
     char line[512];
+    int version = 0;
     while (fgets(line, sizeof line, f)) {
-        if (line[0] == '#') continue;
+        if (line[0] == '#') {
+            (void)sscanf(line, "# passjoin tune cache v%d", &version);
+            continue;
+        }
         char arch[128];
         int tau, lb;
         Entry e;
-        e.p.tuned = true;
-        const int got = sscanf(line, "%127s %d %d %d %d %d %d %d %d %lf", arch, &tau, &lb,
+        // (a space after the last setting: else the whole part of a v2 line's time reads as one)
+        const int got = sscanf(line, "%127s %d %d %d %d %d %d %d %d%*[ \t]%lf", arch, &tau, &lb,
                                &e.p.verify_waves_per_cu, &e.p.seg_chunk, &e.p.big_list,
                                &e.p.probe_blocks_per_cu, &e.p.lane_cands, &e.p.probe_map, &e.ms);
         if (got != 10) {
             // v2: no probe_map column
-            e.p.probe_map = 0;
-            if (sscanf(line, "%127s %d %d %d %d %d %d %d %lf", arch, &tau, &lb,
+            e.p.probe_map = TuneParams{}.probe_map;
+            if (version >= 4 ||
+                sscanf(line, "%127s %d %d %d %d %d %d %d %lf", arch, &tau, &lb,
                        &e.p.verify_waves_per_cu, &e.p.seg_chunk, &e.p.big_list,
                        &e.p.probe_blocks_per_cu, &e.p.lane_cands, &e.ms) != 9)
                 continue;
         }
         if (tau < 0 || tau > kTauMax || lb < 0 || lb > 12 || !tune_params_valid(e.p)) continue;
+        if (version < 4) {
+            TuneParams p;
+            p.big_list = std::min(p.big_list, e.p.big_list);
+            e.p = p;
+        }
         table[Key(arch, tau, lb)] = e;
     }
     fclose(f);
@@ -145,7 +159,7 @@ void write_file(const char* path, const std::map<Key, Entry>& table)
     const std::string tmp = std::string(path) + ".tmp";
     FILE* f = fopen(tmp.c_str(), "w");
     if (!f) throw Error(PJ_EINVAL, "cannot write tune cache %s", path);
-    fprintf(f, "# passjoin tune cache v3: arch tau len_bucket verify_waves_per_cu seg_chunk "
+    fprintf(f, "# passjoin tune cache v4: arch tau len_bucket verify_waves_per_cu seg_chunk "
                "big_list probe_blocks_per_cu lane_cands probe_map ms\n");
     for (const auto& kv : table) {
         const Entry& e = kv.second;
@@ -222,8 +236,7 @@ int pj_tune(const pj_strings* S, int32_t tau, const pj_options* opt, pj_tune_res
             ++trials;
             return best;
         };
-        TuneParams cur;
-        cur.tuned = true;
+        TuneParams cur;                      // what a call without a setting does
         (void)measure(cur);                  // warm-up: allocations, code objects, caches
         const double ms_default = measure(cur);
         double ms_best = ms_default;
@@ -243,7 +256,7 @@ int pj_tune(const pj_strings* S, int32_t tau, const pj_options* opt, pj_tune_res
                 const auto k = key_of(cand);
                 const auto it = seen.find(k);
                 const double ms = it != seen.end() ? it->second : (seen[k] = measure(cand));
-                if (ms < ms_best) {
+                if (ms < 0.99 * ms_best) {       // (runs of one setting differ by about 1%)
                     ms_best = ms;
                     cur = cand;
                     changed = true;
