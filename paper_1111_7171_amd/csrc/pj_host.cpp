@@ -89,6 +89,15 @@ Workspace::~Workspace()
         if (kv.second.p) (void)hipFree(kv.second.p);
 }
 
+void Alloc::set_aside(const char* name, size_t bytes)
+{
+    bytes = (bytes + 255) & ~(size_t)255;
+    if (budget > 0 && used + aside + bytes > (size_t)budget)
+        throw Error(PJ_ENOMEM, "memory budget of %lld bytes exceeded (%s)", (long long)budget,
+                    name);
+    aside += bytes;
+}
+
 void* Workspace::get(const char* name, size_t bytes)
 {
     if (bytes == 0) bytes = 16;
@@ -210,7 +219,8 @@ Owned::~Owned()
 }
 
 // A block of at least the given bytes: one of the pool's that is at most a quarter larger, or a new
-// one, in steps of an eighth of its size so that the next object's fit.
+// one, in steps of an eighth of its size so that the next object's fit.  Under a budget, a new one of
+// just these bytes.
 void* Owned::take(size_t bytes)
 {
     int device = 0;
@@ -218,7 +228,7 @@ void* Owned::take(size_t bytes)
     BlockPool& pool = block_pool();            // (made here at the latest: ~Owned must not throw)
     blocks.reserve(blocks.size() + 1);
     size_t want = bytes;
-    if (bytes <= kPoolLargest) {
+    if (budget <= 0 && bytes <= kPoolLargest) {
         size_t step = 64u << 10;
         while (step * 16 <= bytes) step *= 2;
         want = (bytes + step - 1) / step * step;
@@ -234,6 +244,7 @@ void* Owned::take(size_t bytes)
             blocks.push_back(pool.blocks[best]);
             pool.bytes -= pool.blocks[best].cap;
             pool.blocks.erase(pool.blocks.begin() + (long)best);
+            used += blocks.back().cap;
             return blocks.back().p;
         }
     }
@@ -243,6 +254,7 @@ void* Owned::take(size_t bytes)
         return nullptr;
     }
     blocks.push_back(Block{p, want, device, 0});
+    used += want;
     return p;
 }
 
@@ -250,11 +262,11 @@ void* Owned::get(const char* name, size_t bytes)
 {
     if (bytes == 0) bytes = 16;
     bytes = (bytes + 255) & ~(size_t)255;
-    if (budget > 0 && used + bytes > (size_t)budget)
+    if (budget > 0 && used + aside + bytes > (size_t)budget)
         throw Error(PJ_ENOMEM, "memory budget of %lld bytes exceeded (%s)", (long long)budget,
                     name);
     void* p = nullptr;
-    if (bytes > kSmallMost) p = take(bytes);
+    if (budget > 0 || bytes > kSmallMost) p = take(bytes);
     else {
         if (chunk_left < bytes) {
             chunk = take(kSmallChunk);
@@ -267,7 +279,6 @@ void* Owned::get(const char* name, size_t bytes)
         }
     }
     if (!p) throw Error(PJ_ENOMEM, "hipMalloc(%zu) for %s failed", bytes, name);
-    used += bytes;
     return p;
 }
 
@@ -536,8 +547,12 @@ void build_set(const pj_strings* S, bool on_device, Alloc& A, const std::string&
         d_bytes = S->bytes;
     } else {
         total = S->offsets[n];
-        // (the index of a set reads neither again: scratch of the call)
+        // (the index of a set reads neither again: scratch of the call, which its budget counts)
         Workspace& W = thread_workspace();
+        if (&A != &W) {
+            A.set_aside("offs", sizeof(int32_t) * (size_t)(n + 1));
+            A.set_aside("bytes", (size_t)total + 16);
+        }
         int32_t* o = (int32_t*)W.get(nm("offs").c_str(), sizeof(int32_t) * (size_t)(n + 1));
         hip_check(hipMemcpyAsync(o, S->offsets, sizeof(int32_t) * (size_t)(n + 1),
                                  hipMemcpyHostToDevice, st), "upload offsets");
@@ -647,6 +662,8 @@ void build_index(const DevSet& D, int tau, Alloc& A, const std::string& tag, Dev
         return;
     }
     Workspace& W = thread_workspace();
+    AsideScope keys_aside(A);
+    if (&A != &W) A.set_aside("keys", sizeof(uint64_t) * (size_t)E);
     uint64_t* keys = (uint64_t*)W.get("index.keys", sizeof(uint64_t) * (size_t)E);
     uint32_t* vals = (uint32_t*)A.get(nm("vals").c_str(), sizeof(uint32_t) * (size_t)E);
     uint64_t* keys2 = (uint64_t*)W.get("index.keys2", sizeof(uint64_t) * (size_t)E);

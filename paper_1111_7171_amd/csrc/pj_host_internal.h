@@ -26,8 +26,10 @@ void hip_check(hipError_t e, const char* what);
 struct Alloc {
     long long budget = 0;   // 0 = unlimited
     size_t used = 0;        // bytes requested in the current call
+    size_t aside = 0;       // scratch of the call that lies elsewhere and counts against the budget
     virtual ~Alloc() = default;
     virtual void* get(const char* name, size_t bytes) = 0;
+    void set_aside(const char* name, size_t bytes);
 };
 
 // Grow-only named buffers cached per thread (scratch of one call at a time).
@@ -47,7 +49,8 @@ struct Workspace : Alloc {
 hipError_t device_malloc(void** p, size_t bytes);
 
 // Allocations owned by a long-lived object (an index); freed with it.  Small ones share chunks, and
-// the blocks of one object serve the next: unmapping a block of some 20 MB takes 300-700 us.
+// the blocks of one object serve the next: unmapping a block of some 20 MB takes 300-700 us.  `used`
+// is what the blocks hold.  Under a budget every allocation is a block of its size.
 struct Owned : Alloc {
     struct Block {
         void* p = nullptr;
@@ -63,6 +66,14 @@ struct Owned : Alloc {
 
 private:
     void* take(size_t bytes);
+};
+
+// Scratch counted against A's budget (in addition to what A holds) while the scope lasts.
+struct AsideScope {
+    Alloc& A;
+    const size_t before;
+    explicit AsideScope(Alloc& a) : A(a), before(a.aside) {}
+    ~AsideScope() { A.aside = before; }
 };
 
 Workspace& thread_workspace();
