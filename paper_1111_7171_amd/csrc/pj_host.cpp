@@ -724,7 +724,7 @@ void build_index(const DevSet& D, int tau, Alloc& A, const std::string& tag, Dev
     zero_words(bounds, sizeof(uint32_t) * 2 * (size_t)ngroups, st);
     zero_words(X.dir, sizeof(uint2) * entries, st);
     const size_t dsb = scan_tmp_bytes(ngroups);
-    void* dst = W.get("scan.tmp", std::max(dsb, sb));
+    void* dst = dsb > sb ? W.get("scan.tmp2", dsb) : stmp;
     hip_check(launch_list_dir(keys, runstart, nruns, (uint32_t)E, ngroups, bounds, words, dst, dsb,
                               X.recs, X.gdir, X.dir, st), "list_dir");
     if (with_share) {
@@ -804,6 +804,26 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
     // match), so start from a capped buffer and re-run the probe with the exact size if needed
     uint64_t hit_cap = std::min<uint64_t>(std::max<uint64_t>(bound, 1), 1ull << 26);
     const bool entries = spec.q_tau ? spec.has_entries : (spec.X && spec.X->entries > 0);
+    // a uniform threshold: strings of up to kTileMaxLen bytes pair-major, a wave per 64 of one
+    // length (unless a tuned setting or a test asks for the string-major kernel), longer ones a
+    // block each.  Query batches and the plain path take the string-major kernel.  The default
+    // is what the tuner starts from: 10^6 short strings, probe at tau = 1 / 4, string-major 0.37 /
+    // 2.62 ms, pair-major 0.10 / 1.14.
+    bool split = !spec.q_tau && J.mode != PJ_MODE_PLAIN && J.tp.probe_map == 1;
+    // tests force either kernel (it changes no result)
+    if (const char* e = getenv("PJ_PROBE_XMAJOR")) split = atoi(e) != 0 && !spec.q_tau;
+    const int nl = self ? T1 : 2 * tau + 1;
+    const int64_t first_long = std::max<int64_t>(P.h_lenstart[kTileMaxLen + 1], probe_first);
+    // The position list of the long strings' probe lies behind the hits.  Under a budget it takes the
+    // last records' place, so that a call needs no more memory than without the list; where the
+    // buffer is too small for that, or the hits reach the list, the string-major kernel takes the
+    // long strings.
+    uint64_t item_recs = 0;                    // the list, in hit records
+    const uint64_t item_words = probe_item_count(tau, nl, self ? 1 : 0);
+    const bool lent = W.budget > 0;
+    if (split && first_long < P.n && spec.selection == PJ_SELECT_MULTIMATCH)
+        item_recs = ((item_words + kItemChunks + 1) * sizeof(uint32_t) + sizeof(Hit) - 1) / sizeof(Hit);
+    if (lent && 2 * item_recs > hit_cap) item_recs = 0;
     int t_probe0 = tm.mark();
     unsigned long long c[kJoinCounters];
     // c[0 .. kCounterLine): the counters, each with its statistics lines added
@@ -811,15 +831,21 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
         for (int k = 0; k < kCounterLine; ++k)
             for (int l = 1; l <= kStatShards; ++l) c[k] += c[l * kCounterLine + k];
     };
+    uint64_t held = 0, room = 0;               // records of the buffer, and those for hits
     for (int attempt = 0; attempt < 2; ++attempt) {
-    J.hits = (Hit*)W.get("join.hits", sizeof(Hit) * (size_t)hit_cap);
+    const uint64_t want = hit_cap + (lent ? 0 : item_recs);
+    if (want > held) {
+        J.hits = (Hit*)W.get("join.hits", sizeof(Hit) * (size_t)want);
+        held = want;
+    }
+    room = held - item_recs;
     if (attempt > 0)
         zero_words(J.counters, kJoinCounters * sizeof(unsigned long long), st);
     if (nprobe > 0 && bound > 0 && entries) {
         ProbeParams pp{};
         pp.x_arena = P.sarena; pp.x_slen = P.slen; pp.x_lenstart = P.lenstart; pp.x_gbase = P.gbase;
         pp.g_begin = (uint32_t)probe_first;
-        pp.nl = self ? T1 : 2 * tau + 1;
+        pp.nl = nl;
         pp.threads = (uint64_t)nprobe * (uint64_t)pp.nl * (uint64_t)T1;
         pp.self = self ? 1 : 0;
         pp.q_tau = spec.q_tau;
@@ -835,15 +861,7 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
         pp.ymin = Y.lmin; pp.ymax = Y.lmax;
         pp.sym = spec.sym;
         pp.selection = spec.selection;
-        // a uniform threshold: strings of up to kTileMaxLen bytes pair-major, a wave per 64 of one
-        // length (unless a tuned setting or a test asks for the string-major kernel), longer ones a
-        // block each.  Query batches and the plain path take the string-major kernel.  The default
-        // is what the tuner starts from: 10^6 short strings, probe at tau = 1 / 4, string-major 0.37 /
-        // 2.62 ms, pair-major 0.10 / 1.14.
         const int max_blocks = device_cus() * J.tp.probe_blocks_per_cu;
-        bool split = !spec.q_tau && J.mode != PJ_MODE_PLAIN && J.tp.probe_map == 1;
-        // tests force either kernel (it changes no result)
-        if (const char* e = getenv("PJ_PROBE_XMAJOR")) split = atoi(e) != 0 && !spec.q_tau;
         if (!split && !spec.q_tau && spec.selection == PJ_SELECT_MULTIMATCH && J.mode != PJ_MODE_PLAIN) {
             // the (length, slot) pairs grouped by window size, so a wave's lanes walk windows of
             // one size (the plain path keeps the natural order: it is the unscheduled baseline)
@@ -852,7 +870,7 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
             hip_check(launch_probe_order(tau, pp.nl, pp.self, order, st), "probe_order");
             pp.order = order;
         }
-        pp.hits = J.hits; pp.hit_cap = hit_cap;
+        pp.hits = J.hits; pp.hit_cap = room;
         pp.counters = J.counters;
         pp.shards = kStatShards;
         int k0 = tm.mark();
@@ -876,15 +894,11 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
                                                      std::max<uint32_t>(T.tiles, 1)));
                 hip_check(launch_probe_tiles(pp, T, max_blocks, st), "probe_tiles");
             }
-            const int cut = kTileMaxLen + 1;                 // first length of the long ones
-            const int64_t first_long = std::max<int64_t>(P.h_lenstart[cut], probe_first);
-            if (first_long < P.n && spec.selection == PJ_SELECT_MULTIMATCH) {
+            if (item_recs > 0) {
                 ProbeItems I{};
                 I.chunks = (int)((pairs + kItemPairs - 1) / kItemPairs);
-                uint32_t* items = (uint32_t*)W.get(
-                    "probe.items", sizeof(uint32_t) * (size_t)probe_item_count(tau, pp.nl, pp.self));
-                uint32_t* chunk = (uint32_t*)W.get("probe.chunk",
-                                                   sizeof(uint32_t) * (kItemChunks + 1));
+                uint32_t* items = (uint32_t*)(J.hits + room);
+                uint32_t* chunk = items + item_words;
                 hip_check(launch_probe_items(tau, pp.nl, pp.self, items, chunk, st), "probe_items");
                 I.items = items;
                 I.chunk = chunk;
@@ -908,7 +922,8 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
     readback(c, J.counters, sizeof c, st);
     sync_readback(st);
     add_lines();
-    if (c[0] <= hit_cap) break;
+    if (c[0] <= room) break;
+    if (lent) item_recs = 0;
     hit_cap = c[0];
     J.kernel_marks.clear();
     }
@@ -918,8 +933,8 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
     stats.selected += (int64_t)c[2];
     stats.hits += (int64_t)c[0];
     stats.candidates += (int64_t)c[1];
-    if (J.nhits > hit_cap) throw Error(PJ_EDEVICE, "hit buffer overflow (%llu > %llu)",
-                                       (unsigned long long)J.nhits, (unsigned long long)hit_cap);
+    if (J.nhits > room) throw Error(PJ_EDEVICE, "hit buffer overflow (%llu > %llu)",
+                                    (unsigned long long)J.nhits, (unsigned long long)room);
 
     const bool batched = J.mode != PJ_MODE_PLAIN;
     // batched: hits bucketed into [lists with < big_list candidates | the others], each part by
