@@ -240,7 +240,7 @@ typedef struct {
     int32_t slots;              /* device batches in flight at once, >= 1 */
     int32_t max_batch_queries;  /* queries merged into one device batch, >= 1 */
     int64_t mem_budget_bytes;   /* bound on the summed footprint estimates in flight plus the
-                                   slots' fixed buffers (captured mode: about 33 MB per slot,
+                                   slots' fixed buffers (captured mode: about 34 MB per slot,
                                    taken off the budget at start; PJ_ENOMEM if they do not fit);
                                    0 = none.  The estimate leaves out each batch's accepted-
                                    candidate buffer (8 B per candidate, known only after the

@@ -255,6 +255,8 @@ GraphPlan* graph_plan_create(const pj_index* idx, int max_queries, hipStream_t s
     g->st = st;
     g->L = batch_layout(max_queries, kPlanHits, kPlanCands, kPlanAccepted);
     const BatchLayout& L = g->L;
+    // a block of just these bytes: the server's budget counts them as graph_plan_device_bytes does
+    g->mem.budget = (long long)batch_device_bytes(L);
     uint8_t* base = (uint8_t*)g->mem.get("graph.buffers", batch_device_bytes(L));
     g->B = carve_batch_buffers(L, base);
     hip_check(hipHostMalloc((void**)&g->h_tables, L.tables_bytes + L.arena_bytes,
