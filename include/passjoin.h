@@ -323,8 +323,14 @@ int pj_tune(const pj_strings* S, int32_t tau, const pj_options* opt, pj_tune_res
 /* Releases pairs (host or device memory as recorded in on_device) and zeroes the struct. */
 void pj_pairs_free(pj_pairs* pairs);
 
-/* Releases an index; NULL is ignored. */
+/* Releases an index; NULL is ignored.  The library keeps up to 512 MiB of the device memory of freed
+ * indexes for the next ones: until four more have been freed without using it, until an allocation of
+ * the library's own would fail, or until pj_memory_trim. */
 void pj_index_free(pj_index* idx);
+
+/* Gives the device memory kept from freed indexes back to the driver (for a process whose other users
+ * of the device need it).  Indexes in use are not touched. */
+void pj_memory_trim(void);
 
 /* Text describing the last failure on the calling thread ("" if none). */
 const char* pj_last_error(void);

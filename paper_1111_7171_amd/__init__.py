@@ -20,7 +20,7 @@ import numpy as np
 
 __all__ = [
     "PassJoinError", "load", "pj_self_join", "pj_join", "pj_build_index", "pj_query",
-    "pj_index_info", "pj_index_free", "pj_last_error", "pj_last_stats", "pj_version",
+    "pj_index_info", "pj_index_free", "pj_memory_trim", "pj_last_error", "pj_last_stats", "pj_version",
     "MODE_AUTO", "MODE_PLAIN", "MODE_BATCHED", "MODE_SHARE_PREFIX", "PJ_TAU_MAX", "PJ_LEN_MAX",
     "Server", "Index",
     "pj_tune", "pj_query_noalloc", "pj_self_join_host", "HostPairs", "Plan",
@@ -127,6 +127,8 @@ def load():
         lib.pj_pairs_free.restype = None
         lib.pj_index_free.argtypes = [C.c_void_p]
         lib.pj_index_free.restype = None
+        lib.pj_memory_trim.argtypes = []
+        lib.pj_memory_trim.restype = None
         lib.pj_last_error.argtypes = []
         lib.pj_last_error.restype = C.c_char_p
         lib.pj_last_stats.argtypes = [C.POINTER(PjStats)]
@@ -453,6 +455,11 @@ def pj_index_info(index: Index) -> dict:
 
 def pj_index_free(index: Index):
     index.free()
+
+
+def pj_memory_trim():
+    """Gives the device memory kept from freed indexes back to the driver."""
+    load().pj_memory_trim()
 
 
 def pj_query(index: Index, queries, taus, *, outputs_on_device: bool = False,

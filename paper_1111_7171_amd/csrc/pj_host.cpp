@@ -135,9 +135,9 @@ void Workspace::release_all()
 // time to time would map and unmap the same memory each time (3x10^5 strings at four thresholds
 // built, queried once and freed: 6.2 ms with that, 2.2 ms without).  Blocks serve the device that
 // they lie on; at most kPoolBytes are kept, none above kPoolLargest, and none that the last
-// kPoolAge frees had no successor for; all are given back before an allocation fails.  A block
-// enters after the implicit wait of hipFree, so no work on any stream still uses it, and under the
-// mutex.
+// kPoolAge frees had no successor for; all are given back before an allocation fails and by
+// pj_memory_trim.  A block enters after the implicit wait of hipFree, so no work on any stream still
+// uses it, and under the mutex.
 namespace {
 
 constexpr size_t kPoolBytes = 512u << 20;
@@ -166,10 +166,9 @@ void give_back(const std::vector<Owned::Block>& blocks)
 
 }  // namespace
 
-hipError_t device_malloc(void** p, size_t bytes)
+// whether there was anything to give back
+static bool empty_pool()
 {
-    hipError_t e = hipMalloc(p, bytes);
-    if (e != hipErrorOutOfMemory) return e;
     std::vector<Owned::Block> out;
     {
         BlockPool& pool = block_pool();
@@ -177,10 +176,16 @@ hipError_t device_malloc(void** p, size_t bytes)
         out.swap(pool.blocks);
         pool.bytes = 0;
     }
-    if (out.empty()) return e;
-    (void)hipGetLastError();
     give_back(out);
-    return hipMalloc(p, bytes);
+    return !out.empty();
+}
+
+hipError_t device_malloc(void** p, size_t bytes)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();
+    return empty_pool() ? hipMalloc(p, bytes) : e;
 }
 
 Owned::~Owned()
@@ -1973,6 +1978,14 @@ void pj_pairs_free(pj_pairs* p)
     p->a = p->b = nullptr;
     p->count = 0;
     p->on_device = 0;
+}
+
+void pj_memory_trim(void)
+{
+    try {
+        empty_pool();
+    } catch (const std::bad_alloc&) {        // the first use of the pool: nothing to give back
+    }
 }
 
 const char* pj_last_error(void) { return t_last_error.c_str(); }
