@@ -837,7 +837,14 @@ void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, Joi
             for (int l = 1; l <= kStatShards; ++l) c[k] += c[l * kCounterLine + k];
     };
     uint64_t held = 0, room = 0;               // records of the buffer, and those for hits
-    for (int attempt = 0; attempt < 2; ++attempt) {
+    if (spec.probed) {
+        J.hits = spec.probed->hits;
+        hip_check(hipMemcpyAsync(J.counters, spec.probed->counters, sizeof spec.probed->counts,
+                                 hipMemcpyDeviceToDevice, st), "probed counters");
+        std::copy(spec.probed->counts, spec.probed->counts + 3, c);
+        room = c[0];
+    }
+    for (int attempt = 0; attempt < 2 && !spec.probed; ++attempt) {
     const uint64_t want = hit_cap + (lent ? 0 : item_recs);
     if (want > held) {
         J.hits = (Hit*)W.get("join.hits", sizeof(Hit) * (size_t)want);

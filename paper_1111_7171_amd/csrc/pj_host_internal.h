@@ -158,6 +158,13 @@ void build_set(const pj_strings* S, bool on_device, Alloc& A, const std::string&
                hipStream_t st, bool with_sym = false);
 void build_index(const DevSet& D, int tau, Alloc& A, const std::string& tag, DevIndex& X,
                  hipStream_t st, bool with_inline = false, bool with_share = false);
+// The hits of a query batch that has been probed: records, the probe's counters on the device and here
+// ([0] hits, [1] candidates, [2] selected).
+struct ProbedHits {
+    Hit* hits = nullptr;
+    const unsigned long long* counters = nullptr;
+    uint64_t counts[3] = {};
+};
 // What to probe: a uniform tau against one index, or per-probe thresholds (q_tau, by sorted
 // position of the probe set) against the per-tau indices in refs.
 struct ProbeSpec {
@@ -171,6 +178,7 @@ struct ProbeSpec {
     bool has_entries = true;           // some index has entries
     int selection = 0;                 // PJ_SELECT_*
     int probe_min_len = 0;             // self-join: only strings at least this long probe
+    const ProbedHits* probed = nullptr;   // a batch probed already: only the rest
 };
 
 void run_candidates(const DevSet& P, const DevSet& Y, const ProbeSpec& spec, JoinScratch& J,

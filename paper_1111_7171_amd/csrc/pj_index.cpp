@@ -75,22 +75,71 @@ static void to_host(const pj_strings* Q, bool on_device, HostStrings& H)
 
 int64_t query_selections(const pj_index* idx, int n, int tau);
 
+static TuneParams query_params(const pj_strings* Q, int tmax, const char* tune_cache)
+{
+    return tune_lookup(tune_cache, tmax, Q->n ? (double)(Q->offsets[Q->n] - Q->offsets[0]) / (double)Q->n
+                                             : 0.0);
+}
+
+// Sorts and deduplicates accepted (gx, gy) and appends the pairs of ids.
+static void append_pairs(const pj_index* idx, const DevSet& P, const uint64_t* acc, uint64_t m,
+                         std::vector<uint64_t>& pairs, hipStream_t st)
+{
+    int32_t *da = nullptr, *db = nullptr;
+    uint64_t M = finish_pairs(P, idx->S, false, acc, m, &da, &db, st);
+    std::vector<int32_t> ha(M), hb(M);
+    if (M) {
+        hip_check(hipMemcpyAsync(ha.data(), da, sizeof(int32_t) * M, hipMemcpyDeviceToHost, st), "d2h");
+        hip_check(hipMemcpyAsync(hb.data(), db, sizeof(int32_t) * M, hipMemcpyDeviceToHost, st), "d2h");
+    }
+    hip_check(hipStreamSynchronize(st), "sync");
+    pairs.reserve(pairs.size() + M);
+    for (uint64_t k = 0; k < M; ++k)
+        pairs.push_back(((uint64_t)(uint32_t)ha[k] << 32) | (uint32_t)hb[k]);
+}
+
+// The general path of a batch whose strings and thresholds (d_tau, by sorted position) are on the
+// device; probed: its hits, if it has been probed.
+static void join_queries(const pj_index* idx, const DevSet& P, const int32_t* d_tau, int tmax,
+                         uint64_t bound, const ProbedHits* probed, const TuneParams& tp,
+                         std::vector<uint64_t>& pairs, pj_stats& stats, Timer& tm, hipStream_t st)
+{
+    ProbeSpec spec;
+    spec.self = false;
+    spec.tau = tmax;
+    spec.q_tau = d_tau;
+    spec.refs = idx->refs;
+    spec.bound = bound;
+    spec.has_entries = idx->has_entries;
+    spec.sym = index_sym(idx);
+    spec.probed = probed;
+    JoinScratch J;
+    J.mode = PJ_MODE_BATCHED;
+    J.tp = tp;
+    run_candidates(P, idx->S, spec, J, stats, tm, st);
+    append_pairs(idx, P, J.out, J.naccepted, pairs, st);
+}
+
 // A small batch as one upload, five kernels and one read-back: the phases of a serving slot's
 // pipeline, whose sizes stay on the device, in buffers of the thread's workspace (the general path
 // reads sizes back between its phases, 25 launches and 6 synchronisations; 64 queries against 5x10^5
-// strings 315 -> 164 us).  Returns false, with nothing added, when the batch does not fit: more
-// than kSmallQueries queries or their selections, bytes, candidates or accepted candidates beyond
-// the buffers.  Candidates beyond the bucketing threshold are left to the general path, whose list
-// kernels are made for them.
+// strings 315 -> 164 us).  Returns false, with nothing done, when the batch does not fit: more
+// than kSmallQueries queries or their selections or bytes beyond the buffers.  What the device finds
+// too large goes on from where it is: more accepted candidates than one block sorts are sorted as the
+// general path sorts them, and from more candidates than the bucketing threshold on (whose list kernels
+// are made for them) the general path takes the hits.  (Begun anew there: 27,000 accepted 364 us, so
+// 227; 512 queries with 2x10^6 candidates 478 and 394.)
 constexpr int kSmallQueries = 512;
 constexpr uint64_t kSmallHits = 1ull << 18;
 
 static bool run_small_batch(const pj_index* idx, const pj_strings* Q, const int32_t* taus,
-                            std::vector<uint64_t>& pairs, pj_stats& stats, hipStream_t st)
+                            std::vector<uint64_t>& pairs, pj_stats& stats, hipStream_t st,
+                            const char* tune_cache)
 {
     const uint64_t cand_cap = std::min<uint64_t>(bucket_min_candidates(), 1ull << 20);
     if (Q->n > kSmallQueries || cand_cap == 0) return false;
-    const BatchLayout L = batch_layout(kSmallQueries, kSmallHits, cand_cap, kGraphSortCap);
+    const BatchLayout L = batch_layout(kSmallQueries, kSmallHits, cand_cap,
+                                       cand_cap + kGraphSortCap);
     thread_local std::vector<uint8_t> h_tables, h_result;
     h_tables.resize(L.tables_bytes + L.arena_bytes);
     h_result.resize(L.result_bytes);
@@ -103,7 +152,8 @@ static bool run_small_batch(const pj_index* idx, const pj_strings* Q, const int3
     int tmax = 0;
     for (int64_t q = 0; q < Q->n; ++q) tmax = std::max(tmax, taus[q]);
     GraphBatch G;
-    setup_graph_batch(idx, L, B, tmax, (int)Q->n, TuneParams{}, G);
+    const TuneParams tp = query_params(Q, tmax, tune_cache);
+    setup_graph_batch(idx, L, B, tmax, (int)Q->n, tp, G);
     Timer tm(st);
     const int e0 = tm.mark();
     hip_check(hipMemcpyAsync(B.tables, h_tables.data(), L.tables_bytes + (size_t)bytes,
@@ -120,9 +170,38 @@ static bool run_small_batch(const pj_index* idx, const pj_strings* Q, const int3
     const uint64_t* out = nullptr;
     unsigned long long flags = 0;
     const uint32_t m = batch_result(h_result.data(), part, &out, &flags);
-    if (flags != 0) return false;
-    read_batch_rest(h_result.data(), B.result, m, st);
-    pairs.insert(pairs.end(), out, out + m);
+    if (flags & 1) return false;             // (the selections bound the hits)
+    stats.ms_upload += tm.ms(e0, e1);
+    stats.ms_probe += tm.ms(e1, e2);
+    stats.ms_probe_kernel += tm.ms(e1, e2);
+    // the batch's strings as the general path has them (8: more accepted than one block sorts)
+    DevSet P;
+    P.n = Q->n;
+    P.perm = (int32_t*)(B.tables + L.off_perm);
+    if (flags != 0 && flags != 8) {
+        P.arena_bytes = bytes;
+        P.sarena = B.arena;
+        P.slen = (uint16_t*)(B.tables + L.off_slen);
+        P.lenstart = (int32_t*)(B.tables + L.off_lenstart);
+        P.gbase = (int64_t*)(B.tables + L.off_gbase);
+        memcpy(P.h_lenstart, h_tables.data() + L.off_lenstart, sizeof P.h_lenstart);
+        memcpy(P.h_gbase, h_tables.data() + L.off_gbase, sizeof P.h_gbase);
+        while (P.h_lenstart[P.lmin + 1] == 0) ++P.lmin;
+        P.lmax = P.lmin;
+        for (int l = P.lmin; l < kLenTab; ++l)
+            if (P.h_lenstart[l + 1] > P.h_lenstart[l]) P.lmax = l;
+        const auto* c = (const unsigned long long*)h_result.data();
+        const ProbedHits probed{B.hits, (const unsigned long long*)B.tables, {c[0], c[1], c[2]}};
+        join_queries(idx, P, (const int32_t*)(B.tables + L.off_qtau), tmax, 0, &probed, tp, pairs, stats,
+                     tm, st);
+        return true;
+    }
+    if (flags == 8) {
+        append_pairs(idx, P, B.acc, (uint64_t)part.accepted, pairs, st);
+    } else {
+        read_batch_rest(h_result.data(), B.result, m, st);
+        pairs.insert(pairs.end(), out, out + m);
+    }
     stats.hits += part.hits;
     stats.candidates += part.candidates;
     stats.key_collisions += part.key_collisions;
@@ -131,9 +210,6 @@ static bool run_small_batch(const pj_index* idx, const pj_strings* Q, const int3
     stats.cells += part.cells;
     stats.side_pairs += part.side_pairs;
     stats.verify_launches += part.candidates + part.key_collisions > 0 ? 1 : 0;
-    stats.ms_upload += tm.ms(e0, e1);
-    stats.ms_probe += tm.ms(e1, e2);
-    stats.ms_probe_kernel += tm.ms(e1, e2);
     stats.ms_verify += tm.ms(e2, e3);
     stats.ms_verify_kernel += tm.ms(e2, e3);
     return true;
@@ -162,31 +238,9 @@ void run_query_batch(const pj_index* idx, const pj_strings* Q, const int32_t* ta
     hip_check(hipMemcpyAsync(d_tau_id, taus, sizeof(int32_t) * (size_t)Q->n, hipMemcpyHostToDevice,
                              st), "upload taus");
     hip_check(launch_gather_i32(d_tau_id, P.perm, Q->n, d_tau, st), "gather taus");
-    ProbeSpec spec;
-    spec.self = false;
-    spec.tau = tmax;
-    spec.q_tau = d_tau;
-    spec.refs = idx->refs;
-    spec.bound = bound;
-    spec.has_entries = idx->has_entries;
-    spec.sym = index_sym(idx);
-    JoinScratch J;
-    J.mode = PJ_MODE_BATCHED;
-    J.tp = tune_lookup(tune_cache, tmax, Q->n ? (double)(Q->offsets[Q->n] - Q->offsets[0]) / (double)Q->n
-                                             : 0.0);
     Timer tm(st);
-    run_candidates(P, idx->S, spec, J, stats, tm, st);
-    int32_t *da = nullptr, *db = nullptr;
-    uint64_t M = finish_pairs(P, idx->S, false, J.out, J.naccepted, &da, &db, st);
-    std::vector<int32_t> ha(M), hb(M);
-    if (M) {
-        hip_check(hipMemcpyAsync(ha.data(), da, sizeof(int32_t) * M, hipMemcpyDeviceToHost, st), "d2h");
-        hip_check(hipMemcpyAsync(hb.data(), db, sizeof(int32_t) * M, hipMemcpyDeviceToHost, st), "d2h");
-    }
-    hip_check(hipStreamSynchronize(st), "sync");
-    pairs.reserve(pairs.size() + M);
-    for (uint64_t k = 0; k < M; ++k)
-        pairs.push_back(((uint64_t)(uint32_t)ha[k] << 32) | (uint32_t)hb[k]);
+    join_queries(idx, P, d_tau, tmax, bound, nullptr, query_params(Q, tmax, tune_cache), pairs, stats, tm,
+                 st);
 }
 
 // Substrings a length-n query with threshold tau selects against the lengths present in the
@@ -315,9 +369,9 @@ int pj_query(const pj_index* idx, const pj_strings* Q, const int32_t* taus, cons
         to_host(Q, on_dev, H);
         if (on_dev) validate_host_strings(&H.view, "Q");
         std::vector<uint64_t> pairs;
-        if (Q->n > 0 && !run_small_batch(idx, &H.view, taus, pairs, t_stats, st))
-            run_query_batch(idx, &H.view, taus, pairs, t_stats, st,
-                            opt ? opt->tune_cache : nullptr);
+        const char* tune_cache = opt ? opt->tune_cache : nullptr;
+        if (Q->n > 0 && !run_small_batch(idx, &H.view, taus, pairs, t_stats, st, tune_cache))
+            run_query_batch(idx, &H.view, taus, pairs, t_stats, st, tune_cache);
         uint64_t M = pairs.size();
         std::vector<int32_t> a(M), b(M);
         for (uint64_t k = 0; k < M; ++k) {

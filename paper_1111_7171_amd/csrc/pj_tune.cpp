@@ -68,15 +68,23 @@ bool in(const int (&opts)[N], int v)
 
 std::string arch_name()
 {
+    static std::mutex mu;
+    static std::map<int, std::string> names;     // by device: a call asks each time
     int dev = 0;
     hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) {
+    if (hipGetDevice(&dev) != hipSuccess) {
         (void)hipGetLastError();
         return "unknown";
     }
-    std::string a = prop.gcnArchName;
-    const size_t c = a.find(':');
-    return c == std::string::npos ? a : a.substr(0, c);
+    std::lock_guard<std::mutex> lk(mu);
+    std::string& name = names[dev];
+    if (!name.empty()) return name;
+    if (hipGetDeviceProperties(&prop, dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return "unknown";
+    }
+    const std::string a = prop.gcnArchName;
+    return name = a.substr(0, a.find(':'));
 }
 
 int length_bucket(double mean_len)
