@@ -822,14 +822,15 @@ __global__ __launch_bounds__(kBlock) void k_probe_long(ProbeParams P, Div div, P
                     q[u] = (q[u] >> 8) - rbase;
                     const uint32_t info = s_pair[q[u]];
                     const int len = (int)(info & 2047u);
-                    p[u] = (int)(info >> 16) - 128 + s;
-                    if (len == 0 || p[u] < 1 || p[u] > n - len + 1) continue;
+                    const int at = (int)(info >> 16) - 128 + s;
+                    if (len == 0 || at < 1 || at > n - len + 1) continue;
+                    p[u] = at;
                     uint64_t h = 0;
                     if (len <= exact_len)
                         for (int k = 0; k < len; ++k)
-                            h = (h << sym_bits) | (uint64_t)s_sym[s_b[p[u] - 1 + k]];
+                            h = (h << sym_bits) | (uint64_t)s_sym[s_b[at - 1 + k]];
                     else
-                        h = s_pre[p[u] - 1 + len] - s_pre[p[u] - 1] * s_pow[len - qlo];
+                        h = s_pre[at - 1 + len] - s_pre[at - 1] * s_pow[len - qlo];
                     key[u] = (uint64_t)s_grp[q[u]] << kHashBits | spread_code(len, h, exact_len);
                     const uint32_t k = (info >> 11) & 31u;
                     de[u] = P.dir[s_first[q[u]] + dir_entry(key[u], k)];
