@@ -497,7 +497,7 @@ hipError_t radix_sort_u32(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, ui
 constexpr int kHeadT = 512, kHeadItems = 16, kHeadTile = kHeadT * kHeadItems;
 
 // f(position among the heads, index, key) for every head, in order; *count = their number.
-// Element r * 256 + tid of a tile belongs to thread tid, so the reads are coalesced.
+// Element r * kHeadT + tid of a tile belongs to thread tid, so the reads are coalesced.
 template <typename F>
 __global__ __launch_bounds__(kHeadT) void k_compact_heads(const uint64_t* __restrict__ keys,
                                                           uint64_t n, uint32_t* ticket,
