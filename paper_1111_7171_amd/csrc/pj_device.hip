@@ -2865,11 +2865,16 @@ hipError_t launch_verify_long(const VerifyParams& V, uint64_t ncand, void* scrat
     const Div div = make_div(V.tau + 1);
     // rows of the first pass (10^5 long strings, ms in all with 16 / 32 / 64: tau = 8 0.16, 0.16,
     // 0.17; 16 0.30, 0.30, 0.31; 24 0.81, 0.77, 0.79; 32 2.88, 2.28, 2.41); PJ_LONG_PASSES sets
-    // them (tests and tuning; it changes no result)
+    // them (tests and tuning; it changes no result): the first of a comma list of row counts
     int K = 32;
     if (const char* e = getenv("PJ_LONG_PASSES")) {
-        K = atoi(e);
-        if (K < 1 || K > 4096) return hipErrorInvalidValue;
+        for (const char* c = e; *c;) {
+            const int v = atoi(c);
+            if (v < 1 || v > 4096) return hipErrorInvalidValue;
+            if (c == e) K = v;
+            while (*c && *c != ',') ++c;
+            if (*c == ',') ++c;
+        }
     }
     hipLaunchKernelGGL(k_verify_first, dim3(grid), dim3(64), 0, s, V, div, cands, slot_cnt, off, K,
                        left, left_cnt, right, right_cnt);
