@@ -1,4 +1,4 @@
-// pj_device.hip -- gfx950 kernels of libpassjoin (plain one-kernel-per-phase path).
+// pj_device.hip -- gfx950 kernels of libpassjoin: arena, index, probe, verification, output.
 //
 // Everything here is integer work on wave64: no MFMA (nothing is a dense contraction).  The
 // phases are HBM/L2-bound streaming (arena packing, index build, radix sort), random-access
@@ -985,8 +985,6 @@ __global__ __launch_bounds__(kBlock) void k_verify(VerifyParams V, Div div)
 
 constexpr int kWaveRounds = kBatchedRoundsMax;
 
-// Bucket of a hit: lists with at least `big` candidates after all smaller ones, each part in
-// slot order.
 // Bucket of a hit: small lists, then big ones (from 64 * kLenClasses on), each by the length
 // class of the list's strings and then by slot
 __device__ inline uint32_t hit_bucket(const Hit& v, uint32_t big)

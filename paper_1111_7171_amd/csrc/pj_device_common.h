@@ -312,13 +312,6 @@ __device__ inline void select_window(int method, int n, int l, int tau, int i, S
 // The base is odd and below 2^32, so a Horner step is two 32-bit multiplications.
 constexpr uint64_t kHashBase = 2654435761ull;
 
-__device__ inline uint64_t seg_hash(const uint8_t* w, int len)
-{
-    uint64_t h = 0;
-    for (int k = 0; k < len; ++k) h = h * kHashBase + (uint64_t)w[k] + 1ull;
-    return h;
-}
-
 __device__ inline uint64_t pow_hash(int len)   // B^(len-1)
 {
     uint64_t r = 1, b = kHashBase;
@@ -336,7 +329,7 @@ __device__ inline uint64_t roll_hash(uint64_t h, uint8_t out, uint8_t in, uint64
     return (h - ((uint64_t)out + 1ull) * top) * kHashBase + (uint64_t)in + 1ull;
 }
 
-// SplitMix64 finaliser (Steele, Lea, Flood 2014), used to spread hash bits.
+// SplitMix64 finaliser (Steele, Lea, Flood 2014): the words of a set's checksum.
 __host__ __device__ inline uint64_t mix64(uint64_t x)
 {
     x ^= x >> 30;

@@ -28,7 +28,6 @@ namespace pj {
 // Host results of at least this many bytes per array go to page-locked memory.
 constexpr size_t kPinnedOutputMin = 1u << 20;
 
-// Inverted lists with at least this many candidates are verified a 64-member segment per wave.
 // Below this many candidates the batched path verifies the hits in probe order, in one launch.
 constexpr uint64_t kBucketMinCandidates = 1ull << 20;
 
@@ -440,12 +439,6 @@ void sync_readback(hipStream_t st)
         }
         t_tape->pending.clear();
     }
-}
-
-void upload(void* dev, const void* host, size_t bytes, hipStream_t st)
-{
-    if (t_tape && t_tape->replay) return;
-    hip_check(hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, st), "upload");
 }
 
 void zero_words(void* dev, size_t bytes, hipStream_t st)

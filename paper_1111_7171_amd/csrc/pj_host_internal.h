@@ -81,10 +81,10 @@ int device_cus();
 // candidates from which the batched path buckets its hits (tests set it by the environment)
 uint64_t bucket_min_candidates();
 
-// Values the host reads back from the device to size the next phase.  A self-join plan
-// (pj_plan.cpp) runs the join once recording them in order, then captures the same sequence of
-// launches in a graph: while it captures, every read is served from the record, and nothing is
-// read back, uploaded or synchronised (the plan's own buffers already hold the uploaded tables).
+// Values the host reads back from the device to size the next phase.  A self-join plan runs the join
+// once recording them in order, then captures the same sequence of launches in a graph: while it
+// captures, every read is served from the record, and nothing is read back or synchronised (the
+// tables by length are made on the device, by the captured launches).
 struct ReadTape {
     bool replay = false;
     std::vector<uint8_t> bytes;
@@ -107,8 +107,6 @@ struct ReadbackScope {
         if (std::uncaught_exceptions() > uncaught) drop_readbacks();
     }
 };
-// host table -> device
-void upload(void* dev, const void* host, size_t bytes, hipStream_t st);
 // device memory = 0 with a kernel (bytes a multiple of 4)
 void zero_words(void* dev, size_t bytes, hipStream_t st);
 
@@ -201,11 +199,11 @@ bool index_has_entries(const pj_index* idx);
 int index_device(const pj_index* idx);
 int64_t query_selections(const pj_index* idx, int n, int tau);
 
-// Fixed-capacity buffers of one mixed-tau query batch run by launch_graph_batch: the layout of
-// the batch tables (counters, zero | nx | lenstart | gbase | perm | q_tau | slen, packed on the
-// host) and the arena, uploaded in one copy, and the device work buffers.  Used by the serving
-// slots' captured pipelines (allocated), by small pj_query calls (in the thread's workspace) and by
-// pj_query_noalloc (carved out of a static device array).
+// Fixed-capacity buffers of one mixed-tau query batch run by launch_graph_probe and
+// launch_graph_verify: the layout of the batch tables (counters, zero | nx | lenstart | gbase | perm |
+// q_tau | slen, packed on the host) and the arena, uploaded in one copy, and the device work buffers.
+// Used by the serving slots' captured pipelines (allocated), by small pj_query calls (in the thread's
+// workspace) and by pj_query_noalloc (carved out of a static device array).
 struct BatchLayout {
     int64_t qcap = 0, bcap = 0;             // queries, arena bytes
     uint64_t hcap = 0, cand_cap = 0, acc_cap = 0;

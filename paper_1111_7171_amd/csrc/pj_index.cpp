@@ -3,8 +3,8 @@
 // pj_build_index keeps the length-sorted arena of S and, for each tau in [tau_min, tau_max], the
 // sorted (key, g) entries, list records and directory of the even-partition segments (Sec. 3.1,
 // 3.2).
-// pj_query groups the queries by their threshold and runs the two-set join of Sec. 3.2 of each
-// group against the index of that threshold.
+// pj_query runs the two-set join of Sec. 3.2 of all queries in one pass, each against the index of its
+// own threshold.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -7,9 +7,10 @@
 //     two per-length tables, never gathered per string;
 //   * perm[g] = original id of sorted position g, slen[g] = its length;
 //   * segment index for one tau: (key, g) entries sorted by key, key = group(l, i) << 40 | code,
-//     group(l, i) = (l - (tau+1)) * (tau+1) + (i-1), code = the segment's bytes when it has at
-//     most 5 (exact) or the top 40 bits of a mixed polynomial hash otherwise; equal keys form one
-//     inverted list L_l^i(w) whose members are in ascending g (Sec. 3.2);
+//     group(l, i) = (l - (tau+1)) * (tau+1) + (i-1), code = the segment's packed symbol codes
+//     when they fit 40 bits (exact), or 40 bits of its polynomial hash, either spread by a
+//     multiplication; equal keys form one inverted list L_l^i(w) whose members are in ascending g
+//     (Sec. 3.2);
 //   * list records {key, start, count} in key order, and a directory into them by (l, i) group and
 //     leading code bits.
 #pragma once
