@@ -180,8 +180,8 @@ done:
 // left parts first, right parts of the survivors from a queue) with run_part in place of the banded
 // DP.  That DP took 171 VALU and 167 scalar operations per 64 candidates, each unit 85 % busy.  A
 // row is 6 VALU operations and two LDS reads here in place of some 27 at t = 4, and no string is
-// staged in LDS.  What is left is control and set-up by hit, about 70 operations of either kind a
-// step, and waiting (four waves of eight): a hit's set-up, 250 scalar operations when every wave did
+// staged in LDS.  What is left is control and set-up by hit, about 80 operations of either kind per 64
+// candidates (each unit 75 % busy), and waiting (four waves of eight): a hit's set-up, 250 scalar operations when every wave did
 // it for itself, is done for 64 hits at once, a lane each.  A block holds the tables once (3.8 KB up
 // to t = 3, 22.3 KB with t = 4) for 16 waves, so that two blocks fill a CU.  10^6 short strings at
 // tau = 4 (9.2 x 10^9 candidates): banded DP 46.3 ms, tables 27.1, set-up by lanes 24.6.

@@ -2253,8 +2253,8 @@ __device__ inline uint32_t far_lanes(int t) { return t < 8 ? 8u : t < 16 ? 16u :
 // Side 0: the left parts that k_verify_first left; those that pass become right tasks.  Side 1: the
 // right parts; those that pass are results.  A chunk is one slot's, so one threshold's.  In place of
 // twelve more passes by rows, each with its queue of band rows: first rows and this, 10^5 long
-// strings at tau = 16, 0.98 -> 0.28 ms; at tau = 32, where most candidates are not similar, 2.6 ->
-// 2.1.  Bound by the latency of a step's two reads and two lane exchanges.
+// strings at tau = 16, 0.98 -> 0.30 ms; at tau = 32, where most candidates are not similar, 2.85 ->
+// 2.3.  Bound by the latency of a step's two reads and two lane exchanges.
 __global__ __launch_bounds__(kBlock) void k_verify_far(VerifyParams V, Div div, int side,
                                                        const LongRec* __restrict__ tasks,
                                                        const uint32_t* __restrict__ counts,
