@@ -77,6 +77,28 @@ def load_traffic(kernel: str, sha: str, workload: str):
     return e.get("bytes_per_launch")
 
 
+def lane_cands(cache, tau: int, bucket: int) -> int:
+    """List-segment candidates per lane that a tune cache file sets (default 1)."""
+    lanes, version = 1, ""
+    if cache and os.path.exists(cache):
+        with open(cache) as f:
+            for ln in f:
+                w = ln.split()
+                if ln.startswith("#"):
+                    version = ln
+                elif "cache v4" in version and len(w) == 10 and (int(w[1]), int(w[2])) == (tau, bucket):
+                    lanes = int(w[7])
+    return lanes
+
+
+def list_kernel(tau: int, longest: int, lanes: int) -> str:
+    """The list-segment kernel of a join: the parts as table reads up to tau = 4 for length classes of
+    at most 47 bytes (lists of strings of up to 40 bytes are a class of their own), else the DP."""
+    if tau > 4 or lanes == 2:
+        return "k_verify_segs"
+    return "k_verify_auto" if longest <= 47 else "k_verify_auto, k_verify_segs"
+
+
 def cpu_info() -> dict:
     model = ""
     try:
@@ -473,14 +495,17 @@ def main():
     # long-string path (k_verify_far, indexed strings longer than 128 bytes) or k_verify_batched.
     # Algorithmic work = OPS_PER_CELL integer ops per DP cell of the rows a candidate's DP has
     # (counted on the device per kernel; the table and furthest-row kernels get a row's outcome
-    # without its cells).
+    # without its cells, so their fraction of the peak is not utilisation).
     other_ms = max(verify_ms - list_ms, 0.0)
+    longest = int(col.lengths().max(initial=0))
     if list_ms >= other_ms and list_launches > 0:
-        # (tau <= 4 and strings of up to 47 bytes: the parts as table reads)
-        rk = "k_verify_auto" if max(taus) <= 4 else "k_verify_segs"
+        # the kernel of the threshold whose lists took most
+        top = max(taus, key=lambda t: sum(s["ms_list_kernel"] for u, s in stats if u == t))
+        bucket = int(float(col.lengths().mean()) + 0.5).bit_length()
+        rk = list_kernel(top, longest, lane_cands(cache, top, bucket))
         k_ms, k_cells, k_launches = list_ms, list_cells, list_launches
     else:
-        rk = "k_verify_far" if int(col.lengths().max(initial=0)) > 128 else "k_verify_batched"
+        rk = "k_verify_far" if longest > 128 and max(taus) <= 32 else "k_verify_batched"
         k_ms, k_cells = other_ms, cells - list_cells
         k_launches = len(stats)      # one verification call per self-join
     per_launch_s = k_ms / 1e3 / max(k_launches, 1)
@@ -524,6 +549,7 @@ def main():
             "frac": achieved / PEAK_INT32_TOPS,
             "traffic": traffic,
             "ops_per_cell": OPS_PER_CELL,
+            "cells_computed": rk in ("k_verify_segs", "k_verify_batched"),
             "launches": k_launches,
             "avg_launch_ms": per_launch_s * 1e3,
             "cells_per_launch": k_cells / max(k_launches, 1),
