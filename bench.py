@@ -498,7 +498,12 @@ def main():
     # without its cells, so their fraction of the peak is not utilisation).
     other_ms = max(verify_ms - list_ms, 0.0)
     longest = int(col.lengths().max(initial=0))
-    if list_ms >= other_ms and list_launches > 0:
+    if args.mode == P.MODE_PLAIN:
+        rk, k_ms, k_cells, k_launches = "k_verify", verify_ms, cells, len(stats)
+    elif args.mode == P.MODE_SHARE_PREFIX and min(taus) <= 8:
+        # (chains count their cells with the small lists')
+        rk, k_ms, k_cells, k_launches = "k_verify_chains", verify_ms, cells, len(stats)
+    elif list_ms >= other_ms and list_launches > 0:
         # the kernel of the threshold whose lists took most
         top = max(taus, key=lambda t: sum(s["ms_list_kernel"] for u, s in stats if u == t))
         bucket = int(float(col.lengths().mean()) + 0.5).bit_length()
@@ -549,7 +554,7 @@ def main():
             "frac": achieved / PEAK_INT32_TOPS,
             "traffic": traffic,
             "ops_per_cell": OPS_PER_CELL,
-            "cells_computed": rk in ("k_verify_segs", "k_verify_batched"),
+            "cells_computed": not any(k in rk for k in ("k_verify_auto", "k_verify_far")),
             "launches": k_launches,
             "avg_launch_ms": per_launch_s * 1e3,
             "cells_per_launch": k_cells / max(k_launches, 1),
