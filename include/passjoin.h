@@ -192,11 +192,14 @@ int pj_join(const pj_strings* R, const pj_strings* S, int32_t tau, const pj_opti
 typedef struct pj_index pj_index;
 
 /* Builds an index of S for every tau in [tau_min, tau_max] (0 <= tau_min <= tau_max <=
- * PJ_TAU_MAX).  S is copied to the device; the caller may release it after the call. */
+ * PJ_TAU_MAX).  S is copied to the device; the caller may release it after the call.
+ * opt->mem_budget_bytes bounds the index, the copy of host strings and the sorted keys of one
+ * threshold; the sorts' other scratch is not counted. */
 int pj_build_index(const pj_strings* S, int32_t tau_min, int32_t tau_max, const pj_options* opt,
                    pj_index** out);
 
-/* Number of strings and the tau range of an index (any pointer may be NULL). */
+/* Number of strings and the tau range of an index, and the device memory that its blocks hold (any
+ * pointer may be NULL). */
 int pj_index_info(const pj_index* idx, int64_t* n, int32_t* tau_min, int32_t* tau_max,
                   int64_t* device_bytes);
 
